@@ -17,8 +17,7 @@
  * Conventions
  *  - Every pointer named *_d is device memory owned by the caller.  The
  *    library allocates device memory of its own only for the draft-training
- *    state (msd_train_*); the rocBLAS handle of the prompt GEMMs works in
- *    workspace carved from the caller's buffer.  *_h pointers are host.
+ *    state (msd_train_*).  *_h pointers are host.
  *  - Weights are bfloat16 (raw 16-bit patterns), row-major [out][in], no
  *    biases.  Norm gains are bfloat16 [d].
  *  - All device work is enqueued on the stream given to msd_create, in order.
@@ -161,16 +160,7 @@ int msd_workspace_size(const msd_model_desc* m, const msd_limits* lim, size_t* b
  * returns, the library reads the embedding table, the norm gains and the
  * packed copies only: the row-major matrices may be released; every other
  * pointer must stay valid until msd_destroy.
- * When the limits allow passes over more than 256 rows (a prompt of
- * max_prompt rows, or max_batch trees of max_tree nodes), the GEMMs of such
- * passes run on rocBLAS (bf16 inputs, float32 results) in launches of up to
- * 1024 rows (a last launch of 64 rows or fewer takes the library's own
- * kernels), against a row-major copy of one weight at a time that the
- * library unpacks into the workspace: msd_create then also creates a rocBLAS
- * handle on the stream, gives it a 32 MB workspace carved from
- * bufs->workspace, and runs the prompt GEMM shapes once so that rocBLAS
- * loads their kernels here rather than in the first msd_prefill.
- * MSD_ERR_HIP if the handle cannot be set up. */
+ */
 int msd_create(const msd_model_desc* m, const msd_limits* lim,
                const msd_target_weights* tw, const msd_draft_weights* dw,
                const msd_buffers* bufs, void* stream, msd_ctx** out);
@@ -209,21 +199,13 @@ enum { MSD_DRAFT_VISUAL_EMBEDDING = 0, MSD_DRAFT_VISUAL_FEATURE = 1 };
 int msd_set_draft_input(msd_ctx* ctx, int visual_input);
 
 /*
- * Where msd_prefill's many-row products find the target's weights (the
- * prompt forward of Sec. 3.1; msd_train_accumulate's target forward takes
- * the same path).  enable != 0: the rocBLAS products (see msd_create)
- * read the row-major matrices given to msd_create (wo, w_gate, w_up and
- * w_down of every target layer) in place, instead of first unpacking each
- * packed copy into a workspace slot (a 640-row
- * LLaVA-1.5-7B-shaped prefill: 29.3 -> 25.1 ms).  Those matrices must then
- * stay valid and unchanged until msd_destroy or a call with enable = 0.
- * The q|k|v product keeps its unpacked, stacked copy (one product over all
- * three fills the GPU better than three), and so do the draft layer and
- * f_down (draft training rewrites their packed copies).  Results equal the
- * default path's bit for bit: the same rocBLAS products of the same
- * shapes on the same values.  Takes effect at the next prompt; enqueues no
- * device work.  Default: disabled.  Errors: MSD_ERR_INVALID_ARG for a NULL
- * ctx.
+ * Tells the library that the row-major matrices given to msd_create (wo,
+ * w_gate, w_up and w_down of every target layer) stay valid and unchanged
+ * until msd_destroy or a call with enable = 0, so that products may read them
+ * in place.  Every product of this library reads the packed copies, whose
+ * layout its GEMM takes at every row count, so the call changes neither
+ * results nor time.  Default: disabled.  Errors: MSD_ERR_INVALID_ARG for a
+ * NULL ctx.
  */
 int msd_use_caller_weights(msd_ctx* ctx, int enable);
 

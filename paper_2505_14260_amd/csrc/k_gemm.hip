@@ -1,29 +1,14 @@
-// Thin-M GEMM on gfx950 MFMA: P_s[m][n] = sum_{k in chunk s} X[m][k] * W[n][k],
-// W in bfloat16 (packed, see below), X as split rows (bf16 hi + lo).
-//
-// The decode path multiplies a few dozen activation rows (tree nodes) by
-// large weight matrices, so the kernel is bound by streaming W from HBM once.
+// GEMM of the decode, prompt and training-target paths on gfx950 MFMA:
+// P_s[m][n] = sum over K chunk s of X[m][k] * W[n][k], W in bfloat16 (packed,
+// see below), X as split rows (bf16 hi + lo).
 //
 // Packed weights.  A weight [N][K] is stored as 64-row tiles times 128-column
-// blocks, each block 16 KB in the exact order the four waves of a workgroup
-// consume it: block (t, kb) at element ((t * nkt) + kb) * 8192, inside it
-// ((wave * 4 + c) * 64 + lane) * 8 + e holds W[t*64 + wave*16 + (lane & 15)]
+// blocks, each block 16 KB in the order in which fragments are read: block
+// (t, kb) at element ((t * nkt) + kb) * 8192, inside it
+// ((g16 * 4 + c) * 64 + lane) * 8 + e holds W[t*64 + g16*16 + (lane & 15)]
 // [kb*128 + 32*(lane >> 4) + 8*c + e].  Rows past N and columns past K are
-// zero.  Every wave load is then 1 KB contiguous and every workgroup streams
-// 64 KB spans, read with non-temporal buffer loads (WStream below).  Within
-// one MFMA the K index may
-// be any permutation shared by the two operands; the X fragments use the same
-// permutation.
-//
-// Work split.  K is cut into chunks of NKB blocks; a workgroup (4 waves) owns
-// one chunk and a strided set of tiles, stages its X chunk in LDS once
-// (XOR-swizzled, hi halves then lo halves) and then streams the W blocks of
-// its tiles through a ring of P register stages: having consumed a block it
-// loads the block P places further in its (tile, block) sequence.  The loop
-// has no branch on the data path and stores each tile's partial
-// unconditionally (padded rows go to a small sink), which keeps every weight
-// load in flight across tile boundaries.  Partials part[s][m][n] (float32) are summed in chunk order by
-// the kernel that consumes the product, so the result is deterministic.
+// zero.  Within one MFMA the K index may be any permutation shared by the two
+// operands; the X fragments use the same one.
 //
 // X arrives split by its producer, x = hi + lo with hi = bf16(x) and
 // lo = bf16(x - hi), so W x = W hi + W lo carries about 16 significant bits of
@@ -31,550 +16,265 @@
 // stack of layers, is far larger than the error of the weights' products).
 #include <hip/hip_ext.h>
 
+#include <algorithm>
+
 #include "msd_internal.h"
 
 namespace msd {
 
 namespace {
 
-constexpr int KB = 128;       // K elements per block
-constexpr int TILE_ROWS = 64;  // 4 waves x 16 rows
+constexpr int KB = 128;        // K elements per packed block
+constexpr int TILE_ROWS = 64;  // W rows per packed block
 constexpr int BLOCK_ELEMS = TILE_ROWS * KB;
-// 128-column blocks per K chunk: 8 for up to 32 rows (X chunk 64 or 128 KB
-// of LDS), 4 for 64 rows.  Longer chunks mean fewer partials to write and
-// re-read; the ring depth stays at RING blocks either way.
-constexpr int RING = 4;
-__host__ __device__ constexpr int chunk_blocks(int MT) { return MT <= 2 ? 8 : 4; }
-constexpr int PAIR_MAX_TILES = 5;  // tiles per workgroup of the two-chunk kernel
-// tiles per workgroup of the full-K kernel (k_gemm_fk): launched with 8 or
-// 10 (the registers of twelve tiles' accumulators spill)
-constexpr int FK_MIN_TILES = 8, FK_MAX_TILES = 10;
+constexpr int BLOCK_BYTES = BLOCK_ELEMS * 2;
+constexpr int RSRC_RAW = 0x00020000;  // raw buffer: 32-bit data format, stride 0
+constexpr int PAST = (int)0x80000000u;  // a byte offset past every buffer
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-MSD_DEV uint4 load_stream(const uint16_t* p) {
-  const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
-  return make_uint4(v.x, v.y, v.z, v.w);
-}
 
-// The weight stream of the thin GEMMs: raw buffer loads (32-bit data
-// format, stride 0) over one packed weight of `bytes` bytes, with the
-// non-temporal cache policy.  An element offset e < 0 reads 16 zero bytes:
-// the offset 2^31 lies past the buffer's range, so the load is answered
-// without a memory access (the ring's slots after the last tile and past K).
-// Measured at the 7B verify against the same stream as global loads: plain
-// or device/system-scope policies (sc1, sc0 sc1) 3.90 ms, non-temporal
-// global loads 3.71 ms, these 3.69 ms (draft 0.888 -> 0.877 ms).
-constexpr int WLOAD_POLICY = 2;  // nt; bit 0 would be sc0, bit 4 sc1
-struct WStream {
-  __amdgpu_buffer_rsrc_t r;
-  MSD_DEV WStream(const uint16_t* base, int bytes)
-      : r(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00020000)) {}
-  // e: element offset (a packed weight holds fewer than 2^30 elements)
-  MSD_DEV uint4 load(int e) const {
-    const int off = e >= 0 ? e * 2 : (int)0x80000000u;
-    const u32x4 v = __builtin_bit_cast(
-        u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, WLOAD_POLICY));
-    return make_uint4(v.x, v.y, v.z, v.w);
-  }
+// The kernel's arguments (the split: see GemmPlan).
+struct GemmArgs {
+  const uint16_t *X, *W, *W2;
+  int ldx, M, K;
+  int n_tiles, nkt;    // 64-row tiles and 128-column blocks of W
+  int n_mt, n_nt, nw;  // row tiles, column tiles per weight, weights
+  int S, bps;          // K chunks, blocks per chunk
+  float* part;
+  size_t part_split;
+  int ldp, off2;
 };
 
-// LDS X chunk: row m holds the chunk's columns in 16-byte units (8 bf16);
-// unit u of row m is stored at u ^ (m & 15) so that the 16 rows read by one
-// MFMA operand load hit different banks.
-MSD_DEV int xs_index(int m, int u, int upr) { return m * upr + (u ^ (m & 15)); }
+MSD_DEV constexpr int vmcnt_imm(int n) { return 0x0f70 | (n & 15) | ((n >> 4) << 14); }
 
-// MS (row split): a pass of 33-64 rows runs as two 32-row halves.  Workgroups
-// b and b + 8 (same XCD) take the two halves of one (chunk, tile set), so
-// the second one's weight blocks are L2 hits, and each workgroup streams its
-// weight blocks against a 32-row X chunk twice as long as a 64-row one.
-template <int MT, int NW, int NKB, int P, bool MS = false>
-__global__ __launch_bounds__(256) void k_gemm(GemmArgs a) {
-  static_assert(NKB % P == 0, "ring slots must divide the chunk");
-  extern __shared__ uint4 xs[];
-  constexpr int UPR = NKB * KB / 8;  // 16-byte units per LDS row
-  constexpr int LO = MT * 16 * UPR;  // offset of the lo halves
-  constexpr int NX = MT * 16 * UPR / 256;
-  constexpr int XB = NX < 16 ? NX : 16;  // staging batch (loads in flight)
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int i = lane & 15, g = lane >> 4;
-  const int S = a.S, G = a.G, K = a.K, nkt = a.nkt, n_tiles = a.n_tiles;
-  int unit = blockIdx.x, half = 0;
-  if (MS) {
-    half = (unit >> 3) & 1;
-    unit = ((unit >> 4) << 3) | (unit & 7);
-    if (unit >= S * G) return;
-  }
-  const int M = MS ? min(MT * 16, a.M - MT * 16 * half) : a.M;
-  const int s = unit % S, gi = unit / S;
-  const int n_my = gi < n_tiles ? (n_tiles - gi + G - 1) / G : 0;
-  if (n_my == 0) return;
-  const int kb0 = s * NKB;
-  const int k0 = kb0 * KB;
-  const uint16_t* const W = a.W;
-  const uint16_t* const W2 = a.W2;
-  const int lane_off = wave * (BLOCK_ELEMS / 4) + lane * 8;
-  const int tstride = nkt * BLOCK_ELEMS;
-  // the chunk's blocks; past K (last chunk) the loads read zeros, X being
-  // zero there too
-  const int nvb = min(NKB, nkt - kb0);
-
-  // X[0:MT*16, k0:k0+NKB*128) into LDS; rows past M and columns past K are
-  // zero.  The first batch's loads are issued before the weight ring's, so
-  // the ring's prefetch overlaps the staging.
-  uint4 xh[XB], xl[XB];
-  const int ldx = a.ldx;
-  const uint16_t* const X = a.X + (MS ? (size_t)half * MT * 16 * ldx : 0);
+// A workgroup of four waves computes 32 MT rows of X against 128 NTW rows of
+// W; each wave owns 32 NTW of them.  K runs in half blocks of 64 columns:
+//  - W fragments go from the packed layout straight to registers (a 64-row x
+//    128-column block holds the 16-byte units of a fragment contiguously, and
+//    no two waves of the workgroup share one); a register ring of RD half
+//    blocks keeps them in flight, each step refilled once its MFMAs are done;
+//  - the X rows of a half block go to LDS by buffer loads with the lds bit,
+//    one half block ahead (two buffers), or three ahead (NB = 4) where the
+//    weight stream is the bound: loads complete in order, so waiting for X
+//    one half ahead also drained the ring's older loads (27 rows, 7B-shaped
+//    down 19.9 -> 17.3 us, output 8.7 -> 7.8 us).
+//    LDS row m holds eight 16-byte units, unit u at u ^ (m & 7): the eight
+//    rows that one quarter of an operand read touches fall into distinct
+//    banks.  A load instruction writes 64 consecutive units (eight rows), so
+//    the swizzle is in the lanes' source addresses;
+//  - the fragments of step c + 1 are read from LDS under the MFMAs of step c,
+//    one read between MFMAs.
+// The LDS buffers are separate arrays and the loads into them are buffer
+// loads: the compiler then knows that the reads of one buffer need not wait
+// for the loads into the other (global loads to LDS count as flat accesses
+// and make it wait for everything in flight).  One barrier per half block:
+// before it every wave waits for its own loads into the next buffer; loads
+// issued after them stay in flight.
+//
+// Addresses.  Raw buffer loads check voffset against the record count less
+// soffset, so soffset always stays inside the buffer and whatever may fall
+// outside is in voffset: rows past M (the record count ends at row M),
+// columns past K and blocks past the chunk (voffset 2^31) read zeros.
+//
+// The sum of a row takes its products in the same order whatever MT and NTW
+// are; K chunks are summed by the consumer in chunk order.
+//
+// POL: cache policy of the weight loads.  A weight that only one row tile
+// reads is streamed non-temporally (policy 2: 27 rows, 7B-shaped gate+up
+// 35 -> 32 us); with more row tiles their reads meet in L2 (policy 0).
+//
+// Measured (one launch, weights from HBM; us), 7B-shaped q/k/v, output,
+// gate+up, down; before: weight-streaming kernels of up to 64 rows a launch,
+// rocBLAS from 129 prompt rows on (without unpacking its weights):
+//    27 rows   20.2,  9.3, 34.8, 19.1 -> 18.4,  7.7,  31.6, 16.8
+//    61 rows   25.2, 12.6, 38.5, 23.5 -> 22.4,  9.7,  38.0, 20.7
+//   108 rows   50,   25,   77,   47   -> 29,   15,    43,   31
+//   624 rows   77,   41,  218,  112   -> 100,  39,   172,   92  (1.1-1.3 PFLOP/s)
+//  1024 rows                             148,  55,   277,  138  (1.25-1.39 PFLOP/s)
+// Bound: HBM up to about 100 rows, then the matrix cores: at 624 rows they
+// are 82% busy inside a workgroup, at about 2.15 GHz.
+template <int MT, int NTW, int OCC, int POL, int RD, int NB>
+__global__ __launch_bounds__(256, OCC) void k_gemm(GemmArgs a) {
+  static_assert(NB == 2 || (NB == 4 && RD >= 2), "the first waits count on the ring's loads");
+  constexpr int XD = NB - 1;          // half blocks that X is loaded ahead
+  constexpr int BM = 32 * MT;
+  constexpr int ND = BM / 16;         // loads to LDS per wave and half block
+  constexpr int DPS = (ND + 1) / 2;   // of them per step (in steps 0 and 1)
+  // hi rows, then lo rows, 8 units each
+  __shared__ u32x4 xs0[BM * 16];
+  __shared__ u32x4 xs1[BM * 16];
+  __shared__ u32x4 xs2[NB > 2 ? BM * 16 : 1];
+  __shared__ u32x4 xs3[NB > 2 ? BM * 16 : 1];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // Workgroup i runs on XCD i mod 8: every XCD takes a contiguous range of
+  // the work items, row tiles innermost, so that the row tiles that read one
+  // piece of W run on one XCD and meet in its L2.
+  const int items = a.n_mt * a.n_nt * a.nw * a.S;
+  const int per = (items + 7) >> 3;
+  int t = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
+  if (((int)blockIdx.x >> 3) >= per || t >= items) return;
+  const int mt = t % a.n_mt;
+  t /= a.n_mt;
+  const int s = t % a.S;
+  t /= a.S;
+  const int w = t / a.n_nt, nt = t - w * a.n_nt;
+  const int m0 = mt * BM;
+  const int kb0 = s * a.bps, kb1 = min(a.nkt, kb0 + a.bps);
+  const int K = a.K, nkt = a.nkt;
+  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(w ? a.W2 : a.W), 0, a.n_tiles * nkt * BLOCK_BYTES, RSRC_RAW);
+  const int rowb = a.ldx * 2;
+  const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(a.X + (size_t)m0 * a.ldx), 0, min(a.M - m0, BM) * rowb, RSRC_RAW);
+  const int r = lane & 31, h = lane >> 5;
+  // MFMA step (sp, c) of a block takes the columns 64 sp + 32 h + 8 c + 0..7
+  // from lane half h; the unit of W row r lies at (16-row group, c, row in
+  // the group + 16 * column group 2 sp + h)
+  const int wvo = ((r >> 4) * 256 + (r & 15) + 16 * h) * 16;
+  const int n32 = (nt * 4 + wave) * NTW;  // first 32-row group of the wave
+  int wso[NTW];
 #pragma unroll
-  for (int q = 0; q < XB; ++q) {
-    const int e = threadIdx.x + 256 * q;
-    const int m = e / UPR, u = e - m * UPR;
-    const int col = k0 + 8 * u;
-    const bool ok = m < M && col < K;
-    const uint16_t* src = X + (ok ? (size_t)m * ldx + col : 0);
-    const uint4 h = *reinterpret_cast<const uint4*>(src);
-    const uint4 l = *reinterpret_cast<const uint4*>(src + (ok ? K : 0));
-    xh[q] = ok ? h : make_uint4(0, 0, 0, 0);
-    xl[q] = ok ? l : make_uint4(0, 0, 0, 0);
+  for (int j = 0; j < NTW; ++j) {
+    // groups past the weight (discarded) read its first tile
+    const int q = (n32 + j) >> 1 < a.n_tiles ? n32 + j : 0;
+    wso[j] = (q >> 1) * nkt * BLOCK_BYTES + (q & 1) * (BLOCK_BYTES / 2);
   }
-  const int wbytes = a.n_tiles * a.nkt * BLOCK_ELEMS * 2;
-  const WStream ws1(W, wbytes), ws2(NW == 2 ? W2 : W, wbytes);
-  uint4 ring[P][NW][4];
+  const auto load_w = [&](int kb, int sp, int c, int j) {
+    const int kc = min(kb, kb1 - 1);
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                         rw, kb < kb1 ? wvo : PAST,
+                                         wso[j] + kc * BLOCK_BYTES + c * 1024 + sp * 512, POL));
+  };
+  // Waves 0 and 1 load the hi halves, waves 2 and 3 the lo halves; load q of
+  // a wave fills the eight rows of group (wave & 1) ND + q, lane i the unit
+  // i & 7 of row i >> 3, i.e. source unit (i & 7) ^ (i >> 3).
+  const int xu = (lane & 7) ^ (lane >> 3);
+  const int xvo = ((wave & 1) * ND * 8 + (lane >> 3)) * rowb + xu * 16;
+  const int xso = wave >= 2 ? 2 * K : 0;
+  const auto load_x = [&](u32x4* b, int q, int kb, int sp) {
+    const int k0 = min(kb, kb1 - 1) * KB + sp * 64;
+    const int vo = (kb < kb1 && k0 + 8 * xu < K) ? xvo + q * 8 * rowb : PAST;
+    // the last half block may begin past K: soffset stays inside the buffer
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(
+        rx, (__attribute__((address_space(3))) void*)(b + (wave * ND + q) * 64), 16, vo,
+        xso + 2 * min(k0, K - 8), 0, 0);
+  };
+  u32x4 wr[RD][4][NTW];
+  f32x16 acc[NTW][MT];
 #pragma unroll
-  for (int p = 0; p < P; ++p) {
-    const int o = gi * tstride + (kb0 + p) * BLOCK_ELEMS + lane_off;
-    const bool in = p < nvb;
+  for (int j = 0; j < NTW; ++j)
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[j][m][e] = 0.f;
+#pragma unroll
+  for (int q = 0; q < ND; ++q) load_x(xs0, q, kb0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (NB > 2) {
+#pragma unroll
+    for (int q = 0; q < ND; ++q) load_x(xs1, q, kb0, 1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < ND; ++q) load_x(xs2, q, kb0 + 1, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int d = 0; d < RD; ++d)
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int j = 0; j < NTW; ++j) wr[d][c][j] = load_w(kb0 + d / 2, d & 1, c, j);
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm((XD - 1) * ND + 4 * NTW * RD));
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  u32x4 fx[2][2][MT];  // X fragments of two steps: hi, lo
+  const auto frags = [&](const u32x4* b, int c) {
+    const int u = r * 8 + ((4 * h + c) ^ (r & 7));
+#pragma unroll
+    for (int m = 0; m < MT; ++m) fx[c & 1][0][m] = b[m * 256 + u];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) fx[c & 1][1][m] = b[BM * 8 + m * 256 + u];
+  };
+  // Half block sp of block kb (X in b), loading the X of XD halves further
+  // into bn and refilling ring half rd with the W of RD halves further.
+  const auto half = [&](const u32x4* b, u32x4* bn, int rd, int kb, int sp) {
+    const int xkb = kb + (sp + XD) / 2, xsp = (sp + XD) & 1;
+    const int wkb = kb + (sp + RD) / 2, wsp = (sp + RD) & 1;
+    frags(b, 0);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      const int e = in ? o + c * 512 : -1;
-      ring[p][0][c] = ws1.load(e);
-      if (NW == 2) ring[p][NW - 1][c] = ws2.load(e);
-    }
-  }
+      if (c < 3) frags(b, c + 1);
 #pragma unroll
-  for (int q0 = 0; q0 < NX; q0 += XB) {
-    if (q0 > 0) {
+      for (int q = c * DPS; q < (c + 1) * DPS && q < ND; ++q) load_x(bn, q, xkb, xsp);
+      if (c > 0) {
 #pragma unroll
-      for (int q = 0; q < XB; ++q) {
-        const int e = threadIdx.x + 256 * (q0 + q);
-        const int m = e / UPR, u = e - m * UPR;
-        const int col = k0 + 8 * u;
-        const bool ok = m < M && col < K;
-        const uint16_t* src = X + (ok ? (size_t)m * ldx + col : 0);
-        const uint4 h = *reinterpret_cast<const uint4*>(src);
-        const uint4 l = *reinterpret_cast<const uint4*>(src + (ok ? K : 0));
-        xh[q] = ok ? h : make_uint4(0, 0, 0, 0);
-        xl[q] = ok ? l : make_uint4(0, 0, 0, 0);
+        for (int j = 0; j < NTW; ++j) wr[rd][c - 1][j] = load_w(wkb, wsp, c - 1, j);
       }
-    }
 #pragma unroll
-    for (int q = 0; q < XB; ++q) {
-      const int e = threadIdx.x + 256 * (q0 + q);
-      const int m = e / UPR, u = e - m * UPR;
-      const int xi = xs_index(m, u, UPR);
-      xs[xi] = xh[q];
-      xs[LO + xi] = xl[q];
-    }
-  }
-  __syncthreads();
-
-  const int ldp = a.ldp, off2 = a.off2;
-  float* const part =
-      a.part + (size_t)s * a.part_split + (MS ? (size_t)half * MT * 16 * ldp : 0);
-  float* const sink = a.sink + lane * 4;
-  for (int j = 0; j < n_my; ++j) {
-    const int tile = gi + j * G;
-    // the ring's refills for the next tile; after the last tile they read
-    // zeros (out-of-range offsets, no memory access)
-    const bool more = j + 1 < n_my;
-    const int t_base = tile * tstride + kb0 * BLOCK_ELEMS + lane_off;
-    const int tn_base = t_base + G * tstride;
-    f32x4 acc[NW][MT];
+      for (int hl = 0; hl < 2; ++hl)
 #pragma unroll
-    for (int w = 0; w < NW; ++w)
+        for (int m = 0; m < MT; ++m)
 #pragma unroll
-      for (int t = 0; t < MT; ++t) acc[w][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // passes of P blocks over the chunk; ring slot r of pass pp holds block
-    // pp + r and is refilled with the block P places further
-#pragma unroll 1
-    for (int pp = 0; pp < NKB; pp += P) {
+          for (int j = 0; j < NTW; ++j)
+            acc[j][m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                __builtin_bit_cast(bf16x8, wr[rd][c][j]),
+                __builtin_bit_cast(bf16x8, fx[c & 1][hl][m]), acc[j][m], 0, 0, 0);
+      // one LDS read and at most one load between the MFMAs of a fragment
+      const int loads = (c < 2 ? DPS : 0) + (c > 0 ? NTW : 0);
 #pragma unroll
-      for (int r = 0; r < P; ++r) {
-        const int p = pp + r;
-        uint4 fh[MT][4], fl[MT][4];
-#pragma unroll
-        for (int t = 0; t < MT; ++t)
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            const int xi = xs_index(t * 16 + i, p * 16 + 4 * g + c, UPR);
-            fh[t][c] = xs[xi];
-            fl[t][c] = xs[LO + xi];
-          }
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-#pragma unroll
-          for (int w = 0; w < NW; ++w)
-#pragma unroll
-            for (int t = 0; t < MT; ++t)
-              acc[w][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                  as_bf16x8(ring[r][w][c]), as_bf16x8(fh[t][c]), acc[w][t], 0, 0, 0);
-#pragma unroll
-          for (int w = 0; w < NW; ++w)
-#pragma unroll
-            for (int t = 0; t < MT; ++t)
-              acc[w][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                  as_bf16x8(ring[r][w][c]), as_bf16x8(fl[t][c]), acc[w][t], 0, 0, 0);
-        }
-        // refill: later in this tile, or in the next one
-        const int q = p + P;
-        const bool next = q >= NKB;
-        const int qb = next ? q - NKB : q;  // block of the chunk
-        const bool in = (!next || more) && qb < nvb;
-        const int o = (next ? tn_base : t_base) + qb * BLOCK_ELEMS;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const int e = in ? o + c * 512 : -1;
-          ring[r][0][c] = ws1.load(e);
-          if (NW == 2) ring[r][NW - 1][c] = ws2.load(e);
-        }
+      for (int i = 0; i < 2 * MT; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x8, NTW, 0);
+        if (c < 3) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        if (i < loads) __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
       }
+      __builtin_amdgcn_sched_barrier(0);
     }
-    // C layout of the 16x16 MFMA: lane holds column (lane & 15) = row m,
-    // register r holds W row 4*(lane/16) + r
-    const int n = tile * TILE_ROWS + wave * 16 + 4 * g;
 #pragma unroll
-    for (int w = 0; w < NW; ++w)
-#pragma unroll
-      for (int t = 0; t < MT; ++t) {
-        const int m = t * 16 + i;
-        float* dst = m < M ? part + (size_t)m * ldp + w * off2 + n : sink;
-        *reinterpret_cast<float4*>(dst) =
-            make_float4(acc[w][t][0], acc[w][t][1], acc[w][t][2], acc[w][t][3]);
-      }
-  }
-}
-
-// Units [256 q0, 256 (q0 + XB)) of the X chunk starting at block kb0 (rows
-// past M and columns past K are zero): load_x issues the loads, store_x
-// writes them to LDS (XOR-swizzled, hi then lo halves).
-template <int MT, int NKB, int XB>
-MSD_DEV void load_x(uint4 (&xh)[XB], uint4 (&xl)[XB], const uint16_t* X, int ldx, int M, int K,
-                    int kb0, int q0) {
-  constexpr int UPR = NKB * KB / 8;
-  const int k0 = kb0 * KB;
-#pragma unroll
-  for (int q = 0; q < XB; ++q) {
-    const int e = threadIdx.x + 256 * (q0 + q);
-    const int m = e / UPR, u = e - m * UPR;
-    const int col = k0 + 8 * u;
-    const bool ok = m < M && col < K;
-    const uint16_t* src = X + (ok ? (size_t)m * ldx + col : 0);
-    const uint4 h = *reinterpret_cast<const uint4*>(src);
-    const uint4 l = *reinterpret_cast<const uint4*>(src + (ok ? K : 0));
-    xh[q] = ok ? h : make_uint4(0, 0, 0, 0);
-    xl[q] = ok ? l : make_uint4(0, 0, 0, 0);
-  }
-}
-
-template <int MT, int NKB, int XB>
-MSD_DEV void store_x(uint4* xs, const uint4 (&xh)[XB], const uint4 (&xl)[XB], int q0) {
-  constexpr int UPR = NKB * KB / 8;
-  constexpr int LO = MT * 16 * UPR;
-#pragma unroll
-  for (int q = 0; q < XB; ++q) {
-    const int e = threadIdx.x + 256 * (q0 + q);
-    const int m = e / UPR, u = e - m * UPR;
-    const int xi = xs_index(m, u, UPR);
-    xs[xi] = xh[q];
-    xs[LO + xi] = xl[q];
-  }
-}
-
-// The same product with two K chunks per workgroup, for 64-row passes (whose
-// X chunk fills LDS at 4 blocks) and the widest 32-row ones: each workgroup
-// covers chunks 2s and 2s+1
-// of NT tiles, so it writes one partial per tile for the pair, half the
-// partials (and half the consumer's reads) of one chunk per workgroup.  The
-// weight ring runs through the sequence (chunk 0: tiles 0..NT-1, blocks of
-// each; then chunk 1 likewise) without a branch on its loads; every tile
-// keeps its accumulators across both chunks.  Between the chunks the
-// workgroup restages X in LDS; waiting for those loads also waits for the
-// ring's, once per workgroup.  Slots for tiles past the workgroup's last and
-// blocks past K read zeros.
-//
-// NC (3 or 4 instead of 2): more K chunks per workgroup, for 64-row passes
-// whose partials would otherwise cost more than the extra X restages.
-//
-// BO (block outer): within each chunk the sequence runs block by block over
-// the tiles, so a block's X fragments are read from LDS once for all of the
-// workgroup's tiles instead of once per tile.  Every output element sums the
-// same products in the same order either way.  It pays at 64 rows, where
-// the per-tile fragment reads (eight 16-byte LDS reads per MFMA row tile and
-// K step) held the kernel back: 61-row q/k/v 30.5 -> 25.2 us, down
-// 30.4 -> 24.9 us, gate+up 44.8 -> 41.5 us (7B-shaped), 64-row down
-// 43.8 -> 34.7 us (Qwen-shaped); the fragments' registers make the SwiGLU
-// pair spill from four tiles per workgroup on.
-template <int MT, int NW, int NKB, int P, int NT, bool BO, int NC = 2>
-__global__ __launch_bounds__(256) void k_gemm2(GemmArgs a) {
-  static_assert(NKB % P == 0, "ring slots must divide the chunk");
-  extern __shared__ uint4 xs[];
-  constexpr int UPR = NKB * KB / 8;
-  constexpr int LO = MT * 16 * UPR;
-  constexpr int SEQ = NC * NT * NKB;  // blocks of the workgroup's sequence
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int i = lane & 15, g = lane >> 4;
-  const int S = a.S, G = a.G, M = a.M, nkt = a.nkt, n_tiles = a.n_tiles;
-  const int s = blockIdx.x % S, gi = blockIdx.x / S;
-  const int n_my = gi < n_tiles ? min(NT, (n_tiles - gi + G - 1) / G) : 0;
-  if (n_my == 0) return;
-  const int kb0 = NC * s * NKB;
-  const uint16_t* const W = a.W;
-  const uint16_t* const W2 = a.W2;
-  const size_t lane_off = (size_t)wave * (BLOCK_ELEMS / 4) + lane * 8;
-  const int wbytes = a.n_tiles * a.nkt * BLOCK_ELEMS * 2;
-  const WStream ws1(W, wbytes), ws2(NW == 2 ? W2 : W, wbytes);
-  // element offset of sequence block q, or -1 for zeros; the
-  // sequence of chunk half h is tile by tile (q = (h NT + j) NKB + p), or
-  // block by block with BO (q = (h NKB + p) NT + j)
-  auto block_off = [&](int q) -> long long {
-    const int h = q / (NT * NKB);
-    const int j = BO ? q % NT : (q / NKB) % NT, p = BO ? (q / NT) % NKB : q % NKB;
-    const int kb = kb0 + h * NKB + p;
-    if (q >= SEQ || j >= n_my || kb >= nkt) return -1;
-    return ((long long)(gi + j * G) * nkt + kb) * BLOCK_ELEMS + (long long)lane_off;
+    for (int j = 0; j < NTW; ++j) wr[rd][3][j] = load_w(wkb, wsp, 3, j);
+    __builtin_amdgcn_sched_barrier(0);
+    // The next half's X was loaded XD - 1 halves ago, by the end of step 1:
+    // the refills of steps 2 and 3 and those after step 3 (3 NTW loads) and
+    // all loads of the halves since came later and may stay in flight.
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(3 * NTW + (XD - 1) * (ND + 4 * NTW)));
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
   };
-  constexpr int NX = MT * 16 * UPR / 256;  // X units per thread
-  static_assert(NX == 16, "X staging assumes 16 units per thread");
-  // the first chunk's X loads go out before the ring's, so that its LDS
-  // writes wait for them alone
-  uint4 xh[NX], xl[NX];
-  load_x<MT, NKB, NX>(xh, xl, a.X, a.ldx, M, a.K, kb0, 0);
-  uint4 ring[P][NW][4];
-#pragma unroll
-  for (int p = 0; p < P; ++p) {
-    const long long o = block_off(p);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int e = o >= 0 ? (int)o + c * 512 : -1;
-      ring[p][0][c] = ws1.load(e);
-      if (NW == 2) ring[p][NW - 1][c] = ws2.load(e);
-    }
-  }
-  store_x<MT, NKB, NX>(xs, xh, xl, 0);
-  __syncthreads();
-  f32x4 acc[NT][NW][MT];
-#pragma unroll
-  for (int j = 0; j < NT; ++j)
-#pragma unroll
-    for (int w = 0; w < NW; ++w)
-#pragma unroll
-      for (int t = 0; t < MT; ++t) acc[j][w][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // the ring slot of sequence block q is q % P whatever the chunk h (a
-  // chunk holds NT * NKB blocks, a multiple of P), so the chunk loop of the
-  // SwiGLU pair over more than two chunks stays rolled: unrolled, its
-  // registers spill (single weights keep it unrolled: 3 us faster on the 7B
-  // LM head at 61 rows)
-#pragma unroll((NC == 2 || NW == 1) ? NC : 1)
-  for (int h = 0; h < NC; ++h) {
-    if (h >= 1) {
-      // the next X chunk: its loads go out before the barrier (every wave
-      // done with the previous chunk), its LDS writes after
-      constexpr int XB = NX / 2;
-#pragma unroll
-      for (int q0 = 0; q0 < NX; q0 += XB) {
-        uint4 yh[XB], yl[XB];
-        load_x<MT, NKB, XB>(yh, yl, a.X, a.ldx, M, a.K, kb0 + h * NKB, q0);
-        if (q0 == 0) lds_barrier();
-        store_x<MT, NKB, XB>(xs, yh, yl, q0);
-      }
-      lds_barrier();
-    }
-#define MSD_GEMM2_STEP(Q, J, R)                                                               \
-  {                                                                                          \
-    const int q_ = (Q), j_ = (J), r_ = (R);                                                  \
-    _Pragma("unroll") for (int c = 0; c < 4; ++c) {                                          \
-      _Pragma("unroll") for (int w = 0; w < NW; ++w)                                         \
-      _Pragma("unroll") for (int t = 0; t < MT; ++t)                                         \
-        acc[j_][w][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(                             \
-            as_bf16x8(ring[r_][w][c]), as_bf16x8(fh[t][c]), acc[j_][w][t], 0, 0, 0);         \
-      _Pragma("unroll") for (int w = 0; w < NW; ++w)                                         \
-      _Pragma("unroll") for (int t = 0; t < MT; ++t)                                         \
-        acc[j_][w][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(                             \
-            as_bf16x8(ring[r_][w][c]), as_bf16x8(fl[t][c]), acc[j_][w][t], 0, 0, 0);         \
-    }                                                                                        \
-    const long long o_ = block_off(q_ + P);                                                  \
-    _Pragma("unroll") for (int c = 0; c < 4; ++c) {                                          \
-      const int e_ = o_ >= 0 ? (int)o_ + c * 512 : -1;                                       \
-      ring[r_][0][c] = ws1.load(e_);                                                         \
-      if (NW == 2) ring[r_][NW - 1][c] = ws2.load(e_);                                       \
-    }                                                                                        \
-  }
-#define MSD_GEMM2_FRAGS(PB)                                                                  \
-  _Pragma("unroll") for (int t = 0; t < MT; ++t)                                             \
-  _Pragma("unroll") for (int c = 0; c < 4; ++c) {                                            \
-    const int xi = xs_index(t * 16 + i, (PB) * 16 + 4 * g + c, UPR);                         \
-    fh[t][c] = xs[xi];                                                                       \
-    fl[t][c] = xs[LO + xi];                                                                  \
-  }
-    if constexpr (BO) {
-#pragma unroll
-      for (int p = 0; p < NKB; ++p) {
-        uint4 fh[MT][4], fl[MT][4];
-        MSD_GEMM2_FRAGS(p)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) MSD_GEMM2_STEP((h * NKB + p) * NT + j, j, (p * NT + j) % P)
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < NT; ++j)
-#pragma unroll
-        for (int p = 0; p < NKB; ++p) {
-          uint4 fh[MT][4], fl[MT][4];
-          MSD_GEMM2_FRAGS(p)
-          MSD_GEMM2_STEP((h * NT + j) * NKB + p, j, p % P)
-        }
-    }
-#undef MSD_GEMM2_STEP
-#undef MSD_GEMM2_FRAGS
-  }
-  const int ldp = a.ldp, off2 = a.off2;
-  float* const part = a.part + (size_t)s * a.part_split;
-  float* const sink = a.sink + lane * 4;
-#pragma unroll
-  for (int j = 0; j < NT; ++j) {
-    const int n = (gi + j * G) * TILE_ROWS + wave * 16 + 4 * g;
-#pragma unroll
-    for (int w = 0; w < NW; ++w)
-#pragma unroll
-      for (int t = 0; t < MT; ++t) {
-        const int m = t * 16 + i;
-        float* dst = (m < M && j < n_my) ? part + (size_t)m * ldp + w * off2 + n : sink;
-        *reinterpret_cast<float4*>(dst) =
-            make_float4(acc[j][w][t][0], acc[j][w][t][1], acc[j][w][t][2], acc[j][w][t][3]);
-      }
-  }
-}
-
-// Full-K variant for the widest single weights at 64 rows (LM heads of large
-// vocabularies, many tiles per workgroup): every workgroup covers all of K
-// for NT tiles, chunk by chunk, restaging X in LDS at each chunk and keeping
-// the tiles' accumulators in registers throughout.  It writes one partial
-// per tile (S = 1), where the chunked kernels write one per K chunk: at the
-// Qwen2.5-VL-7B-shaped LM head that is 39 MB instead of 272 MB per 64 rows,
-// and as much less for the consumer to read.
-//
-// With ten tiles' accumulators the X fragments of a whole block no longer
-// fit beside them, so a block is taken in two halves of its K steps (MFMA
-// steps c = 0, 1 and c = 2, 3), and the register ring holds half blocks:
-// 2P of them, as many bytes in flight as P whole blocks.  The ring runs
-// half by half over the tiles, q = ((c NKB + p) 2 + hf) NT + j, so one half's
-// fragments are read from LDS once for all NT tiles; 2 NKB NT is a multiple
-// of 2P, so every chunk uses the same ring slots.  A half block is two
-// 1 KB contiguous loads per wave.  Each restage waits for the ring's loads
-// in flight (loads complete in order), once per chunk.
-template <int MT, int NKB, int P, int NT>
-__global__ __launch_bounds__(256) void k_gemm_fk(GemmArgs a) {
-  constexpr int PH = 2 * P;           // half-block ring slots
-  constexpr int CSEQ = 2 * NKB * NT;  // half blocks per chunk
-  static_assert(CSEQ % PH == 0, "every chunk must start at ring slot 0");
-  extern __shared__ uint4 xs[];
-  constexpr int UPR = NKB * KB / 8;
-  constexpr int LO = MT * 16 * UPR;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int i = lane & 15, g = lane >> 4;
-  const int G = a.G, M = a.M, nkt = a.nkt, n_tiles = a.n_tiles;
-  const int gi = blockIdx.x;
-  const int n_my = gi < n_tiles ? min(NT, (n_tiles - gi + G - 1) / G) : 0;
-  if (n_my == 0) return;
-  const int n_ch = (nkt + NKB - 1) / NKB;
-  const uint16_t* const W = a.W;
-  const size_t lane_off = (size_t)wave * (BLOCK_ELEMS / 4) + lane * 8;
-  // element offset of sequence half block q, or -1 for zeros
-  const WStream ws1(W, a.n_tiles * a.nkt * BLOCK_ELEMS * 2);
-  auto half_off = [&](int q) -> long long {
-    const int c = q / CSEQ, r = q - c * CSEQ;
-    const int ph = r / NT, j = r - ph * NT;
-    const int kb = c * NKB + (ph >> 1);
-    if (j >= n_my || kb >= nkt) return -1;
-    return ((long long)(gi + j * G) * nkt + kb) * BLOCK_ELEMS + (long long)lane_off +
-           (ph & 1) * 1024;
-  };
-  constexpr int NX = MT * 16 * UPR / 256;
-  static_assert(NX == 16, "X staging assumes 16 units per thread");
-  uint4 xh[NX], xl[NX];
-  load_x<MT, NKB, NX>(xh, xl, a.X, a.ldx, M, a.K, 0, 0);
-  uint4 ring[PH][2];
-#pragma unroll
-  for (int q = 0; q < PH; ++q) {
-    const long long o = half_off(q);
-    ring[q][0] = ws1.load((int)o);
-    ring[q][1] = ws1.load(o >= 0 ? (int)o + 512 : -1);
-  }
-  store_x<MT, NKB, NX>(xs, xh, xl, 0);
-  __syncthreads();
-  f32x4 acc[NT][MT];
-#pragma unroll
-  for (int j = 0; j < NT; ++j)
-#pragma unroll
-    for (int t = 0; t < MT; ++t) acc[j][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if constexpr (NB == 2) {
 #pragma unroll 1
-  for (int ch = 0; ch < n_ch; ++ch) {
-    if (ch > 0) {
-      // the chunk's X: loads before the barrier (every wave done with the
-      // previous chunk), LDS writes after
-      constexpr int XB = NX / 2;
-#pragma unroll
-      for (int q0 = 0; q0 < NX; q0 += XB) {
-        uint4 yh[XB], yl[XB];
-        load_x<MT, NKB, XB>(yh, yl, a.X, a.ldx, M, a.K, ch * NKB, q0);
-        if (q0 == 0) lds_barrier();
-        store_x<MT, NKB, XB>(xs, yh, yl, q0);
-      }
-      lds_barrier();
+    for (int kb = kb0; kb < kb1; ++kb) {
+      half(xs0, xs1, 0, kb, 0);
+      half(xs1, xs0, 1 % RD, kb, 1);
     }
-#pragma unroll
-    for (int ph = 0; ph < 2 * NKB; ++ph) {
-      const int p = ph >> 1, hf = ph & 1;
-      uint4 fh[MT][2], fl[MT][2];
-#pragma unroll
-      for (int t = 0; t < MT; ++t)
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          const int xi = xs_index(t * 16 + i, p * 16 + 4 * g + 2 * hf + c, UPR);
-          fh[t][c] = xs[xi];
-          fl[t][c] = xs[LO + xi];
-        }
-#pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        const int r = (ph * NT + j) % PH;
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-#pragma unroll
-          for (int t = 0; t < MT; ++t)
-            acc[j][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                as_bf16x8(ring[r][c]), as_bf16x8(fh[t][c]), acc[j][t], 0, 0, 0);
-#pragma unroll
-          for (int t = 0; t < MT; ++t)
-            acc[j][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                as_bf16x8(ring[r][c]), as_bf16x8(fl[t][c]), acc[j][t], 0, 0, 0);
-        }
-        const long long o = half_off(ch * CSEQ + ph * NT + j + PH);
-        ring[r][0] = ws1.load((int)o);
-        ring[r][1] = ws1.load(o >= 0 ? (int)o + 512 : -1);
-      }
+  } else {
+#pragma unroll 1
+    for (int kb = kb0; kb < kb1; kb += 2) {
+      half(xs0, xs3, 0, kb, 0);
+      half(xs1, xs0, 1, kb, 1);
+      if (kb + 1 >= kb1) break;
+      half(xs2, xs1, 2 % RD, kb + 1, 0);
+      half(xs3, xs2, 3 % RD, kb + 1, 1);
     }
   }
-  const int ldp = a.ldp;
-  float* const part = a.part;
-  float* const sink = a.sink + lane * 4;
+  // C layout of the 32x32 MFMA: lane holds row m = lane & 31, register e the
+  // column 8 (e / 4) + 4 (lane / 32) + e % 4
+  float* const part = a.part + (size_t)s * a.part_split + (size_t)w * a.off2;
 #pragma unroll
-  for (int j = 0; j < NT; ++j) {
-    const int n = (gi + j * G) * TILE_ROWS + wave * 16 + 4 * g;
+  for (int j = 0; j < NTW; ++j) {
+    if ((n32 + j) >> 1 >= a.n_tiles) continue;
 #pragma unroll
-    for (int t = 0; t < MT; ++t) {
-      const int m = t * 16 + i;
-      float* dst = (m < M && j < n_my) ? part + (size_t)m * ldp + n : sink;
-      *reinterpret_cast<float4*>(dst) =
-          make_float4(acc[j][t][0], acc[j][t][1], acc[j][t][2], acc[j][t][3]);
+    for (int m = 0; m < MT; ++m) {
+      const int row = m0 + m * 32 + r;
+      if (row >= a.M) continue;
+      float* const d = part + (size_t)row * a.ldp + (n32 + j) * 32 + 4 * h;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<float4*>(d + 8 * q) = make_float4(
+            acc[j][m][4 * q], acc[j][m][4 * q + 1], acc[j][m][4 * q + 2], acc[j][m][4 * q + 3]);
     }
   }
 }
@@ -613,56 +313,9 @@ __global__ void k_unpack(const uint16_t* src, int N, int K, int nkt, size_t unit
         *reinterpret_cast<const uint4*>(src + q * 8);
 }
 
-// With timing events the launch carries them in its dispatch packet, so they
-// bracket the kernel's execution only.
-template <int MT, int NW>
-void launch_mt(dim3 grid, const GemmArgs& a, const GemmScratch& sc, hipStream_t st) {
-  constexpr int P = RING;
-  constexpr int NKB = chunk_blocks(MT);
-  const size_t lds = (size_t)MT * 16 * NKB * KB * 4;
-  if (sc.ev_start)
-    hipExtLaunchKernelGGL((k_gemm<MT, NW, NKB, P>), grid, dim3(256), lds, st, sc.ev_start,
-                          sc.ev_stop, 0, a);
-  else
-    hipLaunchKernelGGL((k_gemm<MT, NW, NKB, P>), grid, dim3(256), lds, st, a);
-}
-
-template <int MT, int NW, int NT, int NC = 2>
-void launch_pair(dim3 grid, const GemmArgs& a, const GemmScratch& sc, hipStream_t st) {
-  constexpr int P = RING;
-  constexpr int NKB = chunk_blocks(MT);
-  // block outer at 64 rows, but for the SwiGLU pair from four tiles on
-  constexpr bool BO = MT == 4 && (NW == 1 || NT <= 3);
-  const size_t lds = (size_t)MT * 16 * NKB * KB * 4;
-  if (sc.ev_start)
-    hipExtLaunchKernelGGL((k_gemm2<MT, NW, NKB, P, NT, BO, NC>), grid, dim3(256), lds, st,
-                          sc.ev_start, sc.ev_stop, 0, a);
-  else
-    hipLaunchKernelGGL((k_gemm2<MT, NW, NKB, P, NT, BO, NC>), grid, dim3(256), lds, st, a);
-}
-
-template <int NT>
-void launch_fk(dim3 grid, const GemmArgs& a, const GemmScratch& sc, hipStream_t st) {
-  constexpr int MT = 4, P = RING;
-  constexpr int NKB = chunk_blocks(MT);
-  const size_t lds = (size_t)MT * 16 * NKB * KB * 4;
-  if (sc.ev_start)
-    hipExtLaunchKernelGGL((k_gemm_fk<MT, NKB, P, NT>), grid, dim3(256), lds, st, sc.ev_start,
-                          sc.ev_stop, 0, a);
-  else
-    hipLaunchKernelGGL((k_gemm_fk<MT, NKB, P, NT>), grid, dim3(256), lds, st, a);
-}
-
-// The SwiGLU pair over more than two chunks takes at most four tiles per
-// workgroup (PAIR_NC_MAX_TILES): at five its registers spill.
-constexpr int PAIR_NC_MAX_TILES = 4;
-template <int MT, int NW, int NC = 2>
-void launch_pair_nt(int nt, dim3 grid, const GemmArgs& a, const GemmScratch& sc, hipStream_t st) {
-  if (nt == 1) launch_pair<MT, NW, 1, NC>(grid, a, sc, st);
-  else if (nt == 2) launch_pair<MT, NW, 2, NC>(grid, a, sc, st);
-  else if (nt == 3) launch_pair<MT, NW, 3, NC>(grid, a, sc, st);
-  else if (nt == 4) launch_pair<MT, NW, 4, NC>(grid, a, sc, st);
-  else if constexpr (NW == 1 || NC == 2) launch_pair<MT, NW, 5, NC>(grid, a, sc, st);
+MSD_DEV uint4 load_stream(const uint16_t* p) {
+  const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+  return make_uint4(v.x, v.y, v.z, v.w);
 }
 
 // Streaming read of a buffer with the weight stream's access pattern: every
@@ -691,6 +344,39 @@ __global__ __launch_bounds__(256) void k_stream_read(const uint16_t* buf, size_t
   if ((acc.x ^ acc.y ^ acc.z ^ acc.w) == 0x9E3779B9u) sink[blockIdx.x] = 1u;
 }
 
+// The launch function of one kernel variant.
+template <int MT, int NTW, int OCC, int RD, int NB>
+void launch_cfg(const GemmArgs& a, int wgs, const GemmScratch& sc, hipStream_t st) {
+  const dim3 grid(8 * ((wgs + 7) / 8));
+  // with timing events the launch carries them in its dispatch packet, so
+  // they bracket the kernel's execution only
+  const auto go = [&](void (*k)(GemmArgs)) {
+    if (sc.ev_start)
+      hipExtLaunchKernelGGL(k, grid, dim3(256), 0, st, sc.ev_start, sc.ev_stop, 0, a);
+    else
+      hipLaunchKernelGGL(k, grid, dim3(256), 0, st, a);
+  };
+  go(a.n_mt == 1 ? k_gemm<MT, NTW, OCC, 2, RD, NB> : k_gemm<MT, NTW, OCC, 0, RD, NB>);
+}
+
+// The variants.  eff: the share of a CU's matrix peak that one workgroup
+// reaches on it, fitted to launches of 14 weight shapes at 14 row counts (5
+// to 1568); larger tiles wait for less per MFMA.
+struct Config {
+  int MT, NTW;
+  float eff;
+  void (*launch)(const GemmArgs&, int, const GemmScratch&, hipStream_t);
+};
+constexpr Config CONFIGS[] = {
+    {1, 1, 0.30f, launch_cfg<1, 1, 4, 2, 4>}, {1, 2, 0.32f, launch_cfg<1, 2, 2, 2, 4>},
+    {2, 1, 0.51f, launch_cfg<2, 1, 2, 2, 4>}, {2, 2, 0.56f, launch_cfg<2, 2, 2, 2, 2>},
+    {2, 4, 0.68f, launch_cfg<2, 4, 1, 1, 2>}, {3, 2, 0.67f, launch_cfg<3, 2, 2, 1, 2>},
+    {4, 1, 0.49f, launch_cfg<4, 1, 2, 1, 2>}, {4, 2, 0.73f, launch_cfg<4, 2, 1, 1, 2>},
+    {4, 3, 0.76f, launch_cfg<4, 3, 1, 1, 2>}, {5, 2, 0.70f, launch_cfg<5, 2, 1, 1, 2>},
+    {5, 3, 0.75f, launch_cfg<5, 3, 1, 1, 2>}};
+constexpr int N_CONFIGS = sizeof(CONFIGS) / sizeof(CONFIGS[0]);
+constexpr int CUS = 256;
+
 }  // namespace
 
 size_t stream_span_bytes() { return (size_t)4 * BLOCK_ELEMS * sizeof(uint16_t); }
@@ -718,137 +404,49 @@ void launch_pack(const uint16_t* src, int N, int K, uint16_t* dst, hipStream_t s
                      nkt, units, dst);
 }
 
-GemmPlan plan_gemm(int M, int N, int K, int nw, int target_wgs) {
-  GemmPlan p;
-  const int mc = M < 64 ? M : 64;
-  p.MT = mc <= 16 ? 1 : (mc <= 32 ? 2 : 4);
-  p.nkt = (K + KB - 1) / KB;
-  p.nkb = chunk_blocks(p.MT);
-  p.S = (p.nkt + p.nkb - 1) / p.nkb;
-  p.n_tiles = (N + TILE_ROWS - 1) / TILE_ROWS;
-  // workgroups per chunk: about target_wgs in total, every workgroup of a
-  // chunk getting the same number of tiles
-  int G = (target_wgs + p.S - 1) / p.S;
-  if (G > p.n_tiles) G = p.n_tiles;
-  if (G < 1) G = 1;
-  int per = (p.n_tiles + G - 1) / G;
-  G = (p.n_tiles + per - 1) / per;
-  // one workgroup per CU: a few workgroups past the target would run as a
-  // second wave, so take more tiles per workgroup instead
-  while (p.S * G > target_wgs && G > 1) {
-    ++per;
-    G = (p.n_tiles + per - 1) / per;
-  }
-  p.G = G;
-  p.pair = 0;
-  p.per = per;
-  // Two K chunks per workgroup (the tiles' accumulators live in registers,
-  // at most PAIR_MAX_TILES of them).  64-row passes: when at least three
-  // quarters of the target workgroups stay busy.  32-row passes, whose
-  // partials are half as many per weight byte: the SwiGLU pair always (its
-  // 9.5 MB of partials at the 7B shape cost more than the idle CUs: gate+up
-  // 37.0 -> 36.1 us, its consumer about 1 us less), single weights only when
-  // the workgroup count stays within 5% and each workgroup has four tiles or
-  // more to amortise the mid-stream restage of X (the wide LM heads).
-  if ((p.MT == 4 || p.MT == 2) && p.S >= 2) {
-    const int S2 = (p.S + 1) / 2;
-    int G2 = (target_wgs + S2 - 1) / S2;
-    if (G2 > p.n_tiles) G2 = p.n_tiles;
-    int per2 = (p.n_tiles + G2 - 1) / G2;
-    G2 = (p.n_tiles + per2 - 1) / per2;
-    while (S2 * G2 > target_wgs && G2 > 1) {
-      ++per2;
-      G2 = (p.n_tiles + per2 - 1) / per2;
-    }
-    const bool busy = p.MT == 4 ? 4 * S2 * G2 >= 3 * target_wgs
-                                : (nw == 2 || (per2 >= 4 && 20 * S2 * G2 >= 19 * p.S * p.G));
-    if (per2 <= PAIR_MAX_TILES && busy) {
-      p.pair = 2;
-      p.S = S2;
-      p.G = G2;
-      p.per = per2;
-    }
-  }
-  // Full K per workgroup for the widest single weights at 64 rows: when
-  // every workgroup would take FK_MIN_TILES tiles or more at one chunk each,
-  // the X restage per chunk costs less than the chunk partials it saves
-  p.fk = 0;
-  if (p.MT == 4 && nw == 1) {
-    int nt = (p.n_tiles + target_wgs - 1) / target_wgs;
-    nt = (nt + 1) / 2 * 2;  // launched tile counts are even
-    if (nt >= FK_MIN_TILES && nt <= FK_MAX_TILES) {
-      p.fk = nt;
-      p.pair = 0;
-      p.S = 1;
-      p.G = (p.n_tiles + nt - 1) / nt;
-      p.per = nt;
-    }
-  }
-  p.nw = nw;
-  p.ldp = p.n_tiles * TILE_ROWS * nw;
-  p.off2 = p.n_tiles * TILE_ROWS;
-  p.ms = 0;
-  // 33-64 rows, single weights with at most two tiles per workgroup: the X
-  // chunk costs as much as the weight blocks streamed against it, so the
-  // pass runs as two 32-row halves with 8-block chunks (each workgroup
-  // streaming twice the weight bytes per X byte; the output projection at
-  // 61 rows 14.7 -> 12.0 us, Qwen2.5-VL-7B-shaped).  Wider weights stay
-  // whole: there the doubled weight stream per CU (the partner's blocks are
-  // L2 hits, but they still pass through the CU) costs more than the
-  // halved partials save.
-  if (p.MT == 4 && nw == 1 && !p.fk && p.per <= 2) {
-    const GemmPlan h = plan_gemm(32, N, K, nw, target_wgs / 2);
-    if (!h.pair && !h.fk) {
-      p = h;  // same ldp and off2: they depend on N and nw only
-      p.ms = 1;
-    }
-  }
-  // 64-row passes: four or three K chunks per workgroup where that writes
-  // fewer partials.  Single weights: on about as many workgroups, each with
-  // four tiles or more to amortise the X restage between chunks (the 7B LM
-  // head at 61 rows: 8 -> 2 partials, 66.6 -> 55.9 us); not with fewer
-  // tiles (7B down on 256 workgroups of two tiles: 24.9 -> 26.8 us) or
-  // fewer workgroups (7B q/k/v 27.2 -> 31.0 us on 192 instead of 256).  The
-  // SwiGLU pair: while three quarters of the target workgroups stay busy,
-  // since its consumer reads every partial of both weights (Qwen-shaped
-  // 61-row verify 4.71 -> 4.59 ms with 2 partials instead of 4).
-  if (p.MT == 4 && !p.fk && !p.ms) {
-    const int S1 = (p.nkt + p.nkb - 1) / p.nkb;
-    for (int nc = 4; nc >= 3; --nc) {
-      const int Sn = (S1 + nc - 1) / nc;
-      if (Sn >= p.S) continue;
-      int Gn = (target_wgs + Sn - 1) / Sn;
-      if (Gn > p.n_tiles) Gn = p.n_tiles;
-      int pern = (p.n_tiles + Gn - 1) / Gn;
-      Gn = (p.n_tiles + pern - 1) / pern;
-      while (Sn * Gn > target_wgs && Gn > 1) {
-        ++pern;
-        Gn = (p.n_tiles + pern - 1) / pern;
-      }
-      const bool keep = nw == 2 ? 4 * Sn * Gn >= 3 * target_wgs : 20 * Sn * Gn >= 19 * p.S * p.G;
-      const int max_tiles = nw == 2 ? PAIR_NC_MAX_TILES : PAIR_MAX_TILES;
-      if ((nw == 2 || pern >= 4) && pern <= max_tiles && keep) {
-        p.pair = nc;
-        p.S = Sn;
-        p.G = Gn;
-        p.per = pern;
-        break;
+
+// Picks the tile and the number of K chunks with the least estimated time:
+// the larger of the busiest CU's time (whole workgroups, each its MFMA cycles
+// at 2.4 GHz over the variant's eff plus 2.8 us to fill and drain), the
+// matrix rate of the whole chip (about 1.7 PFLOP/s) and the weight stream,
+// plus the partials' writing and their reading by the consumer.  On the 252
+// (shape, rows) pairs it was fitted to, its choice costs 0.3% over the best
+// variant measured for the pair on average, 6% at worst.
+GemmPlan plan_gemm(int M, int N, int K, int nw, size_t max_part) {
+  GemmPlan best{};
+  float best_us = 0.f;
+  const int nkt = (K + KB - 1) / KB, n_tiles = (N + TILE_ROWS - 1) / TILE_ROWS;
+  const int ldp = n_tiles * TILE_ROWS * nw;
+  const float weight_us = (float)N * K * nw * 2.f / 18.5e6f + 1.f;
+  for (int ci = 0; ci < N_CONFIGS; ++ci) {
+    const Config& c = CONFIGS[ci];
+    if ((c.MT - 1) * 32 >= M && c.MT > 1) continue;  // a row tile of padding only
+    const int n_mt = (M + 32 * c.MT - 1) / (32 * c.MT);
+    if (c.MT == 1 && n_mt > 1) continue;
+    // 32-bit byte offsets within a row tile
+    if (c.MT > 1 && (size_t)32 * c.MT * 4 * K >= ((size_t)1 << 31)) continue;
+    const int n_nt = (n_tiles * TILE_ROWS + 128 * c.NTW - 1) / (128 * c.NTW);
+    for (int s = 1; s <= MAX_K_CHUNKS && s <= nkt; ++s) {
+      const int bps = (nkt + s - 1) / s, S = (nkt + bps - 1) / bps;
+      if (S != s) continue;
+      if (s > 1 && (bps < 3 || (size_t)s * M * ldp > max_part)) break;
+      const int items = n_mt * n_nt * nw * s;
+      const float wg_us = bps * 8 * 2 * c.MT * c.NTW * 32 / (2400.f * c.eff) + 2.8f;
+      const float cu_us = (items + CUS - 1) / CUS * wg_us;
+      const float chip_us = (float)items * (c.MT * 32) * (c.NTW * 128) * (bps * 128.f) * 4e-6f / 1732.f;
+      const float part_us = (float)s * M * ldp * (0.9e-6f + 0.8e-6f) + 0.13f * s;
+      const float us = std::max({cu_us, chip_us, weight_us}) + part_us;
+      if (best_us == 0.f || us < best_us) {
+        best_us = us;
+        best = GemmPlan{ci, n_mt, n_nt, n_tiles, nkt, S, bps, items, ldp, n_tiles * TILE_ROWS};
       }
     }
   }
-  return p;
+  return best;
 }
 
-size_t gemm_part_floats(int M, int N, int K, int nw, int target_wgs) {
-  const GemmPlan p = plan_gemm(M, N, K, nw, target_wgs);
-  return (size_t)p.S * M * p.ldp;
-}
-
-void launch_gemm(const uint16_t* X, int ldx, int M, const uint16_t* W, const uint16_t* W2, int N,
-                 int K, float* part, float* sink, const GemmScratch& sc,
-                 hipStream_t st) {
-  const int nw = W2 ? 2 : 1;
-  const GemmPlan pl = plan_gemm(M, N, K, nw, sc.target_wgs);
+void launch_gemm(const GemmPlan& pl, const uint16_t* X, int ldx, int M, const uint16_t* W,
+                 const uint16_t* W2, int K, float* part, const GemmScratch& sc, hipStream_t st) {
   GemmArgs a{};
   a.X = X;
   a.ldx = ldx;
@@ -858,56 +456,16 @@ void launch_gemm(const uint16_t* X, int ldx, int M, const uint16_t* W, const uin
   a.W2 = W2;
   a.n_tiles = pl.n_tiles;
   a.nkt = pl.nkt;
+  a.n_mt = pl.n_mt;
+  a.n_nt = pl.n_nt;
+  a.nw = W2 ? 2 : 1;
   a.S = pl.S;
-  a.G = pl.G;
+  a.bps = pl.bps;
   a.part = part;
   a.part_split = (size_t)M * pl.ldp;
   a.ldp = pl.ldp;
   a.off2 = pl.off2;
-  a.sink = sink;
-  if (pl.ms) {
-    const dim3 grid(16 * ((pl.S * pl.G + 7) / 8));
-    constexpr int NKB = chunk_blocks(2);
-    const size_t lds = (size_t)2 * 16 * NKB * KB * 4;
-    if (sc.ev_start)
-      hipExtLaunchKernelGGL((k_gemm<2, 1, NKB, RING, true>), grid, dim3(256), lds, st, sc.ev_start,
-                            sc.ev_stop, 0, a);
-    else
-      hipLaunchKernelGGL((k_gemm<2, 1, NKB, RING, true>), grid, dim3(256), lds, st, a);
-    return;
-  }
-  const dim3 grid(pl.S * pl.G);
-  if (pl.fk) {
-    if (pl.fk == 8) launch_fk<8>(grid, a, sc, st);
-    else launch_fk<10>(grid, a, sc, st);
-    return;
-  }
-  if (pl.pair == 4) {
-    if (nw == 2) launch_pair_nt<4, 2, 4>(pl.per, grid, a, sc, st);
-    else launch_pair_nt<4, 1, 4>(pl.per, grid, a, sc, st);
-    return;
-  }
-  if (pl.pair == 3) {
-    if (nw == 2) launch_pair_nt<4, 2, 3>(pl.per, grid, a, sc, st);
-    else launch_pair_nt<4, 1, 3>(pl.per, grid, a, sc, st);
-    return;
-  }
-  if (pl.pair == 2) {
-    if (pl.MT == 2 && nw == 2) launch_pair_nt<2, 2>(pl.per, grid, a, sc, st);
-    else if (pl.MT == 2) launch_pair_nt<2, 1>(pl.per, grid, a, sc, st);
-    else if (nw == 2) launch_pair_nt<4, 2>(pl.per, grid, a, sc, st);
-    else launch_pair_nt<4, 1>(pl.per, grid, a, sc, st);
-    return;
-  }
-  if (nw == 2) {
-    if (pl.MT == 1) launch_mt<1, 2>(grid, a, sc, st);
-    else if (pl.MT == 2) launch_mt<2, 2>(grid, a, sc, st);
-    else launch_mt<4, 2>(grid, a, sc, st);
-  } else {
-    if (pl.MT == 1) launch_mt<1, 1>(grid, a, sc, st);
-    else if (pl.MT == 2) launch_mt<2, 1>(grid, a, sc, st);
-    else launch_mt<4, 1>(grid, a, sc, st);
-  }
+  CONFIGS[pl.config].launch(a, pl.items, sc, st);
 }
 
 }  // namespace msd

@@ -100,38 +100,33 @@ constexpr int MAX_VOCAB = 262144;  // 128 top-k slices of 2048 logits
 constexpr int POOL = 1024;              // dynamic-tree candidates per sequence
 constexpr int STAGE_INTS = 1 << 16;
 constexpr int ACC_BACK_INTS = 8 * MSD_MAX_TREE + 8 + 8 + 1;
-// GEMM launch shape: about one workgroup per CU streams best (more
-// concurrent weight streams per CU lower the achieved HBM bandwidth).
-constexpr int GEMM_WGS = 256;
-constexpr int CHUNK = 64;         // rows per weight-streaming GEMM launch
-constexpr int BIG_CHUNK = 1024;   // rows per many-row (rocBLAS) GEMM launch
-constexpr size_t BLAS_WS_BYTES = (size_t)32 << 20;  // rocBLAS's workspace
-// rocBLAS products whose hi and lo results together take at most this many
-// bytes (fewer than BIG_CHUNK rows), or BLAS_ONE_PRODUCT_FULL_BYTES (launches
-// of BIG_CHUNK rows), run as one product over 2M interleaved rows (see
-// blas_gemm)
-constexpr size_t BLAS_ONE_PRODUCT_BYTES = (size_t)192 << 20;
-constexpr size_t BLAS_ONE_PRODUCT_FULL_BYTES = (size_t)128 << 20;
-// Tree passes (verify, draft) over more rows than BIG_MIN_ROWS, and causal
-// passes (prompts, training sequences) over more than PROMPT_BIG_MIN_ROWS,
-// run their GEMMs on rocBLAS in launches of up to BIG_CHUNK rows (bf16
-// products with float32 results against row-major weights; a last launch of
-// CHUNK rows or fewer takes the weight-streaming kernels).  Shorter passes
-// run as weight-streaming launches of CHUNK rows.  7B-shaped prompts: 128
-// rows 9.0 ms streamed against 10.0 ms on rocBLAS, 192 rows 13.5 against
-// 11.1 ms, 256 rows 17.9 against 12.5 ms.  Target tree passes take the
-// prompt threshold when their output, gate, up and down products can read
-// the caller's row-major matrices in place (msd_use_caller_weights): the
-// Qwen2.5-VL-7B-shaped batch-4 verify (244 rows), whose 64-row launches
-// stream every weight four times, 17.2 -> 12.4 ms; unpacking the
-// weights on every verify instead would cost more than it saves (17.9 ms).
-constexpr int BIG_MIN_ROWS = 256;
-constexpr int PROMPT_BIG_MIN_ROWS = 128;
+// Rows per GEMM launch: a pass of more rows runs as launches of equal size.
+constexpr int MAX_LAUNCH_ROWS = 2048;
+constexpr int LM_ROWS = 64;  // rows per LM-head launch (its partials are the widest)
+// Floats of partials that a product may write to be split along K (40 MB;
+// launches over more rows than any verify without allocation takes: 128 MB).
+constexpr size_t PART_CAP = (size_t)10 << 20;
+constexpr size_t PART_CAP_MANY = (size_t)32 << 20;
+constexpr int NOALLOC_MAX_ROWS = 256;  // tree rows of msd_verify_noalloc
+size_t part_cap(int rows) { return rows <= NOALLOC_MAX_ROWS ? PART_CAP : PART_CAP_MANY; }
 
-// Rows per GEMM launch for a pass over `rows` rows (causal: a prompt pass;
-// in_place: the target's row-major matrices are readable in place).
-int row_chunk(int rows, bool causal, bool in_place) {
-  return rows > (causal || in_place ? PROMPT_BIG_MIN_ROWS : BIG_MIN_ROWS) ? BIG_CHUNK : CHUNK;
+// Floats of a partial row of the widest layer product.
+size_t layer_ldp(const msd_model_desc& m) {
+  auto pad = [](int n) { return (size_t)(n + 63) / 64 * 64; };
+  return std::max({pad((m.n_heads + 2 * m.n_kv_heads) * m.head_dim), pad(m.d_model),
+                   2 * pad(m.ffn_dim)});
+}
+
+// Rows per GEMM launch for a pass over `rows` rows.  Passes that
+// msd_verify_noalloc may run keep one launch's partials within PART_CAP, but
+// never take fewer than 64 rows a launch.
+int row_chunk(const msd_model_desc& m, int rows) {
+  if (rows <= NOALLOC_MAX_ROWS) {
+    if (rows <= 64 || rows * layer_ldp(m) <= PART_CAP) return rows;
+    return std::max(64, (int)(PART_CAP / layer_ldp(m)) / 32 * 32);
+  }
+  const int n = (rows + MAX_LAUNCH_ROWS - 1) / MAX_LAUNCH_ROWS;
+  return n == 1 ? rows : ((rows + n - 1) / n + 127) / 128 * 128;
 }
 
 // Bump allocator over the workspace (also used to size it).
@@ -151,7 +146,6 @@ struct Plan {
   int rows_max, lrows, ld_qkv;
   int att_items;  // tree-attention items (sequence, kv head, query tile)
   size_t attn_floats, part_floats;
-  size_t wrm_elems;  // row-major copy of the largest layer weight (0: no rocBLAS path)
 };
 
 Plan make_plan(const msd_model_desc& m, const msd_limits& lim) {
@@ -164,33 +158,12 @@ Plan make_plan(const msd_model_desc& m, const msd_limits& lim) {
   p.att_items = lim.max_batch * m.n_kv_heads * qtiles;
   p.attn_floats =
       attn_partial_floats(lim.max_batch, m.n_kv_heads, qtiles, ATT_MAX_CHUNKS, m.head_dim);
-  // GEMM partials of one launch of up to 64 rows, for the largest weight of
-  // the model (the plans change at 16, 32 and 64 rows; within each class the
-  // partials grow with the rows)
-  const int d = m.d_model, F = m.ffn_dim, hh = m.n_heads * m.head_dim;
-  p.part_floats = 0;
-  for (int mm : {16, 32, 64}) {
-    mm = std::min(mm, p.rows_max);
-    const size_t cand[6] = {gemm_part_floats(mm, p.ld_qkv, d, 1, GEMM_WGS),
-                            gemm_part_floats(mm, d, hh, 1, GEMM_WGS),
-                            gemm_part_floats(mm, F, d, 2, GEMM_WGS),
-                            gemm_part_floats(mm, d, F, 1, GEMM_WGS),
-                            gemm_part_floats(mm, d, 2 * d, 1, GEMM_WGS),
-                            gemm_part_floats(mm, m.vocab, d, 1, GEMM_WGS)};
-    p.part_floats = std::max(p.part_floats, *std::max_element(cand, cand + 6));
-  }
-  // full products of one rocBLAS launch (every GEMM but the LM head, which
-  // always runs in CHUNK-row launches), in either form of blas_gemm
-  p.wrm_elems = 0;
-  if (lim.max_prompt > PROMPT_BIG_MIN_ROWS || lim.max_batch * MSD_MAX_TREE > BIG_MIN_ROWS) {
-    const size_t big = std::min(BIG_CHUNK, p.rows_max);
-    auto ldp = [](int N, int nw) { return (size_t)(N + 63) / 64 * 64 * nw; };
-    const size_t w = std::max({ldp(p.ld_qkv, 1), ldp(d, 1), ldp(F, 2)});
-    p.part_floats = std::max(p.part_floats, big * w);
-    p.part_floats = std::max(p.part_floats,
-                             std::min(2 * big * w, BLAS_ONE_PRODUCT_BYTES / sizeof(float)));
-    p.wrm_elems = std::max({(size_t)p.ld_qkv * d, (size_t)d * hh, (size_t)F * d, (size_t)d * 2 * d});
-  }
+  // GEMM partials of one launch: S chunks of M rows, where S > 1 only within
+  // the cap and S <= MAX_K_CHUNKS
+  const size_t R = std::min(MAX_LAUNCH_ROWS, p.rows_max), ldp = layer_ldp(m);
+  const size_t lr = std::min(LM_ROWS, p.rows_max), lv = (size_t)(m.vocab + 63) / 64 * 64;
+  p.part_floats = std::max({R * ldp, std::min(MAX_K_CHUNKS * R * ldp, part_cap((int)R)),
+                            lr * lv, std::min(MAX_K_CHUNKS * lr * lv, PART_CAP)});
   return p;
 }
 
@@ -237,17 +210,11 @@ struct msd_ctx {
   // activation rows: split rows (bf16 hi + lo) for every MFMA input
   uint16_t *xn, *xb, *fcin, *q, *ao, *act, *h;
   float* part;
-  float* sink;          // GEMM rows past M
-  uint16_t* wrm;        // two row-major bf16 weight slots (rocBLAS prompt GEMMs)
-  const uint16_t* wrm_src[2] = {nullptr, nullptr};  // packed weight each slot holds
-  void* blas_ws;        // rocBLAS's workspace (BLAS_WS_BYTES)
-  rocblas_handle blas = nullptr;  // prompt GEMMs, when plan.wrm_elems > 0
-  // the target's prompt GEMMs read the caller's row-major matrices (layers)
-  // instead of unpacking their packed copies (msd_use_caller_weights)
-  bool caller_w = false;
-  ~msd_ctx() {
-    if (blas) (void)rocblas_destroy_handle(blas);
-  }
+  // plans of the products run so far (plan_gemm), by their sizes
+  struct PlanKey {
+    int M, N, K, nw;
+  };
+  std::vector<std::pair<PlanKey, GemmPlan>> gemm_plans;
   float* ssq;
   Rows rows;
   int *nxt, *prefix, *seq_ids;
@@ -260,7 +227,6 @@ struct msd_ctx {
   float *tk_val, *tk_lse;
   StaticSpec sp;
   DynPool pool;
-  GemmScratch gs;
   float *att_po, *att_ml, *tk_scratch;
   int* att_cnt;
   int* att_place;  // tree attention merged chunks that ran on different XCDs
@@ -345,9 +311,6 @@ size_t carve(msd_ctx* c, const msd_model_desc& m, const msd_limits& lim, char* b
   t->xb = cv.take<uint16_t>((size_t)R * 2 * d);
   t->fcin = cv.take<uint16_t>((size_t)R * 4 * d);
   t->part = cv.take<float>(p.part_floats);
-  t->sink = cv.take<float>(256);
-  t->wrm = p.wrm_elems ? cv.take<uint16_t>(2 * p.wrm_elems) : nullptr;
-  t->blas_ws = p.wrm_elems ? (void*)cv.take<char>(BLAS_WS_BYTES) : nullptr;
   t->ssq = cv.take<float>((size_t)R * ssq_blocks(d));
   t->q = cv.take<uint16_t>((size_t)R * 2 * m.n_heads * m.head_dim);
   t->ao = cv.take<uint16_t>((size_t)R * 2 * m.n_heads * m.head_dim);
@@ -493,144 +456,32 @@ void trace_events(msd_ctx* c, int kind, int M, int N, int K, hipEvent_t* e0, hip
   c->trace.push_back(r);
 }
 
-// The caller's row-major matrices of one many-row product (w2: the second
-// weight of the SwiGLU pair).
-struct RowMajorW {
-  const uint16_t *w, *w2;
-};
-
-// A many-row product on rocBLAS against row-major bf16 weights: the
-// caller's matrices (rm), or else each weight unpacked from the streaming
-// layout into a workspace slot (slot w for the pass's weight w; kept for the
-// pass's further row chunks, forgotten at the start of every layer pass).
-// Then bf16 GEMMs with float32 accumulation and results, issued column-major
-// (C^T = W X^T), give the consumer X_hi[m] . W[n] + X_lo[m] . W[n] (at
-// column w * off2 + n) in one of two forms:
-//  - one product over the 2M rows of K elements that the split rows are
-//    (row 2m the hi half of row m, row 2m + 1 its lo half; X's row stride
-//    must be 2K): C'[2m + h][n], two partials per row that the consumer
-//    sums in hi, lo order;
-//  - two products over the strided views X and X + K, the second adding to
-//    the first: C[m][n], one partial.
-// Either way the sum is hi + lo rounded once.  The one-product form runs
-// launches of fewer than BIG_CHUNK rows with results of at most
-// BLAS_ONE_PRODUCT_BYTES: its doubled row count tiles better (prefills of
-// 640 rows, LLaVA-1.5-7B-shaped, 25.3 -> 20.8 ms; 704 rows, 13B-shaped,
-// 46.8 -> 43.2 ms).  Full BIG_CHUNK launches take it for results of at most
-// BLAS_ONE_PRODUCT_FULL_BYTES, with the K slices below: 3,136 rows 7B-shaped
-// 107.9 -> 100.8 ms, 1,152 rows Qwen2.5-VL-7B-shaped 44.2 -> 37.8 ms.  Their
-// SwiGLU pairs (180 and 310 MB of results) keep two products: with the pair
-// included, before the K slices, 3,136 rows took 123.4 instead of 111.7 ms.
-// A one-product launch with few output tiles is split along K into ns
-// slices, one strided batch each (2 ns partials per row: the hi rows of
-// every slice, then the lo rows), so that the batches fill the GPU.
-#ifndef MAX_K_SLICES
-#define MAX_K_SLICES 8
-#endif
-int blas_gemm(msd_ctx* c, const uint16_t* X, int ldx, int M, const uint16_t* W,
-              const uint16_t* W2, int N, int K, int ldp, int off2, const RowMajorW* rm,
-              Parts* out) {
-  const bool one_product =
-      ldx == 2 * K && 2 * (size_t)M * ldp * sizeof(float) <=
-                          (M < BIG_CHUNK ? BLAS_ONE_PRODUCT_BYTES : BLAS_ONE_PRODUCT_FULL_BYTES);
-  const size_t rows = one_product ? 2 * (size_t)M : (size_t)M;
-  if ((!rm && (size_t)N * K > c->plan.wrm_elems) || rows * ldp > c->plan.part_floats)
-    return fail(c, MSD_ERR_INVALID_ARG, "internal: prompt GEMM exceeds its buffers");
-  // K slices: output tiles counted at 256 x 256; each slice at least 1024
-  // columns, a multiple of 8 (16-byte aligned slice starts), within the buffer
-  int ns = 1;
-  if (one_product) {
-    const int tiles = (int)((rows + 255) / 256) * ((N + 255) / 256);
-    ns = std::max(1, std::min({MAX_K_SLICES, 256 / std::max(tiles, 1), K / 1024}));
-    while (ns > 1 && (K % ns != 0 || (K / ns) % 8 != 0 ||
-                      rows * ldp * ns > c->plan.part_floats))
-      --ns;
-  }
-  const int nw = W2 ? 2 : 1, npad = off2;
-  const float one = 1.f, zero = 0.f;
-  for (int w = 0; w < (W2 ? 2 : 1); ++w) {
-    const uint16_t* A = nullptr;
-    if (rm) {
-      A = w ? rm->w2 : rm->w;
-    } else {
-      const uint16_t* src = w ? W2 : W;
-      uint16_t* wrm = c->wrm + (size_t)w * c->plan.wrm_elems;
-      if (c->wrm_src[w] != src) {
-        launch_unpack(src, N, K, wrm, c->st);
-        LAUNCHED(c);
-        c->wrm_src[w] = src;
-      }
-      A = wrm;
-    }
-    float* C = c->part + (size_t)w * off2;
-    if (ns > 1) {
-      // slice s of weight w at column (s nw + w) npad of rows of nw ns npad
-      const int ks = K / ns, ldc = nw * ns * npad;
-      const rocblas_status st = rocblas_gemm_strided_batched_ex(
-          c->blas, rocblas_operation_transpose, rocblas_operation_none, N, (int)rows, ks, &one,
-          A, rocblas_datatype_bf16_r, K, ks, X, rocblas_datatype_bf16_r, K, ks, &zero, C,
-          rocblas_datatype_f32_r, ldc, (rocblas_stride)nw * npad, C, rocblas_datatype_f32_r, ldc,
-          (rocblas_stride)nw * npad, ns, rocblas_datatype_f32_r, rocblas_gemm_algo_standard, 0, 0);
-      if (st != rocblas_status_success)
-        return fail(c, MSD_ERR_HIP,
-                    std::string("rocblas_gemm_strided_batched_ex: ") + rocblas_status_to_string(st));
-      continue;
-    }
-    for (int h = 0; h < (one_product ? 1 : 2); ++h) {
-      const rocblas_status st = rocblas_gemm_ex(
-          c->blas, rocblas_operation_transpose, rocblas_operation_none, N, (int)rows, K, &one, A,
-          rocblas_datatype_bf16_r, K, X + (size_t)h * K, rocblas_datatype_bf16_r,
-          one_product ? K : ldx, h ? &one : &zero, C, rocblas_datatype_f32_r, ldp, C,
-          rocblas_datatype_f32_r, ldp, rocblas_datatype_f32_r, rocblas_gemm_algo_standard, 0, 0);
-      if (st != rocblas_status_success)
-        return fail(c, MSD_ERR_HIP, std::string("rocblas_gemm_ex: ") + rocblas_status_to_string(st));
-    }
-  }
-  if (ns > 1)
-    *out = Parts{c->part, 2 * ns, (size_t)nw * npad, 2 * nw * ns * npad, npad};
-  else
-    *out = one_product ? Parts{c->part, 2, (size_t)ldp, 2 * ldp, off2}
-                       : Parts{c->part, 1, (size_t)M * ldp, ldp, off2};
-  return MSD_OK;
-}
-
-// The target layer's row-major matrices that the prompt products read in
-// place.  q, k and v stay unpacked: one product over the stacked q|k|v rows
-// keeps more of the GPU busy than three over the caller's separate matrices
-// (LLaVA-1.5-7B-shaped 640-row prefill 25.1 ms against 25.9 ms, 3,136 rows
-// 109.7 against 114.6 ms).
-struct LayerRowMajor {
-  RowMajorW o, gu, d;
-};
-LayerRowMajor layer_row_major(const msd_ctx* c, int l) {
-  const LayerW& w = c->layers[l];
-  return LayerRowMajor{{w.wo, nullptr}, {w.wg, w.wu}, {w.wd, nullptr}};
+// The plan of one launch, kept for the products of the same sizes that follow
+// (a pass repeats four sizes per layer).
+constexpr size_t MAX_PLANS = 256;
+const GemmPlan& gemm_plan(msd_ctx* c, int M, int N, int K, int nw, size_t cap) {
+  for (const auto& e : c->gemm_plans)
+    if (e.first.M == M && e.first.N == N && e.first.K == K && e.first.nw == nw) return e.second;
+  if (c->gemm_plans.size() >= MAX_PLANS) c->gemm_plans.clear();
+  c->gemm_plans.push_back({{M, N, K, nw}, plan_gemm(M, N, K, nw, cap)});
+  return c->gemm_plans.back().second;
 }
 
 // Partial products of rows [0, M) of the split rows X (row stride
 // ldx = 2K) against the packed weight W [N][K] (and W2); returns the view the
-// consumer sums.  Launches of more than CHUNK rows run on rocBLAS, against
-// rm's row-major matrices when given.
+// consumer sums.
 int gemm(msd_ctx* c, int kind, const uint16_t* X, int ldx, int M, const uint16_t* W,
-         const uint16_t* W2, int N, int K, Parts* out, const RowMajorW* rm = nullptr) {
-  if (M > CHUNK) {
-    if (kind == GK_LMHEAD || M > BIG_CHUNK)
-      return fail(c, MSD_ERR_INVALID_ARG, "internal: GEMM launch with too many rows");
-    if (!c->blas) return fail(c, MSD_ERR_INVALID_ARG, "internal: many-row GEMM without rocBLAS");
-    const int nt = (N + 63) / 64, nw = W2 ? 2 : 1;
-    return blas_gemm(c, X, ldx, M, W, W2, N, K, nt * 64 * nw, nt * 64, rm, out);
-  }
-  const GemmPlan pl = plan_gemm(M, N, K, W2 ? 2 : 1, c->gs.target_wgs);
+         const uint16_t* W2, int N, int K, Parts* out) {
+  const GemmPlan& pl = gemm_plan(c, M, N, K, W2 ? 2 : 1, part_cap(M));
   if ((size_t)pl.S * M * pl.ldp > c->plan.part_floats)
     return fail(c, MSD_ERR_INVALID_ARG, "internal: GEMM partials exceed their buffer");
-  GemmScratch gs = c->gs;
+  GemmScratch gs{};
   trace_events(c, kind, M, N, K, &gs.ev_start, &gs.ev_stop);
-  launch_gemm(X, ldx, M, W, W2, N, K, c->part, c->sink, gs, c->st);
+  launch_gemm(pl, X, ldx, M, W, W2, K, c->part, gs, c->st);
   LAUNCHED(c);
   *out = Parts{c->part, pl.S, (size_t)M * pl.ldp, pl.ldp, pl.off2};
   return MSD_OK;
 }
-
 
 // Key chunks of a tree-attention pass: each of a workgroup's TREE_WAVES
 // waves takes chunk_keys / TREE_WAVES keys (a multiple of 32); enough chunks
@@ -694,15 +545,12 @@ int forward_layers(msd_ctx* c, bool draft, int n_seq, int nq, int tree_R, int ma
   const int rows = n_seq * nq;
   const int d = m.d_model, H = m.n_heads, KV = m.n_kv_heads, hd = m.head_dim, F = m.ffn_dim;
   const int nl = draft ? 1 : m.n_layers;
-  const int ch = row_chunk(rows, tree_R < 0, c->caller_w && !draft && c->blas);
-  c->wrm_src[0] = c->wrm_src[1] = nullptr;
+  const int ch = row_chunk(m, rows);
   const int B = c->lim.max_batch, S = c->lim.max_seq;
   const size_t layer_kv = (size_t)B * KV * S * hd;
   for (int l = 0; l < nl; ++l) {
     const LayerW& w = draft ? c->dlayer : c->layers[l];
     const PackedLayer& pw = draft ? c->pdlayer : c->players[l];
-    const bool rmw = c->caller_w && !draft;
-    const LayerRowMajor rl = rmw ? layer_row_major(c, l) : LayerRowMajor{};
     uint16_t* kc = (draft ? c->dk : c->tk) + (size_t)l * layer_kv;
     uint16_t* vc = (draft ? c->dv : c->tv) + (size_t)l * layer_kv;
     Parts pt;
@@ -753,15 +601,14 @@ int forward_layers(msd_ctx* c, bool draft, int n_seq, int nq, int tree_R, int ma
     for (int m0 = 0; m0 < rows; m0 += ch) {
       const int mc = std::min(ch, rows - m0);
       TRY(gemm(c, GK_O, c->ao + (size_t)m0 * 2 * H * hd, 2 * H * hd, mc, pw.o, nullptr, d, H * hd,
-               &pt, rmw ? &rl.o : nullptr));
+               &pt));
       launch_resid(pt, mc, d, RN_ADD, c->x + (size_t)m0 * d, w.n2, c->xn + (size_t)m0 * 2 * d, nullptr,
                    c->ssq + (size_t)m0 * ssq_blocks(d), c->st);
       LAUNCHED(c);
     }
     for (int m0 = 0; m0 < rows; m0 += ch) {
       const int mc = std::min(ch, rows - m0);
-      TRY(gemm(c, GK_GATEUP, c->xn + (size_t)m0 * 2 * d, 2 * d, mc, pw.g, pw.u, F, d, &pt,
-               rmw ? &rl.gu : nullptr));
+      TRY(gemm(c, GK_GATEUP, c->xn + (size_t)m0 * 2 * d, 2 * d, mc, pw.g, pw.u, F, d, &pt));
       launch_silu(pt, row_norm(c, m0), mc, F, c->act + (size_t)m0 * 2 * F, c->st);
       LAUNCHED(c);
     }
@@ -769,8 +616,7 @@ int forward_layers(msd_ctx* c, bool draft, int n_seq, int nq, int tree_R, int ma
     const uint16_t* g_next = last ? final_g : c->layers[l + 1].n1;
     for (int m0 = 0; m0 < rows; m0 += ch) {
       const int mc = std::min(ch, rows - m0);
-      TRY(gemm(c, GK_DOWN, c->act + (size_t)m0 * 2 * F, 2 * F, mc, pw.d, nullptr, d, F, &pt,
-               rmw ? &rl.d : nullptr));
+      TRY(gemm(c, GK_DOWN, c->act + (size_t)m0 * 2 * F, 2 * F, mc, pw.d, nullptr, d, F, &pt));
       if (last && final_g) {
         // the final feature h is materialised (LM head input, draft input)
         launch_resid_norm(pt, 0, mc, d, RN_ADD, c->x + (size_t)m0 * d, final_g, m.norm_eps,
@@ -795,7 +641,7 @@ int forward_layers(msd_ctx* c, bool draft, int n_seq, int nq, int tree_R, int ma
 int draft_pass(msd_ctx* c, int n_seq, int nq, int tree_R, int max_ltot, const uint16_t* visual) {
   const int d = c->m.d_model;
   const int rows = n_seq * nq;
-  const int ch = row_chunk(rows, tree_R < 0, false);
+  const int ch = row_chunk(c->m, rows);
   Parts pt;
   for (int m0 = 0; m0 < rows; m0 += ch) {
     const int mc = std::min(ch, rows - m0);
@@ -863,8 +709,8 @@ int prompt_target(msd_ctx* c, int seq, int n, const int32_t* tokens_h,
 int draft_head(msd_ctx* c, int rows, int k) {
   const int d = c->m.d_model, V = c->m.vocab;
   Parts pt;
-  for (int m0 = 0; m0 < rows; m0 += CHUNK) {
-    const int mc = std::min(CHUNK, rows - m0);
+  for (int m0 = 0; m0 < rows; m0 += LM_ROWS) {
+    const int mc = std::min(LM_ROWS, rows - m0);
     TRY(gemm(c, GK_LMHEAD, c->xb + (size_t)m0 * 2 * d, 2 * d, mc, c->lm_p, nullptr, V, d, &pt));
     launch_topk(pt, mc, V, k, c->tk_idx + (size_t)m0 * k, c->tk_val + (size_t)m0 * k,
                 c->tk_lse + m0, nullptr, c->tk_scratch, c->st);
@@ -1268,35 +1114,6 @@ int train_pass(msd_ctx* c, int n, const void* visual_d, double* loss3) {
   return MSD_OK;
 }
 
-// rocBLAS loads the kernels of a GEMM shape on its first use (about 0.2 s
-// for a context's first prompt).  Run once here, on layer 0's weights and
-// whatever the activation buffers hold, each prompt GEMM shape at the row
-// counts this context's prompts will use: full BIG_CHUNK launches and the
-// launch of a max_prompt-row prompt's last chunk.  The results are
-// discarded.
-int warm_blas(msd_ctx* c) {
-  if (!c->blas) return MSD_OK;
-  const msd_model_desc& m = c->m;
-  const int d = m.d_model, F = m.ffn_dim, hh = m.n_heads * m.head_dim;
-  const int rows = c->lim.max_prompt;
-  std::vector<int> ms;
-  if (rows >= BIG_CHUNK) ms.push_back(BIG_CHUNK);
-  const int tail = rows % BIG_CHUNK;
-  if (rows > PROMPT_BIG_MIN_ROWS && tail > CHUNK) ms.push_back(tail);
-  const PackedLayer& p = c->players[0];
-  for (int M : ms) {
-    Parts pt;
-    TRY(gemm(c, GK_QKV, c->xn, 2 * d, M, p.qkv, nullptr, c->plan.ld_qkv, d, &pt));
-    TRY(gemm(c, GK_O, c->ao, 2 * hh, M, p.o, nullptr, d, hh, &pt));
-    TRY(gemm(c, GK_GATEUP, c->xn, 2 * d, M, p.g, p.u, F, d, &pt));
-    TRY(gemm(c, GK_DOWN, c->act, 2 * F, M, p.d, nullptr, d, F, &pt));
-    TRY(gemm(c, GK_FC, c->fcin, 4 * d, M, c->fc_p, nullptr, d, 2 * d, &pt));
-  }
-  c->wrm_src[0] = c->wrm_src[1] = nullptr;
-  HIPC(c, hipStreamSynchronize(c->st));
-  return MSD_OK;
-}
-
 }  // namespace
 
 extern "C" {
@@ -1360,18 +1177,6 @@ int msd_create(const msd_model_desc* m, const msd_limits* lim, const msd_target_
   c->dk = (uint16_t*)bufs->draft_k;
   c->dv = (uint16_t*)bufs->draft_v;
   carve(c, *m, *lim, (char*)bufs->workspace);
-  if (c->plan.wrm_elems) {
-    // prompt GEMMs on rocBLAS, on the context's stream, in a workspace carved
-    // from the caller's buffer (the context's destructor frees the handle)
-    rocblas_handle hb = nullptr;
-    const bool ok = rocblas_create_handle(&hb) == rocblas_status_success;
-    if (ok) c->blas = hb;
-    if (!ok || rocblas_set_stream(c->blas, c->st) != rocblas_status_success ||
-        rocblas_set_workspace(c->blas, c->blas_ws, BLAS_WS_BYTES) != rocblas_status_success) {
-      delete c;
-      return fail(nullptr, MSD_ERR_HIP, "rocBLAS handle for the prompt GEMMs");
-    }
-  }
   {
     hipError_t e = hipGetDevice(&c->device);
     void* sp = nullptr;
@@ -1383,9 +1188,6 @@ int msd_create(const msd_model_desc* m, const msd_limits* lim, const msd_target_
     }
     c->noalloc_base = static_cast<float*>(sp);
   }
-  c->gs.target_wgs = GEMM_WGS;
-  c->gs.ev_start = nullptr;
-  c->gs.ev_stop = nullptr;
   c->L.assign(lim->max_batch, 0);
   c->pend.assign(lim->max_batch, 0);
   c->ready.assign(lim->max_batch, 0);
@@ -1431,7 +1233,6 @@ int msd_create(const msd_model_desc* m, const msd_limits* lim, const msd_target_
     return MSD_OK;
   };
   r = init();
-  if (r == MSD_OK) r = warm_blas(c);
   if (r != MSD_OK) {
     g_err = c->err;
     (void)hipHostFree(c->stage);
@@ -1519,7 +1320,7 @@ int msd_set_draft_input(msd_ctx* c, int visual_input) {
 
 int msd_use_caller_weights(msd_ctx* c, int enable) {
   if (!c) return fail(nullptr, MSD_ERR_INVALID_ARG, "null context");
-  c->caller_w = enable != 0;
+  (void)enable;  // every product reads the packed weights
   return MSD_OK;
 }
 
@@ -1685,8 +1486,8 @@ int verify_impl(msd_ctx* c, int n_seq, const int32_t* seqs_h, const msd_tree* tr
   TRY(norm_rows(c, rows, c->layers[0].n1));
   TRY(forward_layers(c, false, n_seq, T, T, max_l + T, c->final_norm, c->h, nullptr));
   Parts pt;
-  for (int m0 = 0; m0 < rows; m0 += CHUNK) {
-    const int mc = std::min(CHUNK, rows - m0);
+  for (int m0 = 0; m0 < rows; m0 += LM_ROWS) {
+    const int mc = std::min(LM_ROWS, rows - m0);
     TRY(gemm(c, GK_LMHEAD, c->h + (size_t)m0 * 2 * d, 2 * d, mc, c->lm_p, nullptr, V, d, &pt));
     launch_topk(pt, mc, V, 1, argmax_d + m0, nullptr, nullptr,
                 logits_d ? logits_d + (size_t)m0 * V : nullptr, c->tk_scratch, c->st);
@@ -1698,21 +1499,27 @@ int verify_impl(msd_ctx* c, int n_seq, const int32_t* seqs_h, const msd_tree* tr
 }
 
 // Floats of GEMM partials a verify of `rows` tree rows writes (the largest
-// of its launches: q/k/v, output, gate+up, down and LM head, for each chunk
-// size of CHUNK-row launches).
-size_t verify_part_floats(const msd_model_desc& m, int rows) {
+// of its launches: q/k/v, output, gate+up, down and LM head).
+size_t verify_part_floats(msd_ctx* c, int rows) {
+  const msd_model_desc& m = c->m;
   const int d = m.d_model, F = m.ffn_dim, hh = m.n_heads * m.head_dim;
   const int qkv = (m.n_heads + 2 * m.n_kv_heads) * m.head_dim;
   size_t need = 0;
-  for (int mc : {std::min(CHUNK, rows), rows % CHUNK}) {
-    if (mc <= 0) continue;
-    for (size_t f : {gemm_part_floats(mc, qkv, d, 1, GEMM_WGS),
-                     gemm_part_floats(mc, d, hh, 1, GEMM_WGS),
-                     gemm_part_floats(mc, F, d, 2, GEMM_WGS),
-                     gemm_part_floats(mc, d, F, 1, GEMM_WGS),
-                     gemm_part_floats(mc, m.vocab, d, 1, GEMM_WGS)})
-      need = std::max(need, f);
-  }
+  const auto add = [&](int M, int N, int K, int nw) {
+    const GemmPlan& p = gemm_plan(c, M, N, K, nw, part_cap(M));
+    need = std::max(need, (size_t)p.S * M * p.ldp);
+  };
+  const auto each = [&](int chunk, auto&& f) {
+    f(std::min(chunk, rows));
+    if (rows > chunk && rows % chunk) f(rows % chunk);
+  };
+  each(row_chunk(m, rows), [&](int M) {
+    add(M, qkv, d, 1);
+    add(M, d, hh, 1);
+    add(M, F, d, 2);
+    add(M, d, F, 1);
+  });
+  each(LM_ROWS, [&](int M) { add(M, m.vocab, d, 1); });
   return need;
 }
 
@@ -1735,17 +1542,17 @@ int msd_verify_noalloc(msd_ctx* c, int n_seq, const int32_t* seqs_h, const msd_t
   TRY(check_verify(c, n_seq, seqs_h, trees_d, n_nodes, argmax_d, &max_l));
   const msd_model_desc& m = c->m;
   const int rows = n_seq * n_nodes;
-  if (rows > BIG_MIN_ROWS)
+  if (rows > NOALLOC_MAX_ROWS)
     return fail(c, MSD_ERR_INVALID_ARG,
-                "msd_verify_noalloc takes at most " + std::to_string(BIG_MIN_ROWS) +
+                "msd_verify_noalloc takes at most " + std::to_string(NOALLOC_MAX_ROWS) +
                     " tree rows per call (n_seq * n_nodes)");
   // the same attention chunking as msd_verify, so both compute identically
   const TreeChunks tc = plan_tree_chunks(m, n_seq, n_nodes, max_l + n_nodes,
                                          c->plan.attn_floats);
-  const size_t part = verify_part_floats(m, rows);
+  const size_t part = verify_part_floats(c, rows);
   const size_t att_o = tc.part_floats;
   const size_t att_ml = att_o / m.head_dim * 2 + 64;
-  const size_t tk = topk_scratch_floats(std::min(CHUNK, rows), m.vocab);
+  const size_t tk = topk_scratch_floats(std::min(LM_ROWS, rows), m.vocab);
   auto up = [](size_t f) { return (f + 63) / 64 * 64; };  // 256-byte steps
   const size_t need = up(part) + up(att_o) + up(att_ml) + up(tk);
   if (need * sizeof(float) > MSD_NOALLOC_SCRATCH_BYTES)

@@ -54,33 +54,21 @@ MSD_DEV bool any_tree_err(const int* tree_err, int n_seq) {
 namespace msd {
 
 // ---------------------------------------------------------------- GEMM ----
-// Partial products of a thin X (M split rows) against a packed bf16 weight
-// streamed from HBM: part[s][m][n] = sum over K-chunk s of X[m][k] * W[n][k]
-// (float32).  With a second weight W2 (the SwiGLU pair) its products go to
-// columns [off2, off2 + N).  The consumer sums the S chunks in order.
-struct GemmArgs {
-  const uint16_t* X;        // [M][ldx] split rows: hi at [k], lo at [K + k]
-  int ldx, M, K;
-  const uint16_t* W;        // packed (packed_elems(N, K) elements)
-  const uint16_t* W2;       // second packed weight or null
-  int n_tiles, nkt;         // 64-row tiles, 128-column blocks
-  int S, G;                 // K chunks, workgroups per chunk
-  float* part;              // partials of row 0 of this launch
-  size_t part_split;        // floats between consecutive chunks (M * ldp)
-  int ldp, off2;            // floats between rows; column offset of W2's products
-  float* sink;              // 1 KB written by padded rows
-};
-
+// Partial products of X (M split rows) against a packed bf16 weight:
+// part[s][m][n] = sum over K chunk s of X[m][k] * W[n][k] (float32).  With a
+// second weight W2 (the SwiGLU pair) its products go to columns
+// [off2, off2 + N).  The consumer sums the S chunks in order.
 struct GemmPlan {
-  int MT, nkb, S, G, nw, n_tiles, nkt, ldp, off2;
-  int pair;  // 2, 3 or 4: K chunks per workgroup (S counts their groups); 0: one
-  int fk;    // > 0: all of K per workgroup for fk tiles (S = 1)
-  int per;   // tiles per workgroup
-  int ms;    // 33-64 rows as two 32-row halves (MT, S and G of one half)
+  int config;         // kernel variant
+  int n_mt, n_nt;     // row tiles; column tiles per weight
+  int n_tiles, nkt;   // 64-row tiles and 128-column blocks of a weight
+  int S, bps;         // K chunks, blocks per chunk
+  int items;          // workgroups
+  int ldp, off2;      // floats between partial rows; column offset of W2
 };
+constexpr int MAX_K_CHUNKS = 16;
 
 struct GemmScratch {
-  int target_wgs;                // workgroups per launch
   hipEvent_t ev_start, ev_stop;  // when set: recorded around the kernel itself
 };
 
@@ -90,17 +78,17 @@ size_t packed_elems(int N, int K);
 void launch_pack(const uint16_t* src, int N, int K, uint16_t* dst, hipStream_t st);
 // Row-major bf16 [N][K] back from the packed layout (K a multiple of 8).
 void launch_unpack(const uint16_t* src, int N, int K, uint16_t* dst, hipStream_t st);
-GemmPlan plan_gemm(int M, int N, int K, int nw, int target_wgs);
-// floats of partials for M rows (M <= 64 per launch)
-size_t gemm_part_floats(int M, int N, int K, int nw, int target_wgs);
+// The split of a product of M rows; more than one K chunk only while the
+// partials (S * M * ldp floats) take at most max_part floats.
+GemmPlan plan_gemm(int M, int N, int K, int nw, size_t max_part);
 // Diagnostic: reads spans * stream_span_bytes() bytes of buf with the weight
 // stream's access pattern on wgs workgroups (sink: wgs words, never written
 // for zero-filled buffers).
 size_t stream_span_bytes();
 void launch_stream_read(const uint16_t* buf, size_t spans, int wgs, unsigned* sink,
                         hipStream_t st);
-void launch_gemm(const uint16_t* X, int ldx, int M, const uint16_t* W, const uint16_t* W2, int N,
-                 int K, float* part, float* sink, const GemmScratch& sc, hipStream_t st);
+void launch_gemm(const GemmPlan& pl, const uint16_t* X, int ldx, int M, const uint16_t* W,
+                 const uint16_t* W2, int K, float* part, const GemmScratch& sc, hipStream_t st);
 
 // Partial sums as seen by a consumer: value(m, n) = sum_s p[s*split + m*ld + n];
 // the second weight's products are at column n + off2.

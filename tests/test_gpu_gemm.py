@@ -1,0 +1,95 @@
+"""The packed-weight GEMM at the edges of its tiles and splits, through prompts
+of the C ABI: row counts on both sides of every row-tile height (32 to 160
+rows), of the passes that run as several launches, and widths with partial
+weight tiles and K blocks.  A row's keys and values depend on the rows before
+it only, so one oracle run over the longest prompt is the reference of all.
+
+Tolerance: keys and values are stored in bfloat16 (half a unit in the last
+place is 2^-9 of the value); one more unit for values near a rounding boundary
+gives 2^-7 of the row's largest magnitude.
+"""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import synth
+from synth.configs import TINY, WIDE
+from oracle import model as M
+from oracle import msd as O
+from parity import row_close
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+RTOL = 2.0 ** -7
+
+
+def text_prompt(wl, n):
+    rng = np.random.default_rng(wl.seed)
+    tokens = rng.integers(0, wl.dims.vocab, n).astype(np.int32)
+    return tokens, np.zeros(n, dtype=np.uint8), np.zeros((0, wl.dims.d_model), dtype=np.uint16)
+
+
+def rows_of(view, layer, n, transposed):
+    a = view[layer, 0, :, :, :n] if transposed else view[layer, 0, :, :n, :].transpose(1, 2)
+    bits = a.cpu().numpy().astype(np.int16).view(np.uint16)   # [KV, hd, n]
+    return M.widen(bits).transpose(2, 0, 1).reshape(n, -1)
+
+
+@pytest.mark.parametrize("dims_of, counts", [
+    # a partial 64-row weight tile (F = 2880) and a half K block in the down projection
+    (WIDE.dims, [1, 31, 32, 33, 64, 65, 95, 97, 128, 129, 160, 161, 255, 257, 319]),
+    # q/k/v of 12 tiles, an FFN of 688 (10 tiles and 48 rows; K blocks cut at 48 columns)
+    (TINY.dims, [5, 63, 66, 130, 192, 300]),
+    # K smaller than a block, one 40-wide remainder
+    (dataclasses.replace(WIDE.dims, d_model=168, n_heads=3, n_kv_heads=1, head_dim=64,
+                         ffn_dim=296, vocab=512), [3, 32, 65, 161]),
+], ids=["wide", "tiny", "narrow"])
+def test_prompt_rows_at_tile_edges(dims_of, counts):
+    from paper_2505_14260_amd.msd import Engine
+    wl = dataclasses.replace(TINY, dims=dims_of)
+    n_max = max(counts)
+    w = synth.make_target_weights(dims_of, wl.seed)
+    dr = synth.make_draft_weights(dims_of, w, wl.seed, "random")
+    tokens, vis, rows = text_prompt(wl, n_max)
+    st, _, _, _ = O.prefill(O.Models(dims_of, w, dr), tokens, vis, rows, n_max + 64)
+    eng = Engine(dims_of, w, dr, max_batch=1, max_seq=(n_max + 128) // 64 * 64, max_tree=64,
+                 max_prompt=n_max)
+    try:
+        tk, tv, _, _ = eng.kv_views()
+        for n in counts:
+            print(f"case: {n} rows, d {dims_of.d_model}", flush=True)
+            eng.prefill(0, tokens[:n], vis[:n], rows)
+            torch.cuda.synchronize()
+            for l in range(dims_of.n_layers):
+                for view, ref, tr in ((tk, st.kv.k, False), (tv, st.kv.v, True)):
+                    ok, err = row_close(rows_of(view, l, n, tr), ref[l, :n].reshape(n, -1), RTOL)
+                    assert ok, (n, l, tr, err)
+    finally:
+        eng.close()
+
+
+def test_prompt_of_several_launches():
+    """2,080 rows: two launches per product, the second shorter."""
+    from paper_2505_14260_amd.msd import Engine
+    dims = dataclasses.replace(TINY.dims, n_layers=2)
+    wl = dataclasses.replace(TINY, dims=dims)
+    n = 2080
+    w = synth.make_target_weights(dims, wl.seed)
+    dr = synth.make_draft_weights(dims, w, wl.seed, "random")
+    tokens, vis, rows = text_prompt(wl, n)
+    st, _, _, _ = O.prefill(O.Models(dims, w, dr), tokens, vis, rows, n + 64)
+    eng = Engine(dims, w, dr, max_batch=1, max_seq=n + 96, max_tree=64, max_prompt=n)
+    try:
+        print(f"case: {n} rows", flush=True)
+        eng.prefill(0, tokens, vis, rows)
+        torch.cuda.synchronize()
+        tk, tv, _, _ = eng.kv_views()
+        for l in range(dims.n_layers):
+            for view, ref, tr in ((tk, st.kv.k, False), (tv, st.kv.v, True)):
+                ok, err = row_close(rows_of(view, l, n, tr), ref[l, :n].reshape(n, -1), RTOL)
+                assert ok, (l, tr, err)
+    finally:
+        eng.close()
