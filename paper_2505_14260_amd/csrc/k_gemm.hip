@@ -43,7 +43,12 @@ struct GemmArgs {
   float* part;
   size_t part_split;
   int ldp, off2;
+  ArgmaxOut am;
 };
+
+// What a workgroup does with its sums: store them as partials, or (K whole in
+// one chunk, the LM head of a verify) reduce each row to its best column.
+enum Epilogue { EPI_PART, EPI_ARGMAX };
 
 MSD_DEV constexpr int vmcnt_imm(int n) { return 0x0f70 | (n & 15) | ((n >> 4) << 14); }
 
@@ -93,7 +98,7 @@ MSD_DEV constexpr int vmcnt_imm(int n) { return 0x0f70 | (n & 15) | ((n >> 4) <<
 //  1024 rows                             148,  55,   277,  138  (1.25-1.39 PFLOP/s)
 // Bound: HBM up to about 100 rows, then the matrix cores: at 624 rows they
 // are 82% busy inside a workgroup, at about 2.15 GHz.
-template <int MT, int NTW, int OCC, int POL, int RD, int NB>
+template <int MT, int NTW, int OCC, int POL, int RD, int NB, int EPI>
 __global__ __launch_bounds__(256, OCC) void k_gemm(GemmArgs a) {
   static_assert(NB == 2 || (NB == 4 && RD >= 2), "the first waits count on the ring's loads");
   constexpr int XD = NB - 1;          // half blocks that X is loaded ahead
@@ -262,19 +267,82 @@ __global__ __launch_bounds__(256, OCC) void k_gemm(GemmArgs a) {
   }
   // C layout of the 32x32 MFMA: lane holds row m = lane & 31, register e the
   // column 8 (e / 4) + 4 (lane / 32) + e % 4
-  float* const part = a.part + (size_t)s * a.part_split + (size_t)w * a.off2;
+  if constexpr (EPI == EPI_PART) {
+    float* const part = a.part + (size_t)s * a.part_split + (size_t)w * a.off2;
 #pragma unroll
-  for (int j = 0; j < NTW; ++j) {
-    if ((n32 + j) >> 1 >= a.n_tiles) continue;
+    for (int j = 0; j < NTW; ++j) {
+      if ((n32 + j) >> 1 >= a.n_tiles) continue;
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        const int row = m0 + m * 32 + r;
+        if (row >= a.M) continue;
+        float* const d = part + (size_t)row * a.ldp + (n32 + j) * 32 + 4 * h;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<float4*>(d + 8 * q) = make_float4(
+              acc[j][m][4 * q], acc[j][m][4 * q + 1], acc[j][m][4 * q + 2], acc[j][m][4 * q + 3]);
+      }
+    }
+  } else {
+    // the best (value, id) of each row over the workgroup's columns, as
+    // candidate nt of the row; a NaN ranks as -inf, the lowest id wins ties
+    __shared__ float sv[4][BM];
+    __shared__ int si[4][BM];
+    const int V = a.am.V;
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
       const int row = m0 + m * 32 + r;
-      if (row >= a.M) continue;
-      float* const d = part + (size_t)row * a.ldp + (n32 + j) * 32 + 4 * h;
+      float* const lg = a.am.logits && row < a.M ? a.am.logits + (size_t)row * V : nullptr;
+      float bv = -INFINITY;
+      int bi = NO_ID;
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        *reinterpret_cast<float4*>(d + 8 * q) = make_float4(
-            acc[j][m][4 * q], acc[j][m][4 * q + 1], acc[j][m][4 * q + 2], acc[j][m][4 * q + 3]);
+      for (int j = 0; j < NTW; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int n = (n32 + j) * 32 + 8 * q + 4 * h;
+          float v[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = acc[j][m][4 * q + e];
+          if (lg && a.am.vec) {  // V and the rows are multiples of 16 bytes
+            if (n < V) *reinterpret_cast<float4*>(lg + n) = make_float4(v[0], v[1], v[2], v[3]);
+          } else if (lg) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (n + e < V) lg[n + e] = v[e];
+          }
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float x = v[e] == v[e] ? v[e] : -INFINITY;
+            if (n + e < V && better(x, n + e, bv, bi)) {
+              bv = x;
+              bi = n + e;
+            }
+          }
+        }
+      const float ov = __shfl_xor(bv, 32);
+      const int oi = __shfl_xor(bi, 32);
+      if (better(ov, oi, bv, bi)) {
+        bv = ov;
+        bi = oi;
+      }
+      if (h == 0) {
+        sv[wave][m * 32 + r] = bv;
+        si[wave][m * 32 + r] = bi;
+      }
+    }
+    lds_barrier();
+    if ((int)threadIdx.x < BM && m0 + (int)threadIdx.x < a.M) {
+      float bv = sv[0][threadIdx.x];
+      int bi = si[0][threadIdx.x];
+#pragma unroll
+      for (int q = 1; q < 4; ++q)
+        if (better(sv[q][threadIdx.x], si[q][threadIdx.x], bv, bi)) {
+          bv = sv[q][threadIdx.x];
+          bi = si[q][threadIdx.x];
+        }
+      const size_t o = (size_t)(m0 + threadIdx.x) * a.n_nt + nt;
+      a.am.cand_v[o] = bv;
+      a.am.cand_i[o] = bi;
     }
   }
 }
@@ -356,24 +424,30 @@ void launch_cfg(const GemmArgs& a, int wgs, const GemmScratch& sc, hipStream_t s
     else
       hipLaunchKernelGGL(k, grid, dim3(256), 0, st, a);
   };
-  go(a.n_mt == 1 ? k_gemm<MT, NTW, OCC, 2, RD, NB> : k_gemm<MT, NTW, OCC, 0, RD, NB>);
+  constexpr int MANY = MT == 1 ? 2 : 0;  // cache policy with several row tiles
+  if (a.am.cand_v)
+    go(a.n_mt == 1 ? k_gemm<MT, NTW, OCC, 2, RD, NB, EPI_ARGMAX>
+                   : k_gemm<MT, NTW, OCC, MANY, RD, NB, EPI_ARGMAX>);
+  else
+    go(a.n_mt == 1 ? k_gemm<MT, NTW, OCC, 2, RD, NB, EPI_PART>
+                   : k_gemm<MT, NTW, OCC, MANY, RD, NB, EPI_PART>);
 }
 
 // The variants.  eff: the share of a CU's matrix peak that one workgroup
-// reaches on it, fitted to launches of 14 weight shapes at 14 row counts (5
-// to 1568); larger tiles wait for less per MFMA.
+// reaches on it, fitted to back-to-back launches of 14 weight shapes at 15 row
+// counts (1 to 1568); larger tiles wait for less per MFMA.
 struct Config {
   int MT, NTW;
   float eff;
   void (*launch)(const GemmArgs&, int, const GemmScratch&, hipStream_t);
 };
 constexpr Config CONFIGS[] = {
-    {1, 1, 0.30f, launch_cfg<1, 1, 4, 2, 4>}, {1, 2, 0.32f, launch_cfg<1, 2, 2, 2, 4>},
-    {2, 1, 0.51f, launch_cfg<2, 1, 2, 2, 4>}, {2, 2, 0.56f, launch_cfg<2, 2, 2, 2, 2>},
-    {2, 4, 0.68f, launch_cfg<2, 4, 1, 1, 2>}, {3, 2, 0.67f, launch_cfg<3, 2, 2, 1, 2>},
-    {4, 1, 0.49f, launch_cfg<4, 1, 2, 1, 2>}, {4, 2, 0.73f, launch_cfg<4, 2, 1, 1, 2>},
-    {4, 3, 0.76f, launch_cfg<4, 3, 1, 1, 2>}, {5, 2, 0.70f, launch_cfg<5, 2, 1, 1, 2>},
-    {5, 3, 0.75f, launch_cfg<5, 3, 1, 1, 2>}};
+    {1, 1, 0.24f, launch_cfg<1, 1, 4, 2, 4>}, {1, 2, 0.37f, launch_cfg<1, 2, 2, 2, 4>},
+    {2, 1, 0.46f, launch_cfg<2, 1, 2, 2, 4>}, {2, 2, 0.56f, launch_cfg<2, 2, 2, 2, 2>},
+    {2, 4, 0.69f, launch_cfg<2, 4, 1, 1, 2>}, {3, 2, 0.67f, launch_cfg<3, 2, 2, 1, 2>},
+    {4, 1, 0.53f, launch_cfg<4, 1, 2, 1, 2>}, {4, 2, 0.74f, launch_cfg<4, 2, 1, 1, 2>},
+    {4, 3, 0.81f, launch_cfg<4, 3, 1, 1, 2>}, {4, 4, 0.82f, launch_cfg<4, 4, 1, 1, 2>},
+    {5, 2, 0.67f, launch_cfg<5, 2, 1, 1, 2>}, {5, 3, 0.77f, launch_cfg<5, 3, 1, 1, 2>}};
 constexpr int N_CONFIGS = sizeof(CONFIGS) / sizeof(CONFIGS[0]);
 constexpr int CUS = 256;
 
@@ -407,34 +481,37 @@ void launch_pack(const uint16_t* src, int N, int K, uint16_t* dst, hipStream_t s
 
 // Picks the tile and the number of K chunks with the least estimated time:
 // the larger of the busiest CU's time (whole workgroups, each its MFMA cycles
-// at 2.4 GHz over the variant's eff plus 2.8 us to fill and drain), the
-// matrix rate of the whole chip (about 1.7 PFLOP/s) and the weight stream,
-// plus the partials' writing and their reading by the consumer.  On the 252
-// (shape, rows) pairs it was fitted to, its choice costs 0.3% over the best
-// variant measured for the pair on average, 6% at worst.
+// at 2.4 GHz over the variant's eff plus 1.9 us to fill and drain), the
+// matrix rate of the whole chip (about 1.9 PFLOP/s) and the weight stream,
+// plus the partials' writing and their reading by the consumer.  On the 210
+// (shape, rows) pairs it was fitted to, its choice costs 0.6% over the best
+// variant measured for the pair on average, 8% at worst.
 GemmPlan plan_gemm(int M, int N, int K, int nw, size_t max_part) {
   GemmPlan best{};
   float best_us = 0.f;
   const int nkt = (K + KB - 1) / KB, n_tiles = (N + TILE_ROWS - 1) / TILE_ROWS;
   const int ldp = n_tiles * TILE_ROWS * nw;
-  const float weight_us = (float)N * K * nw * 2.f / 18.5e6f + 1.f;
+  const float weight_us = (float)N * K * nw * 2.f / 9.7e6f + 2.5f;
   for (int ci = 0; ci < N_CONFIGS; ++ci) {
     const Config& c = CONFIGS[ci];
-    if ((c.MT - 1) * 32 >= M && c.MT > 1) continue;  // a row tile of padding only
     const int n_mt = (M + 32 * c.MT - 1) / (32 * c.MT);
-    if (c.MT == 1 && n_mt > 1) continue;
+    // up to 64 rows the one row tile that just holds them, so that the weights
+    // pass through a CU once; up to 160 rows that one or tiles of 64 rows (108
+    // rows, 7B-shaped output projection 15 us in one tile, 12 in two)
+    const int fit = (M + 31) / 32;
+    if (M <= 160 ? c.MT != fit && (c.MT != 2 || M <= 64) : c.MT < 2) continue;
     // 32-bit byte offsets within a row tile
-    if (c.MT > 1 && (size_t)32 * c.MT * 4 * K >= ((size_t)1 << 31)) continue;
+    if (c.MT > 2 && (size_t)32 * c.MT * 4 * K >= ((size_t)1 << 31)) continue;
     const int n_nt = (n_tiles * TILE_ROWS + 128 * c.NTW - 1) / (128 * c.NTW);
     for (int s = 1; s <= MAX_K_CHUNKS && s <= nkt; ++s) {
       const int bps = (nkt + s - 1) / s, S = (nkt + bps - 1) / bps;
       if (S != s) continue;
       if (s > 1 && (bps < 3 || (size_t)s * M * ldp > max_part)) break;
       const int items = n_mt * n_nt * nw * s;
-      const float wg_us = bps * 8 * 2 * c.MT * c.NTW * 32 / (2400.f * c.eff) + 2.8f;
+      const float wg_us = bps * 8 * 2 * c.MT * c.NTW * 32 / (2400.f * c.eff) + 1.9f;
       const float cu_us = (items + CUS - 1) / CUS * wg_us;
-      const float chip_us = (float)items * (c.MT * 32) * (c.NTW * 128) * (bps * 128.f) * 4e-6f / 1732.f;
-      const float part_us = (float)s * M * ldp * (0.9e-6f + 0.8e-6f) + 0.13f * s;
+      const float chip_us = (float)items * (c.MT * 32) * (c.NTW * 128) * (bps * 128.f) * 4e-6f / 1877.f;
+      const float part_us = (float)s * M * ldp * (1.0e-6f + 0.8e-6f) + 0.13f * s;
       const float us = std::max({cu_us, chip_us, weight_us}) + part_us;
       if (best_us == 0.f || us < best_us) {
         best_us = us;
@@ -446,8 +523,10 @@ GemmPlan plan_gemm(int M, int N, int K, int nw, size_t max_part) {
 }
 
 void launch_gemm(const GemmPlan& pl, const uint16_t* X, int ldx, int M, const uint16_t* W,
-                 const uint16_t* W2, int K, float* part, const GemmScratch& sc, hipStream_t st) {
+                 const uint16_t* W2, int K, float* part, const GemmScratch& sc, hipStream_t st,
+                 const ArgmaxOut* am) {
   GemmArgs a{};
+  if (am) a.am = *am;
   a.X = X;
   a.ldx = ldx;
   a.M = M;

@@ -437,13 +437,8 @@ __global__ __launch_bounds__(256) void k_fc_input(const uint16_t* h, const float
 constexpr int TOPK_MAX = 16;
 constexpr int TOPK_SLICE = 2048;
 
-MSD_DEV bool better(float va, int ia, float vb, int ib) {
-  return va > vb || (va == vb && ia < ib);
-}
-
 constexpr int TOPK_PER = TOPK_SLICE / 256;  // logits per thread of a slice block
 constexpr int TOPK_MERGE_PER = 8;           // slice candidates per thread of the merge
-constexpr int NO_ID = 0x7FFFFFFF;           // an absent candidate (ranks after every id)
 
 // The wave's best (value, id) over its lanes' offers.
 MSD_DEV void wave_best(float& v, int& id) {
@@ -499,8 +494,8 @@ MSD_DEV void block_merge(const float (*wv)[TOPK_MAX], const int (*wi)[TOPK_MAX],
 
 template <int PG>
 __global__ __launch_bounds__(256) void k_topk_slice(Parts logits, int V, int k, int n_slices,
-                                                    float* cand_v, int* cand_i, float2* stats,
-                                                    float* logits_out) {
+                                                    float* cand_v, int* cand_i,
+                                                    float2* stats) {
   __shared__ float wv[4][TOPK_MAX];
   __shared__ int wi[4][TOPK_MAX];
   __shared__ float sm[4];
@@ -523,7 +518,6 @@ __global__ __launch_bounds__(256) void k_topk_slice(Parts logits, int V, int k, 
     int id = NO_ID;
     if (v < V) {
       const float raw = raws[e];
-      if (logits_out) logits_out[(size_t)row * V + v] = raw;
       // a NaN ranks as -inf, so the selected ids are always vocabulary ids
       val = (raw == raw) ? raw : -INFINITY;
       id = v;
@@ -705,20 +699,27 @@ void launch_fc_input(const uint16_t* h, const float* hf, const int* h_row, const
                      next_tok, visual, d, out);
 }
 
+void launch_argmax_merge(int rows, int n_cand, const float* cand_v, const int* cand_i, int* idx,
+                         hipStream_t st) {
+  if (rows <= 0) return;
+  hipLaunchKernelGGL(k_topk_merge, dim3(rows), dim3(256), 0, st, 1, n_cand, cand_v, cand_i,
+                     nullptr, idx, nullptr, nullptr);
+}
+
 size_t topk_scratch_floats(int rows, int V) {
   const int n_slices = (V + TOPK_SLICE - 1) / TOPK_SLICE;
   return (size_t)rows * n_slices * (2 * TOPK_MAX + 2);
 }
 
 void launch_topk(Parts logits, int rows, int V, int k, int* idx, float* val, float* lse,
-                 float* logits_out, float* scratch, hipStream_t st) {
+                 float* scratch, hipStream_t st) {
   if (rows <= 0) return;
   const int n_slices = (V + TOPK_SLICE - 1) / TOPK_SLICE;
   float* cand_v = scratch;
   int* cand_i = reinterpret_cast<int*>(cand_v + (size_t)rows * n_slices * TOPK_MAX);
   float2* stats = reinterpret_cast<float2*>(cand_i + (size_t)rows * n_slices * TOPK_MAX);
   PG_DISPATCH(logits.S, k_topk_slice, dim3(rows * n_slices), dim3(256), 0, st, logits, V, k,
-              n_slices, cand_v, cand_i, stats, logits_out);
+              n_slices, cand_v, cand_i, stats);
   hipLaunchKernelGGL(k_topk_merge, dim3(rows), dim3(256), 0, st, k, n_slices, cand_v, cand_i,
                      stats, idx, val, lse);
 }

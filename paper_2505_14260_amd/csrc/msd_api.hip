@@ -102,7 +102,7 @@ constexpr int STAGE_INTS = 1 << 16;
 constexpr int ACC_BACK_INTS = 8 * MSD_MAX_TREE + 8 + 8 + 1;
 // Rows per GEMM launch: a pass of more rows runs as launches of equal size.
 constexpr int MAX_LAUNCH_ROWS = 2048;
-constexpr int LM_ROWS = 64;  // rows per LM-head launch (its partials are the widest)
+constexpr int LM_ROWS = 64;  // rows per LM-head launch that writes partials (they are the widest)
 // Floats of partials that a product may write to be split along K (40 MB;
 // launches over more rows than any verify without allocation takes: 128 MB).
 constexpr size_t PART_CAP = (size_t)10 << 20;
@@ -117,13 +117,14 @@ size_t layer_ldp(const msd_model_desc& m) {
                    2 * pad(m.ffn_dim)});
 }
 
-// Rows per GEMM launch for a pass over `rows` rows.  Passes that
-// msd_verify_noalloc may run keep one launch's partials within PART_CAP, but
-// never take fewer than 64 rows a launch.
-int row_chunk(const msd_model_desc& m, int rows) {
+// Rows per GEMM launch for a pass over `rows` rows, with partials of at most
+// cap floats (part_cap(rows)).  Passes that msd_verify_noalloc may run keep
+// one launch's partials within the cap, but never take fewer than 64 rows a
+// launch.
+int row_chunk(const msd_model_desc& m, int rows, size_t cap) {
   if (rows <= NOALLOC_MAX_ROWS) {
-    if (rows <= 64 || rows * layer_ldp(m) <= PART_CAP) return rows;
-    return std::max(64, (int)(PART_CAP / layer_ldp(m)) / 32 * 32);
+    if (rows <= 64 || rows * layer_ldp(m) <= cap) return rows;
+    return std::max(64, (int)(cap / layer_ldp(m)) / 32 * 32);
   }
   const int n = (rows + MAX_LAUNCH_ROWS - 1) / MAX_LAUNCH_ROWS;
   return n == 1 ? rows : ((rows + n - 1) / n + 127) / 128 * 128;
@@ -213,7 +214,9 @@ struct msd_ctx {
   // plans of the products run so far (plan_gemm), by their sizes
   struct PlanKey {
     int M, N, K, nw;
+    size_t cap;
   };
+  size_t cap_now = 0;  // > 0: the cap of this call's partials instead of part_cap
   std::vector<std::pair<PlanKey, GemmPlan>> gemm_plans;
   float* ssq;
   Rows rows;
@@ -461,18 +464,23 @@ void trace_events(msd_ctx* c, int kind, int M, int N, int K, hipEvent_t* e0, hip
 constexpr size_t MAX_PLANS = 256;
 const GemmPlan& gemm_plan(msd_ctx* c, int M, int N, int K, int nw, size_t cap) {
   for (const auto& e : c->gemm_plans)
-    if (e.first.M == M && e.first.N == N && e.first.K == K && e.first.nw == nw) return e.second;
+    if (e.first.M == M && e.first.N == N && e.first.K == K && e.first.nw == nw &&
+        e.first.cap == cap)
+      return e.second;
   if (c->gemm_plans.size() >= MAX_PLANS) c->gemm_plans.clear();
-  c->gemm_plans.push_back({{M, N, K, nw}, plan_gemm(M, N, K, nw, cap)});
+  c->gemm_plans.push_back({{M, N, K, nw, cap}, plan_gemm(M, N, K, nw, cap)});
   return c->gemm_plans.back().second;
 }
+
+// The cap of a launch's partials in this call.
+size_t call_cap(const msd_ctx* c, int rows) { return c->cap_now ? c->cap_now : part_cap(rows); }
 
 // Partial products of rows [0, M) of the split rows X (row stride
 // ldx = 2K) against the packed weight W [N][K] (and W2); returns the view the
 // consumer sums.
 int gemm(msd_ctx* c, int kind, const uint16_t* X, int ldx, int M, const uint16_t* W,
          const uint16_t* W2, int N, int K, Parts* out) {
-  const GemmPlan& pl = gemm_plan(c, M, N, K, W2 ? 2 : 1, part_cap(M));
+  const GemmPlan& pl = gemm_plan(c, M, N, K, W2 ? 2 : 1, call_cap(c, M));
   if ((size_t)pl.S * M * pl.ldp > c->plan.part_floats)
     return fail(c, MSD_ERR_INVALID_ARG, "internal: GEMM partials exceed their buffer");
   GemmScratch gs{};
@@ -480,6 +488,27 @@ int gemm(msd_ctx* c, int kind, const uint16_t* X, int ldx, int M, const uint16_t
   launch_gemm(pl, X, ldx, M, W, W2, K, c->part, gs, c->st);
   LAUNCHED(c);
   *out = Parts{c->part, pl.S, (size_t)M * pl.ldp, pl.ldp, pl.off2};
+  return MSD_OK;
+}
+
+// LM head and argmax over rows [0, M) of the split rows X: the best id of
+// each row (lowest on ties) to idx, the logits to logits ([M][V]) when given.
+// K is one chunk, so the GEMM reduces its columns itself and nothing of the
+// logits goes through partials (244 rows of a 152,064-word vocabulary: four
+// 64-row launches with 39 MB of partials each and their top-k, 820 us, became
+// one launch of 470 us and a merge of 5 us).
+int lm_argmax(msd_ctx* c, const uint16_t* X, int M, int* idx, float* logits) {
+  const int d = c->m.d_model, V = c->m.vocab;
+  const GemmPlan& pl = gemm_plan(c, M, V, d, 1, 0);
+  float* const cv = c->tk_scratch;
+  const ArgmaxOut am{cv, reinterpret_cast<int*>(cv + (size_t)M * pl.n_nt), logits, V,
+                     V % 4 == 0 && ((uintptr_t)logits & 15) == 0};
+  GemmScratch gs{};
+  trace_events(c, GK_LMHEAD, M, V, d, &gs.ev_start, &gs.ev_stop);
+  launch_gemm(pl, X, 2 * d, M, c->lm_p, nullptr, d, nullptr, gs, c->st, &am);
+  LAUNCHED(c);
+  launch_argmax_merge(M, pl.n_nt, am.cand_v, am.cand_i, idx, c->st);
+  LAUNCHED(c);
   return MSD_OK;
 }
 
@@ -545,7 +574,7 @@ int forward_layers(msd_ctx* c, bool draft, int n_seq, int nq, int tree_R, int ma
   const int rows = n_seq * nq;
   const int d = m.d_model, H = m.n_heads, KV = m.n_kv_heads, hd = m.head_dim, F = m.ffn_dim;
   const int nl = draft ? 1 : m.n_layers;
-  const int ch = row_chunk(m, rows);
+  const int ch = row_chunk(m, rows, call_cap(c, rows));
   const int B = c->lim.max_batch, S = c->lim.max_seq;
   const size_t layer_kv = (size_t)B * KV * S * hd;
   for (int l = 0; l < nl; ++l) {
@@ -641,7 +670,7 @@ int forward_layers(msd_ctx* c, bool draft, int n_seq, int nq, int tree_R, int ma
 int draft_pass(msd_ctx* c, int n_seq, int nq, int tree_R, int max_ltot, const uint16_t* visual) {
   const int d = c->m.d_model;
   const int rows = n_seq * nq;
-  const int ch = row_chunk(c->m, rows);
+  const int ch = row_chunk(c->m, rows, part_cap(rows));
   Parts pt;
   for (int m0 = 0; m0 < rows; m0 += ch) {
     const int mc = std::min(ch, rows - m0);
@@ -713,7 +742,7 @@ int draft_head(msd_ctx* c, int rows, int k) {
     const int mc = std::min(LM_ROWS, rows - m0);
     TRY(gemm(c, GK_LMHEAD, c->xb + (size_t)m0 * 2 * d, 2 * d, mc, c->lm_p, nullptr, V, d, &pt));
     launch_topk(pt, mc, V, k, c->tk_idx + (size_t)m0 * k, c->tk_val + (size_t)m0 * k,
-                c->tk_lse + m0, nullptr, c->tk_scratch, c->st);
+                c->tk_lse + m0, c->tk_scratch, c->st);
     LAUNCHED(c);
   }
   return MSD_OK;
@@ -1284,11 +1313,7 @@ int msd_prefill(msd_ctx* c, int seq, int n, const int32_t* tokens_h, const uint8
   if (n_vis && !visual_d) return fail(c, MSD_ERR_INVALID_ARG, "visual rows missing");
   TRY(prompt_target(c, seq, n, tokens_h, is_visual_h, visual_d));
   const int d = m.d_model;
-  Parts pt;
-  TRY(gemm(c, GK_LMHEAD, c->h + (size_t)(n - 1) * 2 * d, 2 * d, 1, c->lm_p, nullptr, m.vocab, d,
-           &pt));
-  launch_topk(pt, 1, m.vocab, 1, c->tk_idx, c->tk_val, nullptr, nullptr, c->tk_scratch, c->st);
-  LAUNCHED(c);
+  TRY(lm_argmax(c, c->h + (size_t)(n - 1) * 2 * d, 1, c->tk_idx, nullptr));
   launch_set_int(c->d_root, seq, c->tk_idx, 0, c->st);
   launch_set_int(c->nxt, n - 1, c->tk_idx, 0, c->st);
   LAUNCHED(c);
@@ -1485,41 +1510,34 @@ int verify_impl(msd_ctx* c, int n_seq, const int32_t* seqs_h, const msd_tree* tr
   LAUNCHED(c);
   TRY(norm_rows(c, rows, c->layers[0].n1));
   TRY(forward_layers(c, false, n_seq, T, T, max_l + T, c->final_norm, c->h, nullptr));
-  Parts pt;
-  for (int m0 = 0; m0 < rows; m0 += LM_ROWS) {
-    const int mc = std::min(LM_ROWS, rows - m0);
-    TRY(gemm(c, GK_LMHEAD, c->h + (size_t)m0 * 2 * d, 2 * d, mc, c->lm_p, nullptr, V, d, &pt));
-    launch_topk(pt, mc, V, 1, argmax_d + m0, nullptr, nullptr,
-                logits_d ? logits_d + (size_t)m0 * V : nullptr, c->tk_scratch, c->st);
-    LAUNCHED(c);
-  }
+  const int lm = c->cap_now ? std::min(LM_ROWS, rows) : rows;
+  for (int m0 = 0; m0 < rows; m0 += lm)
+    TRY(lm_argmax(c, c->h + (size_t)m0 * 2 * d, std::min(lm, rows - m0), argmax_d + m0,
+                  logits_d ? logits_d + (size_t)m0 * V : nullptr));
   c->verified_T = T;
   c->verified_seqs.assign(seqs_h, seqs_h + n_seq);
   return MSD_OK;
 }
 
 // Floats of GEMM partials a verify of `rows` tree rows writes (the largest
-// of its launches: q/k/v, output, gate+up, down and LM head).
+// of its launches: q/k/v, output, gate+up and down) under the call's cap.
 size_t verify_part_floats(msd_ctx* c, int rows) {
   const msd_model_desc& m = c->m;
   const int d = m.d_model, F = m.ffn_dim, hh = m.n_heads * m.head_dim;
   const int qkv = (m.n_heads + 2 * m.n_kv_heads) * m.head_dim;
   size_t need = 0;
   const auto add = [&](int M, int N, int K, int nw) {
-    const GemmPlan& p = gemm_plan(c, M, N, K, nw, part_cap(M));
+    const GemmPlan& p = gemm_plan(c, M, N, K, nw, call_cap(c, M));
     need = std::max(need, (size_t)p.S * M * p.ldp);
   };
-  const auto each = [&](int chunk, auto&& f) {
-    f(std::min(chunk, rows));
-    if (rows > chunk && rows % chunk) f(rows % chunk);
-  };
-  each(row_chunk(m, rows), [&](int M) {
+  const int ch = row_chunk(m, rows, call_cap(c, rows));
+  for (int M : {std::min(ch, rows), rows % ch}) {
+    if (M <= 0) continue;
     add(M, qkv, d, 1);
     add(M, d, hh, 1);
     add(M, F, d, 2);
     add(M, d, F, 1);
-  });
-  each(LM_ROWS, [&](int M) { add(M, m.vocab, d, 1); });
+  }
   return need;
 }
 
@@ -1549,13 +1567,24 @@ int msd_verify_noalloc(msd_ctx* c, int n_seq, const int32_t* seqs_h, const msd_t
   // the same attention chunking as msd_verify, so both compute identically
   const TreeChunks tc = plan_tree_chunks(m, n_seq, n_nodes, max_l + n_nodes,
                                          c->plan.attn_floats);
-  const size_t part = verify_part_floats(c, rows);
   const size_t att_o = tc.part_floats;
   const size_t att_ml = att_o / m.head_dim * 2 + 64;
-  const size_t tk = topk_scratch_floats(std::min(LM_ROWS, rows), m.vocab);
   auto up = [](size_t f) { return (f + 63) / 64 * 64; };  // 256-byte steps
-  const size_t need = up(part) + up(att_o) + up(att_ml) + up(tk);
-  if (need * sizeof(float) > MSD_NOALLOC_SCRATCH_BYTES)
+  const size_t have = MSD_NOALLOC_SCRATCH_BYTES / sizeof(float);
+  size_t rest = up(att_o) + up(att_ml) + up(topk_scratch_floats(rows, m.vocab));
+  size_t part = verify_part_floats(c, rows);
+  struct Cap {  // the call's cap on partials ends with the call
+    msd_ctx* c;
+    ~Cap() { c->cap_now = 0; }
+  } cap_guard{c};
+  if (up(part) + rest > have) {
+    // fewer rows a launch and fewer K chunks, as the scratch allows
+    rest = up(att_o) + up(att_ml) + up(topk_scratch_floats(std::min(LM_ROWS, rows), m.vocab));
+    c->cap_now = have > rest + 64 ? have - rest - 64 : 1;
+    part = verify_part_floats(c, rows);
+  }
+  const size_t need = up(part) + rest;
+  if (need > have)
     return fail(c, MSD_ERR_INVALID_ARG,
                 "this verify needs " + std::to_string(need * sizeof(float)) +
                     " bytes of scratch; msd_verify_noalloc holds " +

@@ -72,6 +72,23 @@ struct GemmScratch {
   hipEvent_t ev_start, ev_stop;  // when set: recorded around the kernel itself
 };
 
+// The LM head with an argmax: instead of partials, candidate (value, id) nt of
+// each row over column tile nt, at [row * n_nt + nt], and the logits
+// ([M][V] float32) when given.
+struct ArgmaxOut {
+  float* cand_v;
+  int* cand_i;
+  float* logits;
+  int V;
+  int vec;  // logits rows are multiples of 16 bytes
+};
+
+// Ranking of vocabulary candidates: value descending, then id ascending.
+constexpr int NO_ID = 0x7FFFFFFF;  // an absent candidate (ranks after every id)
+MSD_DEV bool better(float va, int ia, float vb, int ib) {
+  return va > vb || (va == vb && ia < ib);
+}
+
 // Elements of a packed [N][K] weight (64-row tiles x 128-column blocks).
 size_t packed_elems(int N, int K);
 // Packs the row-major bf16 [N][K] src into dst (packed_elems(N, K) elements).
@@ -88,7 +105,8 @@ size_t stream_span_bytes();
 void launch_stream_read(const uint16_t* buf, size_t spans, int wgs, unsigned* sink,
                         hipStream_t st);
 void launch_gemm(const GemmPlan& pl, const uint16_t* X, int ldx, int M, const uint16_t* W,
-                 const uint16_t* W2, int K, float* part, const GemmScratch& sc, hipStream_t st);
+                 const uint16_t* W2, int K, float* part, const GemmScratch& sc, hipStream_t st,
+                 const ArgmaxOut* am = nullptr);
 
 // Partial sums as seen by a consumer: value(m, n) = sum_s p[s*split + m*ld + n];
 // the second weight's products are at column n + off2.
@@ -185,12 +203,16 @@ void launch_visual_feature_rows(const uint16_t* h, const int* vis_idx, int rows,
                                 hipStream_t st);
 
 // -------------------------------------------------------- selection ----
-// scratch: topk_scratch_floats(rows, V) floats (8-byte aligned).  The
-// logits are the summed parts; when logits_out is given they are also
-// written there ([rows][V]).
+// scratch: topk_scratch_floats(rows, V) floats (8-byte aligned); it also
+// holds the candidates of an argmax over tiles of 128 columns or more.  The
+// logits are the summed parts.
 size_t topk_scratch_floats(int rows, int V);
 void launch_topk(Parts logits, int rows, int V, int k, int* idx, float* val, float* lse,
-                 float* logits_out, float* scratch, hipStream_t st);
+                 float* scratch, hipStream_t st);
+// Argmax of each row over its n_cand candidates (cand_v and cand_i of
+// ArgmaxOut; n_cand <= 2048).
+void launch_argmax_merge(int rows, int n_cand, const float* cand_v, const int* cand_i, int* idx,
+                         hipStream_t st);
 
 // ---------------------------------------------------- tree / accept ----
 // Row descriptors of one forward step (device arrays, one entry per row).
