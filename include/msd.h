@@ -350,7 +350,9 @@ int msd_set_state(msd_ctx* ctx, int seq, int L, const void* h_d, int32_t next_to
  * next-token distribution.  A batch's loss is the mean of loss_i over all
  * rows of its sequences.  Trained: f_down, the draft layer's seven matrices
  * and two norm gains (float32 master copies); the embedding table and the
- * LM head stay frozen.  Arithmetic in float32 (the contractions on rocBLAS).
+ * LM head stay frozen.  Arithmetic in float32; in the products over weights
+ * every float32 operand enters the bf16 matrix units as three terms that hold
+ * its 24 bits, with float32 sums.
  *
  * msd_train_accumulate adds one sequence's gradient sums and writes its
  * loss sums to loss_h[3] (total, regression part, token part, each summed

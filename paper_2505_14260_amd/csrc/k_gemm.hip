@@ -44,11 +44,26 @@ struct GemmArgs {
   size_t part_split;
   int ldp, off2;
   ArgmaxOut am;
+  // EPI_SUM: columns [0, N) of each weight's products, plus add when given
+  // (rows of ldp floats, as part)
+  const float* add;
+  int N;
+  size_t wplane;  // elements between the planes of a weight (TW > 1)
 };
 
 // What a workgroup does with its sums: store them as partials, or (K whole in
-// one chunk, the LM head of a verify) reduce each row to its best column.
-enum Epilogue { EPI_PART, EPI_ARGMAX };
+// one chunk) reduce each row to its best column (the LM head of a verify) or
+// store them added to a matrix (the training products).
+enum Epilogue { EPI_PART, EPI_ARGMAX, EPI_SUM };
+
+// Products of an operand pair given as TX and TW bf16 terms of falling size:
+// term i of X with term (plane) p of W for i + p < TX, the rest being below
+// the last bit of the sum's largest terms.
+MSD_DEV constexpr int n_products(int TX, int TW) {
+  int n = 0;
+  for (int p = 0; p < TW; ++p) n += TX - p;
+  return n;
+}
 
 MSD_DEV constexpr int vmcnt_imm(int n) { return 0x0f70 | (n & 15) | ((n >> 4) << 14); }
 
@@ -98,18 +113,27 @@ MSD_DEV constexpr int vmcnt_imm(int n) { return 0x0f70 | (n & 15) | ((n >> 4) <<
 //  1024 rows                             148,  55,   277,  138  (1.25-1.39 PFLOP/s)
 // Bound: HBM up to about 100 rows, then the matrix cores: at 624 rows they
 // are 82% busy inside a workgroup, at about 2.15 GHz.
-template <int MT, int NTW, int OCC, int POL, int RD, int NB, int EPI>
+//
+// TX, TW: terms of X and of W.  The decode and prompt paths have TX = 2 (hi and
+// lo) and bf16 weights (TW = 1).  The training products have float32 operands
+// as three terms each, h = bf16(x), m = bf16(x - h), l = bf16(x - h - m), 24
+// bits in all (k_train.hip): X rows of 3K, W as three packed planes, and the
+// six products down to 2^-16 of the first; or three terms against the bf16 LM
+// head.
+template <int MT, int NTW, int OCC, int POL, int RD, int NB, int EPI, int TX = 2, int TW = 1>
 __global__ __launch_bounds__(256, OCC) void k_gemm(GemmArgs a) {
   static_assert(NB == 2 || (NB == 4 && RD >= 2), "the first waits count on the ring's loads");
   constexpr int XD = NB - 1;          // half blocks that X is loaded ahead
   constexpr int BM = 32 * MT;
-  constexpr int ND = BM / 16;         // loads to LDS per wave and half block
+  constexpr int UNITS = TX * BM * 8;  // 16-byte units of a half block of X
+  constexpr int ND = UNITS / 256;     // loads to LDS per wave and half block
+  static_assert(UNITS % 256 == 0, "X units divide over the waves");
   constexpr int DPS = (ND + 1) / 2;   // of them per step (in steps 0 and 1)
-  // hi rows, then lo rows, 8 units each
-  __shared__ u32x4 xs0[BM * 16];
-  __shared__ u32x4 xs1[BM * 16];
-  __shared__ u32x4 xs2[NB > 2 ? BM * 16 : 1];
-  __shared__ u32x4 xs3[NB > 2 ? BM * 16 : 1];
+  // the rows of term 0, then of term 1, ..., 8 units each
+  __shared__ u32x4 xs0[UNITS];
+  __shared__ u32x4 xs1[UNITS];
+  __shared__ u32x4 xs2[NB > 2 ? UNITS : 1];
+  __shared__ u32x4 xs3[NB > 2 ? UNITS : 1];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // Workgroup i runs on XCD i mod 8: every XCD takes a contiguous range of
@@ -127,8 +151,11 @@ __global__ __launch_bounds__(256, OCC) void k_gemm(GemmArgs a) {
   const int m0 = mt * BM;
   const int kb0 = s * a.bps, kb1 = min(a.nkt, kb0 + a.bps);
   const int K = a.K, nkt = a.nkt;
-  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(w ? a.W2 : a.W), 0, a.n_tiles * nkt * BLOCK_BYTES, RSRC_RAW);
+  __amdgpu_buffer_rsrc_t rw[TW];
+#pragma unroll
+  for (int p = 0; p < TW; ++p)
+    rw[p] = __builtin_amdgcn_make_buffer_rsrc((void*)((w ? a.W2 : a.W) + p * a.wplane), 0,
+                                              a.n_tiles * nkt * BLOCK_BYTES, RSRC_RAW);
   const int rowb = a.ldx * 2;
   const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
       (void*)(a.X + (size_t)m0 * a.ldx), 0, min(a.M - m0, BM) * rowb, RSRC_RAW);
@@ -145,34 +172,42 @@ __global__ __launch_bounds__(256, OCC) void k_gemm(GemmArgs a) {
     const int q = (n32 + j) >> 1 < a.n_tiles ? n32 + j : 0;
     wso[j] = (q >> 1) * nkt * BLOCK_BYTES + (q & 1) * (BLOCK_BYTES / 2);
   }
-  const auto load_w = [&](int kb, int sp, int c, int j) {
+  const auto load_w = [&](int kb, int sp, int c, int j, int p) {
     const int kc = min(kb, kb1 - 1);
     return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                         rw, kb < kb1 ? wvo : PAST,
+                                         rw[p], kb < kb1 ? wvo : PAST,
                                          wso[j] + kc * BLOCK_BYTES + c * 1024 + sp * 512, POL));
   };
-  // Waves 0 and 1 load the hi halves, waves 2 and 3 the lo halves; load q of
-  // a wave fills the eight rows of group (wave & 1) ND + q, lane i the unit
-  // i & 7 of row i >> 3, i.e. source unit (i & 7) ^ (i >> 3).
+  // Load q of a wave fills the eight rows of group wave ND + q (groups run
+  // through the rows of term 0, then of term 1, ...), lane i the unit i & 7 of
+  // row i >> 3, i.e. source unit (i & 7) ^ (i >> 3).
   const int xu = (lane & 7) ^ (lane >> 3);
-  const int xvo = ((wave & 1) * ND * 8 + (lane >> 3)) * rowb + xu * 16;
-  const int xso = wave >= 2 ? 2 * K : 0;
+  const int xvo = (lane >> 3) * rowb + xu * 16;
   const auto load_x = [&](u32x4* b, int q, int kb, int sp) {
     const int k0 = min(kb, kb1 - 1) * KB + sp * 64;
-    const int vo = (kb < kb1 && k0 + 8 * xu < K) ? xvo + q * 8 * rowb : PAST;
+    const int g = wave * ND + q, term = g / (BM / 8), rg = g - term * (BM / 8);
+    const int vo = (kb < kb1 && k0 + 8 * xu < K) ? xvo + rg * 8 * rowb : PAST;
     // the last half block may begin past K: soffset stays inside the buffer
     __builtin_amdgcn_raw_ptr_buffer_load_lds(
-        rx, (__attribute__((address_space(3))) void*)(b + (wave * ND + q) * 64), 16, vo,
-        xso + 2 * min(k0, K - 8), 0, 0);
+        rx, (__attribute__((address_space(3))) void*)(b + g * 64), 16, vo,
+        2 * (term * K + min(k0, K - 8)), 0, 0);
   };
-  u32x4 wr[RD][4][NTW];
-  f32x16 acc[NTW][MT];
+  constexpr int NW = NTW * TW;  // weight loads per step
+  u32x4 wr[RD][4][NW];
+  // acc: the sums; with three terms, the products below the first go to sums of
+  // their own (low), whose rounding is as much smaller, added at the end (256
+  // columns: relative error 2.4e-7 in one sum, 0.8e-7 in two; a float32 GEMM 1.5e-7)
+  constexpr bool LOW = TX == 3;
+  f32x16 acc[NTW][MT], low[LOW ? NTW : 1][LOW ? MT : 1];
 #pragma unroll
   for (int j = 0; j < NTW; ++j)
 #pragma unroll
     for (int m = 0; m < MT; ++m)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[j][m][e] = 0.f;
+      for (int e = 0; e < 16; ++e) {
+        acc[j][m][e] = 0.f;
+        if constexpr (LOW) low[j][m][e] = 0.f;
+      }
 #pragma unroll
   for (int q = 0; q < ND; ++q) load_x(xs0, q, kb0, 0);
   __builtin_amdgcn_sched_barrier(0);
@@ -189,19 +224,19 @@ __global__ __launch_bounds__(256, OCC) void k_gemm(GemmArgs a) {
 #pragma unroll
     for (int c = 0; c < 4; ++c)
 #pragma unroll
-      for (int j = 0; j < NTW; ++j) wr[d][c][j] = load_w(kb0 + d / 2, d & 1, c, j);
+      for (int j = 0; j < NW; ++j) wr[d][c][j] = load_w(kb0 + d / 2, d & 1, c, j % NTW, j / NTW);
   __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_waitcnt(vmcnt_imm((XD - 1) * ND + 4 * NTW * RD));
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm((XD - 1) * ND + 4 * NW * RD));
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
-  u32x4 fx[2][2][MT];  // X fragments of two steps: hi, lo
+  u32x4 fx[2][TX][MT];  // X fragments of two steps
   const auto frags = [&](const u32x4* b, int c) {
     const int u = r * 8 + ((4 * h + c) ^ (r & 7));
 #pragma unroll
-    for (int m = 0; m < MT; ++m) fx[c & 1][0][m] = b[m * 256 + u];
+    for (int t = 0; t < TX; ++t)
 #pragma unroll
-    for (int m = 0; m < MT; ++m) fx[c & 1][1][m] = b[BM * 8 + m * 256 + u];
+      for (int m = 0; m < MT; ++m) fx[c & 1][t][m] = b[t * BM * 8 + m * 256 + u];
   };
   // Half block sp of block kb (X in b), loading the X of XD halves further
   // into bn and refilling ring half rd with the W of RD halves further.
@@ -217,34 +252,41 @@ __global__ __launch_bounds__(256, OCC) void k_gemm(GemmArgs a) {
       for (int q = c * DPS; q < (c + 1) * DPS && q < ND; ++q) load_x(bn, q, xkb, xsp);
       if (c > 0) {
 #pragma unroll
-        for (int j = 0; j < NTW; ++j) wr[rd][c - 1][j] = load_w(wkb, wsp, c - 1, j);
+        for (int j = 0; j < NW; ++j) wr[rd][c - 1][j] = load_w(wkb, wsp, c - 1, j % NTW, j / NTW);
       }
 #pragma unroll
-      for (int hl = 0; hl < 2; ++hl)
+      for (int t = 0; t < TX; ++t)
 #pragma unroll
-        for (int m = 0; m < MT; ++m)
+        for (int p = 0; p < TW; ++p) {
+          if (t + p >= TX) continue;
 #pragma unroll
-          for (int j = 0; j < NTW; ++j)
-            acc[j][m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                __builtin_bit_cast(bf16x8, wr[rd][c][j]),
-                __builtin_bit_cast(bf16x8, fx[c & 1][hl][m]), acc[j][m], 0, 0, 0);
-      // one LDS read and at most one load between the MFMAs of a fragment
-      const int loads = (c < 2 ? DPS : 0) + (c > 0 ? NTW : 0);
+          for (int m = 0; m < MT; ++m)
 #pragma unroll
-      for (int i = 0; i < 2 * MT; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x8, NTW, 0);
+            for (int j = 0; j < NTW; ++j) {
+              f32x16& sum = LOW && t + p > 0 ? low[LOW ? j : 0][LOW ? m : 0] : acc[j][m];
+              sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                  __builtin_bit_cast(bf16x8, wr[rd][c][p * NTW + j]),
+                  __builtin_bit_cast(bf16x8, fx[c & 1][t][m]), sum, 0, 0, 0);
+            }
+        }
+      // one LDS read and at most one load between groups of MFMAs
+      constexpr int GROUP = n_products(TX, TW) * NTW / TX;
+      const int loads = (c < 2 ? DPS : 0) + (c > 0 ? NW : 0);
+#pragma unroll
+      for (int i = 0; i < TX * MT; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x8, GROUP, 0);
         if (c < 3) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         if (i < loads) __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (int j = 0; j < NTW; ++j) wr[rd][3][j] = load_w(wkb, wsp, 3, j);
+    for (int j = 0; j < NW; ++j) wr[rd][3][j] = load_w(wkb, wsp, 3, j % NTW, j / NTW);
     __builtin_amdgcn_sched_barrier(0);
     // The next half's X was loaded XD - 1 halves ago, by the end of step 1:
-    // the refills of steps 2 and 3 and those after step 3 (3 NTW loads) and
+    // the refills of steps 2 and 3 and those after step 3 (3 NW loads) and
     // all loads of the halves since came later and may stay in flight.
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(3 * NTW + (XD - 1) * (ND + 4 * NTW)));
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(3 * NW + (XD - 1) * (ND + 4 * NW)));
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
@@ -265,6 +307,14 @@ __global__ __launch_bounds__(256, OCC) void k_gemm(GemmArgs a) {
       half(xs3, xs2, 3 % RD, kb + 1, 1);
     }
   }
+  if constexpr (LOW) {
+#pragma unroll
+    for (int j = 0; j < NTW; ++j)
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[j][m][e] += low[j][m][e];
+  }
   // C layout of the 32x32 MFMA: lane holds row m = lane & 31, register e the
   // column 8 (e / 4) + 4 (lane / 32) + e % 4
   if constexpr (EPI == EPI_PART) {
@@ -283,6 +333,28 @@ __global__ __launch_bounds__(256, OCC) void k_gemm(GemmArgs a) {
               acc[j][m][4 * q], acc[j][m][4 * q + 1], acc[j][m][4 * q + 2], acc[j][m][4 * q + 3]);
       }
     }
+  } else if constexpr (EPI == EPI_SUM) {
+    const size_t wo = (size_t)w * a.off2;
+#pragma unroll
+    for (int j = 0; j < NTW; ++j)
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        const int row = m0 + m * 32 + r;
+        if (row >= a.M) continue;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int n = (n32 + j) * 32 + 8 * q + 4 * h;  // N is a multiple of 4
+          if (n >= a.N) continue;
+          const size_t o = (size_t)row * a.ldp + wo + n;
+          float4 v = make_float4(acc[j][m][4 * q], acc[j][m][4 * q + 1], acc[j][m][4 * q + 2],
+                                 acc[j][m][4 * q + 3]);
+          if (a.add) {
+            const float4 d = *reinterpret_cast<const float4*>(a.add + o);
+            v = make_float4(v.x + d.x, v.y + d.y, v.z + d.z, v.w + d.w);
+          }
+          *reinterpret_cast<float4*>(a.part + o) = v;
+        }
+      }
   } else {
     // the best (value, id) of each row over the workgroup's columns, as
     // candidate nt of the row; a NaN ranks as -inf, the lowest id wins ties
@@ -545,6 +617,101 @@ void launch_gemm(const GemmPlan& pl, const uint16_t* X, int ldx, int M, const ui
   a.ldp = pl.ldp;
   a.off2 = pl.off2;
   CONFIGS[pl.config].launch(a, pl.items, sc, st);
+}
+
+namespace {
+
+// C = add + the sum of S partials, four columns per thread.
+__global__ __launch_bounds__(256) void k_sum_parts(const float* part, int S, size_t split, int ldp,
+                                                   int N, const float* add, float* C, int ldc) {
+  const int n = 4 * (blockIdx.x * 256 + threadIdx.x);
+  if (n >= N) return;
+  const size_t o = (size_t)blockIdx.y * ldc + n;
+  float4 v = add ? *reinterpret_cast<const float4*>(add + o) : make_float4(0.f, 0.f, 0.f, 0.f);
+  const float* p = part + (size_t)blockIdx.y * ldp + n;
+  for (int q = 0; q < S; ++q) {
+    const float4 x = *reinterpret_cast<const float4*>(p + q * split);
+    v = make_float4(v.x + x.x, v.y + x.y, v.z + x.z, v.w + x.w);
+  }
+  *reinterpret_cast<float4*>(C + o) = v;
+}
+
+template <int MT, int NTW, int TX, int TW>
+void launch_sum_cfg(const GemmArgs& a, int items, bool part, hipStream_t st) {
+  const dim3 grid(8 * ((items + 7) / 8));
+  constexpr int OCC = 1;
+  if (part)
+    hipLaunchKernelGGL((k_gemm<MT, NTW, OCC, 0, 1, 2, EPI_PART, TX, TW>), grid, dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL((k_gemm<MT, NTW, OCC, 0, 1, 2, EPI_SUM, TX, TW>), grid, dim3(256), 0, st, a);
+}
+
+template <int TX, int TW>
+void launch_sum_terms(int MT, const GemmArgs& a, int items, bool part, hipStream_t st) {
+  if (MT == 4) launch_sum_cfg<4, 2, TX, TW>(a, items, part, st);
+  else launch_sum_cfg<2, 2, TX, TW>(a, items, part, st);
+}
+
+}  // namespace
+
+// The training products: two tile heights, K split while the tiles leave CUs
+// idle and the partials fit.  The estimate is plan_gemm's (its eff values).
+void launch_gemm_sum(const SumGemm& g, hipStream_t st) {
+  const int nkt = (g.K + KB - 1) / KB;
+  // a plane's byte offsets are 32-bit: wider matrices go in column ranges
+  const size_t tile_bytes = (size_t)nkt * BLOCK_BYTES;
+  const int max_n = (int)std::min<size_t>(((((size_t)1 << 31) - 1) / tile_bytes) * TILE_ROWS, 1 << 30);
+  for (int n0 = 0; n0 < g.N; n0 += max_n) {
+    const int N = std::min(max_n, g.N - n0);
+    const int n_tiles = (N + TILE_ROWS - 1) / TILE_ROWS, ldp = n_tiles * TILE_ROWS;
+    int np = 0;
+    for (int p = 0; p < g.TW; ++p) np += g.TX - p;
+    int best_mt = 4, best_bps = nkt;
+    float best_us = 0.f;
+    for (int MT : {4, 2}) {
+      const int n_mt = (g.M + 32 * MT - 1) / (32 * MT), n_nt = (ldp + 255) / 256;
+      for (int s = 1; s <= MAX_K_CHUNKS && s <= nkt; ++s) {
+        const int bps = (nkt + s - 1) / s;
+        if ((nkt + bps - 1) / bps != s) continue;
+        if (s > 1 && (bps < 4 || g.M > 65535 || (size_t)s * g.M * ldp > g.max_part)) break;
+        const int items = n_mt * n_nt * s;
+        const float wg_us = bps * 8 * np * MT * 2 * 32 / (2400.f * (MT == 4 ? 0.74f : 0.56f)) + 1.9f;
+        const float us = (items + CUS - 1) / CUS * wg_us + (s > 1 ? s + 1 : 1) * (float)g.M * ldp * 1.8e-6f;
+        if (best_us == 0.f || us < best_us) {
+          best_us = us;
+          best_mt = MT;
+          best_bps = bps;
+        }
+      }
+    }
+    GemmArgs a{};
+    a.X = g.X;
+    a.ldx = g.TX * g.K;
+    a.M = g.M;
+    a.K = g.K;
+    a.W = g.W + (size_t)(n0 / TILE_ROWS) * nkt * BLOCK_ELEMS;
+    a.wplane = g.wplane;
+    a.n_tiles = n_tiles;
+    a.nkt = nkt;
+    a.n_mt = (g.M + 32 * best_mt - 1) / (32 * best_mt);
+    a.n_nt = (ldp + 255) / 256;
+    a.nw = 1;
+    a.bps = best_bps;
+    a.S = (nkt + best_bps - 1) / best_bps;
+    a.N = N;
+    const bool parts = a.S > 1;
+    a.part = parts ? g.part : g.C + n0;
+    a.ldp = parts ? ldp : g.ldc;
+    a.part_split = (size_t)g.M * ldp;
+    a.add = g.add ? g.add + n0 : nullptr;
+    const int items = a.n_mt * a.n_nt * a.S;
+    if (g.TW == 3) launch_sum_terms<3, 3>(best_mt, a, items, parts, st);
+    else if (g.TX == 3) launch_sum_terms<3, 1>(best_mt, a, items, parts, st);
+    else launch_sum_terms<2, 1>(best_mt, a, items, parts, st);
+    if (parts)
+      hipLaunchKernelGGL(k_sum_parts, dim3((N + 1023) / 1024, g.M), dim3(256), 0, st, g.part, a.S,
+                         a.part_split, ldp, N, a.add, g.C + n0, g.ldc);
+  }
 }
 
 }  // namespace msd

@@ -2,9 +2,13 @@
 // teacher-forced draft layer over a training sequence, its loss (regression
 // toward the next target feature plus the token cross-entropy against the
 // target's next-token distribution) and the backward pass, and the AdamW
-// update.  The contractions run as rocBLAS float32 GEMMs issued by the host
-// orchestration; these kernels do everything between them.  Row-major
-// throughout; a training pass has R = n - 1 rows (positions 0 .. n-2).
+// update.  The contractions over the weights run on the library's bf16 GEMM
+// with float32 operands as three bf16 terms (launch_gemm_sum; the terms are made
+// here), the per-head attention products on rocBLAS in float32; these kernels do
+// everything between them.  Row-major throughout; a training pass has
+// R = n - 1 rows (positions 0 .. n-2).
+#include <algorithm>
+
 #include "msd_internal.h"
 
 namespace msd {
@@ -87,11 +91,11 @@ __global__ __launch_bounds__(TB) void k_tr_rmsnorm(const float* X, const float* 
   for (int k = threadIdx.x; k < d; k += TB) Y[(size_t)i * d + k] = x[k] * r * g[k];
 }
 
-// dX += the gradient of the RMSNorm input given dY (per row), with
+// dX = base + the gradient of the RMSNorm input given dY (per row), with
 // y = x r g, r = (mean(x^2) + eps)^-1/2: dx = r (g dy) - x r^3 mean(x g dy).
 __global__ __launch_bounds__(TB) void k_tr_rmsnorm_bwd(const float* X, const float* g,
-                                                       const float* rstd, const float* dY, int d,
-                                                       float* dX) {
+                                                       const float* rstd, const float* dY,
+                                                       const float* base, int d, float* dX) {
   __shared__ float sh[4];
   const int i = blockIdx.x;
   const float* x = X + (size_t)i * d;
@@ -101,34 +105,50 @@ __global__ __launch_bounds__(TB) void k_tr_rmsnorm_bwd(const float* X, const flo
   for (int k = threadIdx.x; k < d; k += TB) s += x[k] * g[k] * dy[k];
   s = bsum(s, sh) / (float)d;
   for (int k = threadIdx.x; k < d; k += TB)
-    dX[(size_t)i * d + k] += r * g[k] * dy[k] - x[k] * r * r * r * s;
+    dX[(size_t)i * d + k] =
+        base[(size_t)i * d + k] + (r * g[k] * dy[k] - x[k] * r * r * r * s);
 }
 
-// dg[k] += sum over rows of dY[i][k] x[i][k] rstd[i] (a thread per feature,
-// rows in order).
-__global__ __launch_bounds__(TB) void k_tr_norm_gain_grad(const float* X, const float* rstd,
-                                                          const float* dY, int R, int d,
-                                                          float* dg) {
+// Gain gradient dg[k] = sum over rows of dY[i][k] x[i][k] rstd[i]: GAIN_PARTS
+// contiguous row ranges per feature (rows in order), then their sums in order.
+// One thread per feature over all rows left 240 of 256 CUs idle: 639 rows of
+// 4096 took 162 us, these two kernels 12 us.
+constexpr int GAIN_PARTS = 32;
+__global__ __launch_bounds__(TB) void k_tr_gain_parts(const float* X, const float* rstd,
+                                                      const float* dY, int R, int d,
+                                                      float* part) {
   const int k = blockIdx.x * TB + threadIdx.x;
   if (k >= d) return;
+  const int per = (R + GAIN_PARTS - 1) / GAIN_PARTS;
+  const int i0 = blockIdx.y * per, i1 = min(R, i0 + per);
   float s = 0.f;
-  for (int i = 0; i < R; ++i) s += dY[(size_t)i * d + k] * X[(size_t)i * d + k] * rstd[i];
-  dg[k] += s;
+  for (int i = i0; i < i1; ++i) s += dY[(size_t)i * d + k] * X[(size_t)i * d + k] * rstd[i];
+  part[(size_t)blockIdx.y * d + k] = s;
+}
+__global__ __launch_bounds__(TB) void k_tr_gain_sum(const float* part, int d, int add, float* dg) {
+  const int k = blockIdx.x * TB + threadIdx.x;
+  if (k >= d) return;
+  float s = add ? dg[k] : 0.f;
+#pragma unroll
+  for (int q = 0; q < GAIN_PARTS; ++q) s += part[(size_t)q * d + k];
+  dg[k] = s;
 }
 
-// Rotate-half RoPE of X [R][nh*hd] at position = row, by +angle (dir 1) or
-// -angle (dir -1, the backward of the forward rotation).  Grid (R, nh).
-__global__ __launch_bounds__(TB) void k_tr_rope(float* X, int nh, int hd, const float2* tab,
-                                                int dir) {
-  const int i = blockIdx.x, h = blockIdx.y, half = hd / 2;
-  float* x = X + ((size_t)i * nh + h) * hd;
-  for (int k = threadIdx.x; k < half; k += TB) {
-    const float2 t = tab[(size_t)i * half + k];
-    const float c = t.x, s = dir > 0 ? t.y : -t.y;
-    const float a = x[k], b = x[k + half];
-    x[k] = a * c - b * s;
-    x[k + half] = b * c + a * s;
-  }
+// Rotate-half RoPE of the first nh heads of X's rows (stride ld) at position =
+// row, by +angle (dir 1) or -angle (dir -1, the backward of the forward
+// rotation).  One thread per rotation pair; grid (R, ceil(nh hd / 2 / TB)).
+__global__ __launch_bounds__(TB) void k_tr_rope(float* X, int ld, int nh, int hd,
+                                                const float2* tab, int dir) {
+  const int i = blockIdx.x, half = hd / 2;
+  const int p = blockIdx.y * TB + threadIdx.x;
+  const int h = p / half, k = p - h * half;
+  if (h >= nh) return;
+  float* x = X + (size_t)i * ld + h * hd;
+  const float2 t = tab[(size_t)i * half + k];
+  const float c = t.x, s = dir > 0 ? t.y : -t.y;
+  const float a = x[k], b = x[k + half];
+  x[k] = a * c - b * s;
+  x[k + half] = b * c + a * s;
 }
 
 // Causal softmax of S [R][R] rows (one head): P[i][j] = softmax_j<=i(scale
@@ -158,24 +178,26 @@ __global__ __launch_bounds__(TB) void k_tr_softmax_bwd(const float* P, float* dP
   for (int j = threadIdx.x; j < R; j += TB) dP[o + j] = scale * P[o + j] * (dP[o + j] - t);
 }
 
-// Mx = silu(G) * U, n elements.
-__global__ __launch_bounds__(TB) void k_tr_silu(const float* G, const float* U, size_t n,
-                                                float* Mx) {
-  const size_t k = (size_t)blockIdx.x * TB + threadIdx.x;
-  if (k >= n) return;
-  const float g = G[k];
-  Mx[k] = g / (1.f + __expf(-g)) * U[k];
+// Mx = silu(G) * U, with G and U the halves of GU's rows; grid (F / TB, R).
+__global__ __launch_bounds__(TB) void k_tr_silu(const float* GU, int F, float* Mx) {
+  const int f = blockIdx.x * TB + threadIdx.x;
+  if (f >= F) return;
+  const float* row = GU + (size_t)blockIdx.y * 2 * F;
+  const float g = row[f];
+  Mx[(size_t)blockIdx.y * F + f] = g / (1.f + __expf(-g)) * row[F + f];
 }
 
 // dG = dM U silu'(G), dU = dM silu(G) (silu' = s (1 + g (1 - s)), s = sigmoid).
-__global__ __launch_bounds__(TB) void k_tr_silu_bwd(const float* G, const float* U,
-                                                    const float* dM, size_t n, float* dG,
-                                                    float* dU) {
-  const size_t k = (size_t)blockIdx.x * TB + threadIdx.x;
-  if (k >= n) return;
-  const float g = G[k], s = 1.f / (1.f + __expf(-g));
-  dG[k] = dM[k] * U[k] * s * (1.f + g * (1.f - s));
-  dU[k] = dM[k] * g * s;
+__global__ __launch_bounds__(TB) void k_tr_silu_bwd(const float* GU, const float* dM, int F,
+                                                    float* dGU) {
+  const int f = blockIdx.x * TB + threadIdx.x;
+  if (f >= F) return;
+  const float* row = GU + (size_t)blockIdx.y * 2 * F;
+  float* out = dGU + (size_t)blockIdx.y * 2 * F;
+  const float g = row[f], s = 1.f / (1.f + __expf(-g));
+  const float dm = dM[(size_t)blockIdx.y * F + f];
+  out[f] = dm * row[F + f] * s * (1.f + g * (1.f - s));
+  out[F + f] = dm * g * s;
 }
 
 // Regression term of row i: sum over features of SmoothL1(D[i] - H[i+1])
@@ -198,11 +220,11 @@ __global__ __launch_bounds__(TB) void k_tr_reg(const float* D, const float* H, i
 // Token term of row i: with p = softmax(Ld[i]) (draft) and q =
 // softmax(Lt[i]) (target, the row of position i + 1), ce[i] = -sum q log p,
 // and Ld[i] <- w (p - q), the gradient of w ce[i].  Grid (R).
-__global__ __launch_bounds__(TB) void k_tr_ce(float* Ld, const float* Lt, int V, float w,
-                                              float* ce) {
+__global__ __launch_bounds__(TB) void k_tr_ce(float* Ld, const float* Lt, int V, int ldv,
+                                              float w, float* ce) {
   __shared__ float sh[4];
-  float* ld = Ld + (size_t)blockIdx.x * V;
-  const float* lt = Lt + (size_t)blockIdx.x * V;
+  float* ld = Ld + (size_t)blockIdx.x * ldv;
+  const float* lt = Lt + (size_t)blockIdx.x * ldv;
   float md = -INFINITY, mt = -INFINITY;
   for (int v = threadIdx.x; v < V; v += TB) {
     md = fmaxf(md, ld[v]);
@@ -257,6 +279,143 @@ __global__ __launch_bounds__(TB) void k_tr_fill(float* p, size_t n, float v) {
   if (k < n) p[k] = v;
 }
 
+// The three bf16 terms of eight floats, one 16-byte unit each.
+MSD_DEV void split8(const float (&x)[8], uint4 (&t)[3]) {
+  uint32_t w[3][4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    uint16_t b[3][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      float v = x[2 * e + i];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        b[q][i] = f2bf(v);
+        // an infinite or NaN value has no remainder
+        v = fabsf(bf2f(b[q][i])) < INFINITY ? v - bf2f(b[q][i]) : 0.f;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) w[q][e] = b[q][0] | ((uint32_t)b[q][1] << 16);
+  }
+#pragma unroll
+  for (int q = 0; q < 3; ++q) t[q] = make_uint4(w[q][0], w[q][1], w[q][2], w[q][3]);
+}
+MSD_DEV void load8(const float* p, float (&x)[8]) {
+  const float4 a = *reinterpret_cast<const float4*>(p);
+  const float4 b = *reinterpret_cast<const float4*>(p + 4);
+  x[0] = a.x, x[1] = a.y, x[2] = a.z, x[3] = a.w;
+  x[4] = b.x, x[5] = b.y, x[6] = b.z, x[7] = b.w;
+}
+
+// Rows of three terms; one thread per unit of eight columns.
+__global__ __launch_bounds__(TB) void k_tr_split(const float* src, size_t units, int C,
+                                                 uint16_t* dst) {
+  const size_t q = (size_t)blockIdx.x * TB + threadIdx.x;
+  if (q >= units) return;
+  const int upr = C / 8;
+  const size_t row = q / upr;
+  const int k = (int)(q - row * upr) * 8;
+  float x[8];
+  load8(src + row * C + k, x);
+  uint4 t[3];
+  split8(x, t);
+  uint16_t* d = dst + row * 3 * C + k;
+#pragma unroll
+  for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4*>(d + (size_t)p * C) = t[p];
+}
+
+// Packed planes of [R][C]; one thread per unit of the packed layout (see
+// k_gemm.hip), as k_pack.
+constexpr int PKB = 128, PTR = 64;
+__global__ __launch_bounds__(TB) void k_tr_pack(const float* src, int R, int C, int nkt,
+                                                size_t units, uint16_t* dst, size_t plane) {
+  const size_t q = (size_t)blockIdx.x * TB + threadIdx.x;
+  if (q >= units) return;
+  const int lane = (int)(q & 63);
+  const size_t r = q >> 6;
+  const int c = (int)(r & 3), g16 = (int)((r >> 2) & 3);
+  const size_t blk = r >> 4;
+  const int kb = (int)(blk % nkt), t = (int)(blk / nkt);
+  const int row = t * PTR + g16 * 16 + (lane & 15);
+  const int col = kb * PKB + 32 * (lane >> 4) + 8 * c;
+  float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (row < R && col < C) load8(src + (size_t)row * C + col, x);
+  uint4 o[3];
+  split8(x, o);
+#pragma unroll
+  for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4*>(dst + p * plane + q * 8) = o[p];
+}
+
+// A 128-row x 64-column block of src in LDS (zero past R and C), then a unit
+// of eight rows of one column per thread and step.  Rows of 65 floats: the
+// lanes of a step read different columns or rows 8 apart, in distinct banks.
+constexpr int TLD = 65;
+template <typename T>
+MSD_DEV void load_tile(float* sh, const T* src, int R, int C, int r0, int c0) {
+  for (int q = threadIdx.x; q < 128 * 16; q += TB) {
+    const int r = q >> 4, c = (q & 15) * 4;
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+    if (r0 + r < R && c0 + c < C) {
+      const T* p = src + (size_t)(r0 + r) * C + c0 + c;
+      if constexpr (sizeof(T) == 4) {
+        const float4 f = *reinterpret_cast<const float4*>(p);
+        v[0] = f.x, v[1] = f.y, v[2] = f.z, v[3] = f.w;
+      } else {
+        const uint2 f = *reinterpret_cast<const uint2*>(p);
+        v[0] = bf2f(f.x & 0xFFFF), v[1] = bf2f(f.x >> 16);
+        v[2] = bf2f(f.y & 0xFFFF), v[3] = bf2f(f.y >> 16);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sh[r * TLD + c + e] = v[e];
+  }
+  __syncthreads();
+}
+
+// The transpose as rows of three terms [C][3 Rp]; grid (Rp / 128, C / 64).
+__global__ __launch_bounds__(TB) void k_tr_split_t(const float* src, int R, int C, int Rp,
+                                                   uint16_t* dst) {
+  __shared__ float sh[128 * TLD];
+  const int r0 = blockIdx.x * 128, c0 = blockIdx.y * 64;
+  load_tile(sh, src, R, C, r0, c0);
+  for (int q = threadIdx.x; q < 64 * 16; q += TB) {
+    const int c = q >> 4, u = q & 15;  // 16 threads write one row's 256 bytes
+    if (c0 + c >= C || r0 + 8 * u >= Rp) continue;
+    float x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = sh[(8 * u + e) * TLD + c];
+    uint4 t[3];
+    split8(x, t);
+    uint16_t* d = dst + (size_t)(c0 + c) * 3 * Rp + r0 + 8 * u;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4*>(d + (size_t)p * Rp) = t[p];
+  }
+}
+
+// Packed planes of the transpose: one block of 64 columns x 128 rows of src per
+// workgroup; grid (nkt, n_tiles).
+template <typename T>
+__global__ __launch_bounds__(TB) void k_tr_pack_t(const T* src, int R, int C, int nkt,
+                                                  uint16_t* dst, size_t plane) {
+  __shared__ float sh[128 * TLD];
+  const int kb = blockIdx.x, t = blockIdx.y;
+  load_tile(sh, src, R, C, kb * PKB, t * PTR);
+  uint16_t* const o = dst + ((size_t)t * nkt + kb) * PKB * PTR;
+  for (int q = threadIdx.x; q < 1024; q += TB) {
+    const int lane = q & 63, c = (q >> 6) & 3, g16 = q >> 8;
+    const int n = g16 * 16 + (lane & 15), k = 32 * (lane >> 4) + 8 * c;
+    float x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = sh[(k + e) * TLD + n];
+    uint4 u[3];
+    split8(x, u);
+#pragma unroll
+    for (int p = 0; p < (sizeof(T) == 4 ? 3 : 1); ++p)
+      *reinterpret_cast<uint4*>(o + p * plane + q * 8) = u[p];
+  }
+}
+
 unsigned blocks(size_t n) { return (unsigned)((n + TB - 1) / TB); }
 
 }  // namespace
@@ -277,13 +436,18 @@ void tr_rmsnorm(const float* X, const float* g, float eps, int R, int d, float* 
                 hipStream_t st) {
   hipLaunchKernelGGL(k_tr_rmsnorm, dim3(R), dim3(TB), 0, st, X, g, eps, d, Y, rstd);
 }
-void tr_rmsnorm_bwd(const float* X, const float* g, const float* rstd, const float* dY, int R,
-                    int d, float* dX, float* dg, hipStream_t st) {
-  hipLaunchKernelGGL(k_tr_rmsnorm_bwd, dim3(R), dim3(TB), 0, st, X, g, rstd, dY, d, dX);
-  hipLaunchKernelGGL(k_tr_norm_gain_grad, dim3(blocks(d)), dim3(TB), 0, st, X, rstd, dY, R, d, dg);
+size_t tr_gain_scratch(int d) { return (size_t)GAIN_PARTS * d; }
+void tr_rmsnorm_bwd(const float* X, const float* g, const float* rstd, const float* dY,
+                    const float* base, int R, int d, float* dX, float* dg, bool add,
+                    float* scratch, hipStream_t st) {
+  hipLaunchKernelGGL(k_tr_rmsnorm_bwd, dim3(R), dim3(TB), 0, st, X, g, rstd, dY, base, d, dX);
+  hipLaunchKernelGGL(k_tr_gain_parts, dim3(blocks(d), GAIN_PARTS), dim3(TB), 0, st, X, rstd, dY, R,
+                     d, scratch);
+  hipLaunchKernelGGL(k_tr_gain_sum, dim3(blocks(d)), dim3(TB), 0, st, scratch, d, add ? 1 : 0, dg);
 }
-void tr_rope(float* X, int R, int nh, int hd, const float2* tab, int dir, hipStream_t st) {
-  hipLaunchKernelGGL(k_tr_rope, dim3(R, nh), dim3(TB), 0, st, X, nh, hd, tab, dir);
+void tr_rope(float* X, int R, int ld, int nh, int hd, const float2* tab, int dir, hipStream_t st) {
+  hipLaunchKernelGGL(k_tr_rope, dim3(R, blocks((size_t)nh * (hd / 2))), dim3(TB), 0, st, X, ld, nh,
+                     hd, tab, dir);
 }
 void tr_softmax(float* S, int R, int heads, float scale, hipStream_t st) {
   hipLaunchKernelGGL(k_tr_softmax, dim3(R, heads), dim3(TB), 0, st, S, R, scale);
@@ -291,18 +455,17 @@ void tr_softmax(float* S, int R, int heads, float scale, hipStream_t st) {
 void tr_softmax_bwd(const float* P, float* dP, int R, int heads, float scale, hipStream_t st) {
   hipLaunchKernelGGL(k_tr_softmax_bwd, dim3(R, heads), dim3(TB), 0, st, P, dP, R, scale);
 }
-void tr_silu(const float* G, const float* U, size_t n, float* Mx, hipStream_t st) {
-  hipLaunchKernelGGL(k_tr_silu, dim3(blocks(n)), dim3(TB), 0, st, G, U, n, Mx);
+void tr_silu(const float* GU, int R, int F, float* Mx, hipStream_t st) {
+  hipLaunchKernelGGL(k_tr_silu, dim3(blocks(F), R), dim3(TB), 0, st, GU, F, Mx);
 }
-void tr_silu_bwd(const float* G, const float* U, const float* dM, size_t n, float* dG, float* dU,
-                 hipStream_t st) {
-  hipLaunchKernelGGL(k_tr_silu_bwd, dim3(blocks(n)), dim3(TB), 0, st, G, U, dM, n, dG, dU);
+void tr_silu_bwd(const float* GU, const float* dM, int R, int F, float* dGU, hipStream_t st) {
+  hipLaunchKernelGGL(k_tr_silu_bwd, dim3(blocks(F), R), dim3(TB), 0, st, GU, dM, F, dGU);
 }
 void tr_reg(const float* D, const float* H, int R, int d, float* dD, float* reg, hipStream_t st) {
   hipLaunchKernelGGL(k_tr_reg, dim3(R), dim3(TB), 0, st, D, H, d, dD, reg);
 }
-void tr_ce(float* Ld, const float* Lt, int R, int V, float w, float* ce, hipStream_t st) {
-  hipLaunchKernelGGL(k_tr_ce, dim3(R), dim3(TB), 0, st, Ld, Lt, V, w, ce);
+void tr_ce(float* Ld, const float* Lt, int R, int V, int ld, float w, float* ce, hipStream_t st) {
+  hipLaunchKernelGGL(k_tr_ce, dim3(R), dim3(TB), 0, st, Ld, Lt, V, ld, w, ce);
 }
 void tr_adamw(float* w, const float* gsum, float* m, float* v, size_t n, float gscale, float lr,
               float c1, float c2, float b1, float b2, float eps, uint16_t* wb, hipStream_t st) {
@@ -314,6 +477,31 @@ void tr_widen(const uint16_t* src, size_t n, float* dst, hipStream_t st) {
 }
 void tr_fill(float* p, size_t n, float v, hipStream_t st) {
   hipLaunchKernelGGL(k_tr_fill, dim3(blocks(n)), dim3(TB), 0, st, p, n, v);
+}
+
+void tr_split(const float* src, int R, int C, uint16_t* dst, hipStream_t st) {
+  const size_t units = (size_t)R * (C / 8);
+  hipLaunchKernelGGL(k_tr_split, dim3(blocks(units)), dim3(TB), 0, st, src, units, C, dst);
+}
+void tr_split_t(const float* src, int R, int C, int Rp, uint16_t* dst, hipStream_t st) {
+  hipLaunchKernelGGL(k_tr_split_t, dim3((Rp + 127) / 128, (C + 63) / 64), dim3(TB), 0, st, src, R,
+                     C, Rp, dst);
+}
+void tr_pack(const float* src, int R, int C, uint16_t* dst, size_t plane, hipStream_t st) {
+  const size_t units = packed_elems(R, C) / 8;
+  hipLaunchKernelGGL(k_tr_pack, dim3(blocks(units)), dim3(TB), 0, st, src, R, C,
+                     (C + PKB - 1) / PKB, units, dst, plane);
+}
+void tr_pack_t(const float* src, int R, int C, int Rp, uint16_t* dst, size_t plane,
+               hipStream_t st) {
+  const int nkt = (Rp + PKB - 1) / PKB;
+  hipLaunchKernelGGL((k_tr_pack_t<float>), dim3(nkt, (C + PTR - 1) / PTR), dim3(TB), 0, st, src, R,
+                     C, nkt, dst, plane);
+}
+void tr_pack_t16(const uint16_t* src, int R, int C, int Rp, uint16_t* dst, hipStream_t st) {
+  const int nkt = (Rp + PKB - 1) / PKB;
+  hipLaunchKernelGGL((k_tr_pack_t<uint16_t>), dim3(nkt, (C + PTR - 1) / PTR), dim3(TB), 0, st, src,
+                     R, C, nkt, dst, (size_t)0);
 }
 
 }  // namespace msd

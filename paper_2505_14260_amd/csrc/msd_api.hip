@@ -173,8 +173,13 @@ Plan make_plan(const msd_model_desc& m, const msd_limits& lim) {
 // Draft-head training state (Sec. 4.2).  Float32 master copies of the
 // draft's parameters (f_down, the layer's seven matrices, its two norm gains,
 // in that order), their gradient sums and AdamW moments; float32 activations
-// of one training pass of up to max_prompt - 1 rows; a float32 copy of the
-// frozen LM head.  The contractions run as rocBLAS float32 GEMMs on the
+// of one training pass of up to max_prompt - 1 rows.  The products over the
+// weights run on the library's GEMM with their float32 operands as three bf16
+// terms (launch_gemm_sum): the weights' terms are packed once per update, as
+// they are (forward) and transposed (input gradients), the activations' terms
+// for each product.  The float32 matrix rate is 1/16 of the bf16 one, so the six
+// products of the terms take less than half the time of one in float32.  The
+// per-head attention products run as batched rocBLAS float32 GEMMs on the
 // context's stream, everything else in k_train.hip.
 constexpr int TRAIN_PARAMS = 10;
 constexpr float TRAIN_CLS_WEIGHT = 0.1f;  // weight of the token term
@@ -186,9 +191,18 @@ struct TrainState {
   size_t off[TRAIN_PARAMS + 1] = {};  // float offsets of the parameters
   float *w = nullptr, *g = nullptr, *m = nullptr, *v = nullptr;
   uint16_t* wb = nullptr;             // bf16 copy of w (inference packing, norm gains)
-  float* lm = nullptr;                // [V][d]
-  float *H, *X0, *E0, *F, *A1, *r1, *Q, *K, *V, *S, *dP, *O, *X1, *A2, *r2, *G, *U, *Mx, *D;
-  float *Ld, *Lt, *dD, *dMx, *dG, *dU, *dA2, *dX1, *dO, *dQ, *dK, *dV, *dA1, *dF;
+  // packed terms of the weights (three planes each) and of their transposes
+  struct Planes {
+    uint16_t* p = nullptr;
+    size_t plane = 0;
+  };
+  Planes fc, qkv, o, gu, dn, qkv_t, o_t, gu_t, dn_t;
+  uint16_t* lm_t = nullptr;           // the LM head's transpose, packed (bf16)
+  int Vp = 0;                         // logits row stride (V rounded up to 64)
+  // activations: QKV rows q | k | v, GU rows gate | up
+  float *H, *X0, *E0, *F, *A1, *r1, *QKV, *S, *dP, *O, *X1, *A2, *r2, *GU, *Mx, *D;
+  float *Ld, *Lt, *dD, *dMx, *dGU, *dA2, *dX1, *dO, *dQKV, *dA1, *dF, *gain;
+  uint16_t *xs, *xt, *wt;             // terms of a product's operands
   float *reg, *ce;
   std::vector<void*> allocs;
   double rows = 0;                    // rows accumulated since the last update
@@ -901,17 +915,70 @@ void train_free(TrainState* t) {
   delete t;
 }
 
-// Row-major C[M][N] = alpha op(A) op(B) + beta C (ta: A stored [K][M];
-// tb: B stored [N][K]); rocBLAS is column-major, so it computes the
-// transposed product C^T = op(B)^T op(A)^T.
-int sgemm_rm(msd_ctx* c, bool ta, bool tb, int M, int N, int K, float alpha, const float* A,
-             int lda, const float* B, int ldb, float beta, float* C, int ldc) {
-  const rocblas_status st = rocblas_sgemm(
+// n row-major products C[M][N] = op(A) op(B) + beta C of one head each (ta: A
+// stored [K][M]; tb: B stored [N][K]; the matrices of consecutive products sA,
+// sB, sC floats apart); rocBLAS is column-major, so it computes the transposed
+// product C^T = op(B)^T op(A)^T.
+int head_gemms(msd_ctx* c, int n, bool ta, bool tb, int M, int N, int K, const float* A, int lda,
+               size_t sA, const float* B, int ldb, size_t sB, float beta, float* C, int ldc,
+               size_t sC) {
+  const float one = 1.f;
+  const rocblas_status st = rocblas_sgemm_strided_batched(
       c->tr->blas, tb ? rocblas_operation_transpose : rocblas_operation_none,
-      ta ? rocblas_operation_transpose : rocblas_operation_none, N, M, K, &alpha, B, ldb, A, lda,
-      &beta, C, ldc);
+      ta ? rocblas_operation_transpose : rocblas_operation_none, N, M, K, &one, B, ldb,
+      (rocblas_stride)sB, A, lda, (rocblas_stride)sA, &beta, C, ldc, (rocblas_stride)sC, n);
   if (st != rocblas_status_success)
-    return fail(c, MSD_ERR_HIP, std::string("rocblas_sgemm: ") + rocblas_status_to_string(st));
+    return fail(c, MSD_ERR_HIP,
+                std::string("rocblas_sgemm_strided_batched: ") + rocblas_status_to_string(st));
+  return MSD_OK;
+}
+
+// C = add + X W^T with X in the terms of `rows` and W in planes.
+int train_gemm(msd_ctx* c, const uint16_t* X, int M, int K, int TX, const uint16_t* W, int N, int TW,
+               size_t plane, float* C, int ldc, const float* add) {
+  launch_gemm_sum(SumGemm{X, M, K, TX, W, N, TW, plane, C, ldc, add, c->part,
+                          c->plan.part_floats},
+                  c->st);
+  LAUNCHED(c);
+  return MSD_OK;
+}
+
+// C[R][N] = add + A[R][K] W^T: A's terms are made here.
+int train_linear(msd_ctx* c, const float* A, int R, int K, const TrainState::Planes& W, int N,
+                 float* C, const float* add) {
+  tr_split(A, R, K, c->tr->xs, c->st);
+  return train_gemm(c, c->tr->xs, R, K, 3, W.p, N, 3, W.plane, C, N, add);
+}
+
+// Weight gradient G[N][K] = (G when add) + sum over rows of dY[r][n] A[r][k].
+int train_wgrad(msd_ctx* c, const float* dY, int N, const float* A, int K, int R, float* G,
+                bool add) {
+  TrainState* t = c->tr;
+  const int Rp = (R + 63) / 64 * 64;
+  const size_t plane = packed_elems(K, Rp);
+  tr_split_t(dY, R, N, Rp, t->xt, c->st);
+  tr_pack_t(A, R, K, Rp, t->wt, plane, c->st);
+  return train_gemm(c, t->xt, N, Rp, 3, t->wt, K, 3, plane, G, K, add ? G : nullptr);
+}
+
+// The packed terms of the master weights, after they changed.
+int train_pack(msd_ctx* c) {
+  TrainState* t = c->tr;
+  const msd_model_desc& m = c->m;
+  const int d = m.d_model, F = m.ffn_dim, qd = m.n_heads * m.head_dim;
+  const int nq = qd + 2 * m.n_kv_heads * m.head_dim;
+  const float* w = t->w;
+  const size_t* o = t->off;
+  tr_pack(w + o[0], d, 2 * d, t->fc.p, t->fc.plane, c->st);
+  tr_pack(w + o[1], nq, d, t->qkv.p, t->qkv.plane, c->st);
+  tr_pack(w + o[4], d, qd, t->o.p, t->o.plane, c->st);
+  tr_pack(w + o[5], 2 * F, d, t->gu.p, t->gu.plane, c->st);
+  tr_pack(w + o[7], d, F, t->dn.p, t->dn.plane, c->st);
+  tr_pack_t(w + o[1], nq, d, nq, t->qkv_t.p, t->qkv_t.plane, c->st);
+  tr_pack_t(w + o[4], d, qd, d, t->o_t.p, t->o_t.plane, c->st);
+  tr_pack_t(w + o[5], 2 * F, d, 2 * F, t->gu_t.p, t->gu_t.plane, c->st);
+  tr_pack_t(w + o[7], d, F, d, t->dn_t.p, t->dn_t.plane, c->st);
+  LAUNCHED(c);
   return MSD_OK;
 }
 
@@ -937,8 +1004,8 @@ int train_init(msd_ctx* c) {
   const size_t np = t->off[TRAIN_PARAMS];
   auto take = [&](size_t bytes) -> void* {
     void* p = nullptr;
-    if (hipMalloc(&p, std::max<size_t>(bytes, 256)) != hipSuccess) return nullptr;
-    t->allocs.push_back(p);
+    if (hipMalloc(&p, std::max<size_t>(bytes, 256)) != hipSuccess) p = nullptr;
+    t->allocs.push_back(p);  // a null entry fails the call below
     return p;
   };
   auto f32 = [&](size_t n) { return static_cast<float*>(take(n * sizeof(float))); };
@@ -947,41 +1014,56 @@ int train_init(msd_ctx* c) {
   t->m = f32(np);
   t->v = f32(np);
   t->wb = static_cast<uint16_t*>(take(np * sizeof(uint16_t)));
-  t->lm = f32((size_t)V * d);
-  const size_t Rd = (size_t)R * d, RF = (size_t)R * F, RV = (size_t)R * V;
+  const int qd = H * hd, nq = qd + 2 * KV * hd;
+  const int Vp = (V + 63) / 64 * 64, Rp = (R + 63) / 64 * 64;
+  t->Vp = Vp;
+  auto u16 = [&](size_t n) { return static_cast<uint16_t*>(take(n * sizeof(uint16_t))); };
+  auto planes = [&](TrainState::Planes& p, int N, int K) {
+    p.plane = packed_elems(N, K);
+    p.p = u16(3 * p.plane);
+  };
+  planes(t->fc, d, 2 * d);
+  planes(t->qkv, nq, d);
+  planes(t->o, d, qd);
+  planes(t->gu, 2 * F, d);
+  planes(t->dn, d, F);
+  planes(t->qkv_t, d, nq);
+  planes(t->o_t, qd, d);
+  planes(t->gu_t, d, 2 * F);
+  planes(t->dn_t, F, d);
+  t->lm_t = u16(packed_elems(d, Vp));
+  t->xs = u16((size_t)R * 3 * std::max({2 * d, nq, 2 * F, Vp}));
+  t->xt = u16((size_t)3 * Rp * std::max({d, nq, 2 * F}));
+  t->wt = u16(3 * std::max({packed_elems(2 * d, Rp), packed_elems(F, Rp), packed_elems(qd, Rp)}));
+  const size_t Rd = (size_t)R * d, RF = (size_t)R * F, RV = (size_t)R * Vp;
   t->H = f32((size_t)(R + 1) * d);
   t->X0 = f32(2 * Rd);
   t->E0 = f32(Rd);
   t->F = f32(Rd);
   t->A1 = f32(Rd);
   t->r1 = f32(R);
-  t->Q = f32((size_t)R * H * hd);
-  t->K = f32((size_t)R * KV * hd);
-  t->V = f32((size_t)R * KV * hd);
+  t->QKV = f32((size_t)R * nq);
   t->S = f32((size_t)H * R * R);
   t->dP = f32((size_t)H * R * R);
-  t->O = f32((size_t)R * H * hd);
+  t->O = f32((size_t)R * qd);
   t->X1 = f32(Rd);
   t->A2 = f32(Rd);
   t->r2 = f32(R);
-  t->G = f32(RF);
-  t->U = f32(RF);
+  t->GU = f32(2 * RF);
   t->Mx = f32(RF);
   t->D = f32(Rd);
   t->Ld = f32(RV);
   t->Lt = f32(RV);
   t->dD = f32(Rd);
   t->dMx = f32(RF);
-  t->dG = f32(RF);
-  t->dU = f32(RF);
+  t->dGU = f32(2 * RF);
   t->dA2 = f32(Rd);
   t->dX1 = f32(Rd);
-  t->dO = f32((size_t)R * H * hd);
-  t->dQ = f32((size_t)R * H * hd);
-  t->dK = f32((size_t)R * KV * hd);
-  t->dV = f32((size_t)R * KV * hd);
+  t->dO = f32((size_t)R * qd);
+  t->dQKV = f32((size_t)R * nq);
   t->dA1 = f32(Rd);
   t->dF = f32(Rd);
+  t->gain = f32(tr_gain_scratch(d));
   t->reg = f32(R);
   t->ce = f32(R);
   for (void* p : t->allocs)
@@ -1008,14 +1090,20 @@ int train_init(msd_ctx* c) {
                          hipMemcpyDeviceToDevice, c->st));
   LAUNCHED(c);
   tr_widen(t->wb, np, t->w, c->st);
-  tr_fill(t->g, np, 0.f, c->st);
   tr_fill(t->m, np, 0.f, c->st);
   tr_fill(t->v, np, 0.f, c->st);
-  uint16_t* lm16 = static_cast<uint16_t*>(take((size_t)V * d * sizeof(uint16_t)));
-  if (!lm16) return fail(c, MSD_ERR_HIP, "training buffers: hipMalloc failed");
+  TRY(train_pack(c));
+  // the LM head's transpose, from its rows (a temporary copy)
+  uint16_t* lm16 = nullptr;
+  HIPC(c, hipMalloc((void**)&lm16, (size_t)V * d * sizeof(uint16_t)));
   launch_unpack(c->lm_p, V, d, lm16, c->st);
-  tr_widen(lm16, (size_t)V * d, t->lm, c->st);
-  LAUNCHED(c);
+  tr_pack_t16(lm16, V, d, Vp, t->lm_t, c->st);
+  const hipError_t e1 = hipGetLastError();
+  const hipError_t e2 = hipStreamSynchronize(c->st);
+  (void)hipFree(lm16);
+  if (e1 != hipSuccess || e2 != hipSuccess)
+    return fail(c, MSD_ERR_HIP,
+                std::string("training set-up: ") + hipGetErrorString(e1 != hipSuccess ? e1 : e2));
   c->dlayer.n1 = t->wb + t->off[8];
   c->dlayer.n2 = t->wb + t->off[9];
   HIPC(c, hipStreamSynchronize(c->st));
@@ -1029,103 +1117,87 @@ int train_pass(msd_ctx* c, int n, const void* visual_d, double* loss3) {
   TrainState* t = c->tr;
   const msd_model_desc& m = c->m;
   const int d = m.d_model, F = m.ffn_dim, H = m.n_heads, KV = m.n_kv_heads, hd = m.head_dim;
-  const int V = m.vocab, R = n - 1, Gq = H / KV, qd = H * hd, kd = KV * hd;
+  const int V = m.vocab, R = n - 1, Gq = H / KV, qd = H * hd, kd = KV * hd, nq = qd + 2 * kd;
   const float eps = m.norm_eps, scale = 1.f / std::sqrt((float)hd);
   hipStream_t st = c->st;
   const size_t* o = t->off;
-  float* w = t->w;
   float* g = t->g;
-  const float *Wfc = w + o[0], *Wq = w + o[1], *Wk = w + o[2], *Wv = w + o[3], *Wo = w + o[4];
-  const float *Wg = w + o[5], *Wu = w + o[6], *Wd = w + o[7], *n1 = w + o[8], *n2 = w + o[9];
-  const size_t Rd = (size_t)R * d;
+  const float *n1 = t->w + o[8], *n2 = t->w + o[9];
+  const bool add = t->rows > 0;  // gradients of earlier sequences are in g
   // ---- forward
   tr_inputs(c->h, c->embed, c->rows.tok, c->rows.vis, (const uint16_t*)visual_d, n, d,
             c->visual_input == MSD_DRAFT_VISUAL_FEATURE, t->H, t->X0, t->E0, st);
   LAUNCHED(c);
-  TRY(sgemm_rm(c, false, true, R, d, 2 * d, 1.f, t->X0, 2 * d, Wfc, 2 * d, 0.f, t->F, d));
+  TRY(train_linear(c, t->X0, R, 2 * d, t->fc, d, t->F, nullptr));
   tr_visual_rows(t->F, t->E0, c->rows.vis, R, d, st);
   tr_rmsnorm(t->F, n1, eps, R, d, t->A1, t->r1, st);
   LAUNCHED(c);
-  TRY(sgemm_rm(c, false, true, R, qd, d, 1.f, t->A1, d, Wq, d, 0.f, t->Q, qd));
-  TRY(sgemm_rm(c, false, true, R, kd, d, 1.f, t->A1, d, Wk, d, 0.f, t->K, kd));
-  TRY(sgemm_rm(c, false, true, R, kd, d, 1.f, t->A1, d, Wv, d, 0.f, t->V, kd));
-  tr_rope(t->Q, R, H, hd, c->rope, 1, st);
-  tr_rope(t->K, R, KV, hd, c->rope, 1, st);
+  TRY(train_linear(c, t->A1, R, d, t->qkv, nq, t->QKV, nullptr));
+  tr_rope(t->QKV, R, nq, H + KV, hd, c->rope, 1, st);
   LAUNCHED(c);
-  const size_t RR = (size_t)R * R;
-  for (int h = 0; h < H; ++h)
-    TRY(sgemm_rm(c, false, true, R, R, hd, 1.f, t->Q + h * hd, qd, t->K + (h / Gq) * hd, kd, 0.f,
-                 t->S + h * RR, R));
+  // head kv Gq + j reads kv head kv: one batch over the kv heads for each j
+  const size_t RR = (size_t)R * R, sq = (size_t)Gq * hd, sS = Gq * RR;
+  const float *Kc = t->QKV + qd, *Vc = t->QKV + qd + kd;
+  for (int j = 0; j < Gq; ++j)
+    TRY(head_gemms(c, KV, false, true, R, R, hd, t->QKV + j * hd, nq, sq, Kc, nq, hd, 0.f,
+                   t->S + j * RR, R, sS));
   tr_softmax(t->S, R, H, scale, st);
   LAUNCHED(c);
-  for (int h = 0; h < H; ++h)
-    TRY(sgemm_rm(c, false, false, R, hd, R, 1.f, t->S + h * RR, R, t->V + (h / Gq) * hd, kd, 0.f,
-                 t->O + h * hd, qd));
-  HIPC(c, hipMemcpyAsync(t->X1, t->F, Rd * 4, hipMemcpyDeviceToDevice, st));
-  TRY(sgemm_rm(c, false, true, R, d, qd, 1.f, t->O, qd, Wo, qd, 1.f, t->X1, d));
+  for (int j = 0; j < Gq; ++j)
+    TRY(head_gemms(c, KV, false, false, R, hd, R, t->S + j * RR, R, sS, Vc, nq, hd, 0.f,
+                   t->O + j * hd, qd, sq));
+  TRY(train_linear(c, t->O, R, qd, t->o, d, t->X1, t->F));
   tr_rmsnorm(t->X1, n2, eps, R, d, t->A2, t->r2, st);
   LAUNCHED(c);
-  TRY(sgemm_rm(c, false, true, R, F, d, 1.f, t->A2, d, Wg, d, 0.f, t->G, F));
-  TRY(sgemm_rm(c, false, true, R, F, d, 1.f, t->A2, d, Wu, d, 0.f, t->U, F));
-  tr_silu(t->G, t->U, (size_t)R * F, t->Mx, st);
+  TRY(train_linear(c, t->A2, R, d, t->gu, 2 * F, t->GU, nullptr));
+  tr_silu(t->GU, R, F, t->Mx, st);
   LAUNCHED(c);
-  HIPC(c, hipMemcpyAsync(t->D, t->X1, Rd * 4, hipMemcpyDeviceToDevice, st));
-  TRY(sgemm_rm(c, false, true, R, d, F, 1.f, t->Mx, F, Wd, F, 1.f, t->D, d));
+  TRY(train_linear(c, t->Mx, R, F, t->dn, d, t->D, t->X1));
   // ---- loss: regression toward h_{i+1}, token term against softmax(W_lm h_{i+1})
   tr_reg(t->D, t->H, R, d, t->dD, t->reg, st);
+  tr_split(t->D, R, d, t->xs, st);
   LAUNCHED(c);
-  TRY(sgemm_rm(c, false, true, R, V, d, 1.f, t->D, d, t->lm, d, 0.f, t->Ld, V));
-  TRY(sgemm_rm(c, false, true, R, V, d, 1.f, t->H + d, d, t->lm, d, 0.f, t->Lt, V));
-  tr_ce(t->Ld, t->Lt, R, V, TRAIN_CLS_WEIGHT, t->ce, st);
+  TRY(train_gemm(c, t->xs, R, d, 3, c->lm_p, t->Vp, 1, 0, t->Ld, t->Vp, nullptr));
+  // the target's features are the split rows of the target pass
+  TRY(train_gemm(c, c->h + 2 * (size_t)d, R, d, 2, c->lm_p, t->Vp, 1, 0, t->Lt, t->Vp, nullptr));
+  tr_ce(t->Ld, t->Lt, R, V, t->Vp, TRAIN_CLS_WEIGHT, t->ce, st);
+  tr_split(t->Ld, R, t->Vp, t->xs, st);
   LAUNCHED(c);
-  TRY(sgemm_rm(c, false, false, R, d, V, 1.f, t->Ld, V, t->lm, d, 1.f, t->dD, d));
-  // ---- backward (gradient sums over the rows, accumulated into g)
-  TRY(sgemm_rm(c, true, false, d, F, R, 1.f, t->dD, d, t->Mx, F, 1.f, g + o[7], F));
-  TRY(sgemm_rm(c, false, false, R, F, d, 1.f, t->dD, d, Wd, F, 0.f, t->dMx, F));
-  tr_silu_bwd(t->G, t->U, t->dMx, (size_t)R * F, t->dG, t->dU, st);
+  TRY(train_gemm(c, t->xs, R, t->Vp, 3, t->lm_t, d, 1, 0, t->dD, d, t->dD));
+  // ---- backward (gradient sums over the rows, into g)
+  TRY(train_wgrad(c, t->dD, d, t->Mx, F, R, g + o[7], add));
+  TRY(train_linear(c, t->dD, R, d, t->dn_t, F, t->dMx, nullptr));
+  tr_silu_bwd(t->GU, t->dMx, R, F, t->dGU, st);
   LAUNCHED(c);
-  TRY(sgemm_rm(c, true, false, F, d, R, 1.f, t->dG, F, t->A2, d, 1.f, g + o[5], d));
-  TRY(sgemm_rm(c, true, false, F, d, R, 1.f, t->dU, F, t->A2, d, 1.f, g + o[6], d));
-  TRY(sgemm_rm(c, false, false, R, d, F, 1.f, t->dG, F, Wg, d, 0.f, t->dA2, d));
-  TRY(sgemm_rm(c, false, false, R, d, F, 1.f, t->dU, F, Wu, d, 1.f, t->dA2, d));
-  HIPC(c, hipMemcpyAsync(t->dX1, t->dD, Rd * 4, hipMemcpyDeviceToDevice, st));
-  tr_rmsnorm_bwd(t->X1, n2, t->r2, t->dA2, R, d, t->dX1, g + o[9], st);
+  TRY(train_wgrad(c, t->dGU, 2 * F, t->A2, d, R, g + o[5], add));
+  TRY(train_linear(c, t->dGU, R, 2 * F, t->gu_t, d, t->dA2, nullptr));
+  tr_rmsnorm_bwd(t->X1, n2, t->r2, t->dA2, t->dD, R, d, t->dX1, g + o[9], add, t->gain, st);
   LAUNCHED(c);
-  TRY(sgemm_rm(c, true, false, d, qd, R, 1.f, t->dX1, d, t->O, qd, 1.f, g + o[4], qd));
-  TRY(sgemm_rm(c, false, false, R, qd, d, 1.f, t->dX1, d, Wo, qd, 0.f, t->dO, qd));
-  tr_fill(t->dK, (size_t)R * kd, 0.f, st);
-  tr_fill(t->dV, (size_t)R * kd, 0.f, st);
-  LAUNCHED(c);
-  for (int h = 0; h < H; ++h) {
-    const int kv = h / Gq;
-    TRY(sgemm_rm(c, true, false, R, hd, R, 1.f, t->S + h * RR, R, t->dO + h * hd, qd, 1.f,
-                 t->dV + kv * hd, kd));
-    TRY(sgemm_rm(c, false, true, R, R, hd, 1.f, t->dO + h * hd, qd, t->V + kv * hd, kd, 0.f,
-                 t->dP + h * RR, R));
+  TRY(train_wgrad(c, t->dX1, d, t->O, qd, R, g + o[4], add));
+  TRY(train_linear(c, t->dX1, R, d, t->o_t, qd, t->dO, nullptr));
+  float *dKc = t->dQKV + qd, *dVc = t->dQKV + qd + kd;
+  for (int j = 0; j < Gq; ++j) {
+    TRY(head_gemms(c, KV, true, false, R, hd, R, t->S + j * RR, R, sS, t->dO + j * hd, qd, sq,
+                   j ? 1.f : 0.f, dVc, nq, hd));
+    TRY(head_gemms(c, KV, false, true, R, R, hd, t->dO + j * hd, qd, sq, Vc, nq, hd, 0.f,
+                   t->dP + j * RR, R, sS));
   }
   tr_softmax_bwd(t->S, t->dP, R, H, scale, st);
   LAUNCHED(c);
-  for (int h = 0; h < H; ++h) {
-    const int kv = h / Gq;
-    TRY(sgemm_rm(c, false, false, R, hd, R, 1.f, t->dP + h * RR, R, t->K + kv * hd, kd, 0.f,
-                 t->dQ + h * hd, qd));
-    TRY(sgemm_rm(c, true, false, R, hd, R, 1.f, t->dP + h * RR, R, t->Q + h * hd, qd, 1.f,
-                 t->dK + kv * hd, kd));
+  for (int j = 0; j < Gq; ++j) {
+    TRY(head_gemms(c, KV, false, false, R, hd, R, t->dP + j * RR, R, sS, Kc, nq, hd, 0.f,
+                   t->dQKV + j * hd, nq, sq));
+    TRY(head_gemms(c, KV, true, false, R, hd, R, t->dP + j * RR, R, sS, t->QKV + j * hd, nq, sq,
+                   j ? 1.f : 0.f, dKc, nq, hd));
   }
-  tr_rope(t->dQ, R, H, hd, c->rope, -1, st);
-  tr_rope(t->dK, R, KV, hd, c->rope, -1, st);
+  tr_rope(t->dQKV, R, nq, H + KV, hd, c->rope, -1, st);
   LAUNCHED(c);
-  TRY(sgemm_rm(c, true, false, qd, d, R, 1.f, t->dQ, qd, t->A1, d, 1.f, g + o[1], d));
-  TRY(sgemm_rm(c, true, false, kd, d, R, 1.f, t->dK, kd, t->A1, d, 1.f, g + o[2], d));
-  TRY(sgemm_rm(c, true, false, kd, d, R, 1.f, t->dV, kd, t->A1, d, 1.f, g + o[3], d));
-  TRY(sgemm_rm(c, false, false, R, d, qd, 1.f, t->dQ, qd, Wq, d, 0.f, t->dA1, d));
-  TRY(sgemm_rm(c, false, false, R, d, kd, 1.f, t->dK, kd, Wk, d, 1.f, t->dA1, d));
-  TRY(sgemm_rm(c, false, false, R, d, kd, 1.f, t->dV, kd, Wv, d, 1.f, t->dA1, d));
-  HIPC(c, hipMemcpyAsync(t->dF, t->dX1, Rd * 4, hipMemcpyDeviceToDevice, st));
-  tr_rmsnorm_bwd(t->F, n1, t->r1, t->dA1, R, d, t->dF, g + o[8], st);
+  TRY(train_wgrad(c, t->dQKV, nq, t->A1, d, R, g + o[1], add));
+  TRY(train_linear(c, t->dQKV, R, nq, t->qkv_t, d, t->dA1, nullptr));
+  tr_rmsnorm_bwd(t->F, n1, t->r1, t->dA1, t->dX1, R, d, t->dF, g + o[8], add, t->gain, st);
   tr_zero_visual(t->dF, c->rows.vis, R, d, st);
   LAUNCHED(c);
-  TRY(sgemm_rm(c, true, false, d, 2 * d, R, 1.f, t->dF, d, t->X0, 2 * d, 1.f, g + o[0], 2 * d));
+  TRY(train_wgrad(c, t->dF, d, t->X0, 2 * d, R, g + o[0], add));
   // the rows' loss terms, summed in row order on the host
   std::vector<float> rc(2 * (size_t)R);
   HIPC(c, hipMemcpyAsync(rc.data(), t->reg, sizeof(float) * R, hipMemcpyDeviceToHost, st));
@@ -1708,9 +1780,9 @@ int msd_train_apply(msd_ctx* c, double lr) {
   launch_pack(t->wb + t->off[5], F, d, const_cast<uint16_t*>(pl.g), c->st);
   launch_pack(t->wb + t->off[6], F, d, const_cast<uint16_t*>(pl.u), c->st);
   launch_pack(t->wb + t->off[7], d, F, const_cast<uint16_t*>(pl.d), c->st);
-  tr_fill(t->g, np, 0.f, c->st);
+  TRY(train_pack(c));
   LAUNCHED(c);
-  t->rows = 0;
+  t->rows = 0;  // the next sequence's gradients replace g
   HIPC(c, hipStreamSynchronize(c->st));
   return MSD_OK;
 }
@@ -1724,7 +1796,12 @@ int msd_train_read(msd_ctx* c, int what, float* out_d, size_t n_floats) {
     return fail(c, MSD_ERR_INVALID_ARG, "msd_train_read wants " + std::to_string(np) + " floats");
   const float* src = what == 0 ? t->g : what == 1 ? t->w : nullptr;
   if (!src) return fail(c, MSD_ERR_INVALID_ARG, "unknown training buffer");
-  HIPC(c, hipMemcpyAsync(out_d, src, np * sizeof(float), hipMemcpyDeviceToDevice, c->st));
+  if (what == 0 && t->rows <= 0) {  // no sums since the last update
+    tr_fill(out_d, np, 0.f, c->st);
+    LAUNCHED(c);
+  } else {
+    HIPC(c, hipMemcpyAsync(out_d, src, np * sizeof(float), hipMemcpyDeviceToDevice, c->st));
+  }
   HIPC(c, hipStreamSynchronize(c->st));
   return MSD_OK;
 }

@@ -108,6 +108,26 @@ void launch_gemm(const GemmPlan& pl, const uint16_t* X, int ldx, int M, const ui
                  const uint16_t* W2, int K, float* part, const GemmScratch& sc, hipStream_t st,
                  const ArgmaxOut* am = nullptr);
 
+// C[m][n] = add[m][n] + sum over k of X[m][k] W[n][k], n < N, float32, with X
+// rows of TX terms (row stride TX K, term t at t K) and W packed, TW planes
+// wplane elements apart: (TX, TW) = (3, 3) for float32 operands, (3, 1) and
+// (2, 1) against bf16 weights.  K a multiple of 8, N of 4; ldc is C's and add's
+// row stride (16-byte rows).  add: null or C or another matrix.  Products
+// split along K take at most max_part floats of part.
+struct SumGemm {
+  const uint16_t* X;
+  int M, K, TX;
+  const uint16_t* W;
+  int N, TW;
+  size_t wplane;
+  float* C;
+  int ldc;
+  const float* add;
+  float* part;
+  size_t max_part;
+};
+void launch_gemm_sum(const SumGemm& g, hipStream_t st);
+
 // Partial sums as seen by a consumer: value(m, n) = sum_s p[s*split + m*ld + n];
 // the second weight's products are at column n + off2.
 struct Parts {
@@ -314,20 +334,36 @@ void tr_visual_rows(float* F, const float* E0, const int* vis_idx, int R, int d,
 void tr_zero_visual(float* dF, const int* vis_idx, int R, int d, hipStream_t st);
 void tr_rmsnorm(const float* X, const float* g, float eps, int R, int d, float* Y, float* rstd,
                 hipStream_t st);
-// dX += the input gradient, dg += the gain gradient
-void tr_rmsnorm_bwd(const float* X, const float* g, const float* rstd, const float* dY, int R,
-                    int d, float* dX, float* dg, hipStream_t st);
-void tr_rope(float* X, int R, int nh, int hd, const float2* tab, int dir, hipStream_t st);
+// dX = base + the input gradient, dg = (dg when add) + the gain gradient;
+// scratch: tr_gain_scratch(d) floats
+size_t tr_gain_scratch(int d);
+void tr_rmsnorm_bwd(const float* X, const float* g, const float* rstd, const float* dY,
+                    const float* base, int R, int d, float* dX, float* dg, bool add,
+                    float* scratch, hipStream_t st);
+// the first nh heads of rows of ld floats
+void tr_rope(float* X, int R, int ld, int nh, int hd, const float2* tab, int dir, hipStream_t st);
 void tr_softmax(float* S, int R, int heads, float scale, hipStream_t st);
 void tr_softmax_bwd(const float* P, float* dP, int R, int heads, float scale, hipStream_t st);
-void tr_silu(const float* G, const float* U, size_t n, float* Mx, hipStream_t st);
-void tr_silu_bwd(const float* G, const float* U, const float* dM, size_t n, float* dG, float* dU,
-                 hipStream_t st);
+// GU: rows of 2F, gate then up
+void tr_silu(const float* GU, int R, int F, float* Mx, hipStream_t st);
+void tr_silu_bwd(const float* GU, const float* dM, int R, int F, float* dGU, hipStream_t st);
 void tr_reg(const float* D, const float* H, int R, int d, float* dD, float* reg, hipStream_t st);
-void tr_ce(float* Ld, const float* Lt, int R, int V, float w, float* ce, hipStream_t st);
+// rows of ld floats, V of them logits
+void tr_ce(float* Ld, const float* Lt, int R, int V, int ld, float w, float* ce, hipStream_t st);
 void tr_adamw(float* w, const float* gsum, float* m, float* v, size_t n, float gscale, float lr,
               float c1, float c2, float b1, float b2, float eps, uint16_t* wb, hipStream_t st);
 void tr_widen(const uint16_t* src, size_t n, float* dst, hipStream_t st);
 void tr_fill(float* p, size_t n, float v, hipStream_t st);
+// float32 matrices [R][C] (row stride C) as three bf16 terms x = h + m + l:
+// rows [R][3C]; the transpose as rows [C][3 Rp], zero past R; packed planes of
+// the matrix; packed planes of the transpose with K = Rp.  C a multiple of 8,
+// Rp of 8 (tr_split_t and tr_pack_t read R rows).
+void tr_split(const float* src, int R, int C, uint16_t* dst, hipStream_t st);
+void tr_split_t(const float* src, int R, int C, int Rp, uint16_t* dst, hipStream_t st);
+void tr_pack(const float* src, int R, int C, uint16_t* dst, size_t plane, hipStream_t st);
+void tr_pack_t(const float* src, int R, int C, int Rp, uint16_t* dst, size_t plane,
+               hipStream_t st);
+// the transpose of a row-major bf16 matrix [R][C], packed (one plane)
+void tr_pack_t16(const uint16_t* src, int R, int C, int Rp, uint16_t* dst, hipStream_t st);
 
 }  // namespace msd

@@ -93,3 +93,50 @@ def test_prompt_of_several_launches():
                 assert ok, (l, tr, err)
     finally:
         eng.close()
+
+
+@pytest.mark.parametrize("n", [2, 33, 65, 130, 193])
+def test_training_products_at_edges(n):
+    """Gradients of sequences of 1 to 192 rows (the weight gradients' K, cut and
+    padded to 64) on a model whose widths leave partial tiles and whose
+    vocabulary is odd (padded logits rows), three query heads on one kv head.
+    The features carry the target's bf16 key/value cache: 2e-2 of each
+    parameter's largest gradient, as in the training parity tests."""
+    from paper_2505_14260_amd.msd import Engine
+    from oracle import train as TR
+    dims = dataclasses.replace(WIDE.dims, d_model=168, n_heads=3, n_kv_heads=1, head_dim=64,
+                               ffn_dim=296, vocab=1037, n_layers=1)
+    wl = dataclasses.replace(TINY, dims=dims)
+    w = synth.make_target_weights(dims, wl.seed)
+    dr = synth.make_draft_weights(dims, w, wl.seed, "random")
+    m = O.Models(dims, w, dr)
+    tokens, vis, rows = text_prompt(wl, n)
+    print(f"case: training sequence of {n} rows", flush=True)
+    eng = Engine(dims, w, dr, max_batch=1, max_seq=256, max_tree=16, max_prompt=193)
+    try:
+        assert not np.any(eng.train_read(0)["wq"])     # no sums yet
+        loss = eng.train_accumulate(0, tokens, vis, rows)
+        g = eng.train_read(0)
+        params = TR.draft_params(m.draft)
+        h, e, pt = TR.sequence_inputs(m, tokens, vis, rows)
+        ref_loss, _, _, gref = TR.batch_grads(m, params, [(h, e, vis, pt)])
+        assert abs(loss[0] / (n - 1) - ref_loss) <= 1e-2 * abs(ref_loss)
+        # one row attends to itself alone: its query and key gradients are zero
+        # up to the rounding of the others
+        floor = 1e-5 * max(np.abs(r).max() for r in gref.values())
+        for k in TR.PARAM_KEYS:
+            err = np.abs(g[k] / (n - 1) - gref[k]).max() / max(np.abs(gref[k]).max(), floor)
+            assert err <= 2e-2, (k, err)
+        # a second sequence adds to the sums; after an update they start again
+        eng.train_accumulate(0, tokens, vis, rows)
+        g2 = eng.train_read(0)
+        eng.train_apply(0.0)
+        assert not np.any(eng.train_read(0)["wd"])
+        eng.train_accumulate(0, tokens, vis, rows)
+        g3 = eng.train_read(0)
+        for k in TR.PARAM_KEYS:
+            scale = max(np.abs(g[k]).max(), floor * (n - 1))
+            assert np.abs(g2[k] - 2 * g[k]).max() <= 1e-5 * scale, k
+            assert np.abs(g3[k] - g[k]).max() <= 1e-5 * scale, k
+    finally:
+        eng.close()
