@@ -572,6 +572,7 @@ GemmPlan plan_gemm(int M, int N, int K, int nw, size_t max_part) {
     // rows, 7B-shaped output projection 15 us in one tile, 12 in two)
     const int fit = (M + 31) / 32;
     if (M <= 160 ? c.MT != fit && (c.MT != 2 || M <= 64) : c.MT < 2) continue;
+    if (c.MT == 3 && M > 320) continue;  // measured up to 320 rows; above, 4x3 reads less LDS
     // 32-bit byte offsets within a row tile
     if (c.MT > 2 && (size_t)32 * c.MT * 4 * K >= ((size_t)1 << 31)) continue;
     const int n_nt = (n_tiles * TILE_ROWS + 128 * c.NTW - 1) / (128 * c.NTW);

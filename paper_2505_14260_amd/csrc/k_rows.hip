@@ -209,9 +209,10 @@ MSD_DEV float row_rstd(const RowNorm& rn, int row) {
 // (row, head, rotation pair i): a block of ROPE_THREADS threads covers
 // ROPE_THREADS / (hd/2) heads of one row (hd/2 divides ROPE_THREADS).
 constexpr int ROPE_THREADS = 256;
+// heads: how many of the H + 2 KV heads to do (the first ones).
 template <int PG>
-__global__ __launch_bounds__(ROPE_THREADS) void k_rope_kv(Parts qkv, RowNorm rn, int H, int KV,
-                                                          int hd, const int* pos,
+__global__ __launch_bounds__(ROPE_THREADS) void k_rope_kv(Parts qkv, RowNorm rn, int heads, int H,
+                                                          int KV, int hd, const int* pos,
                                                           const int* row_seq,
                                                           const int* row_slot, const float2* tab,
                                                           uint16_t* q, uint16_t* kc,
@@ -222,7 +223,7 @@ __global__ __launch_bounds__(ROPE_THREADS) void k_rope_kv(Parts qkv, RowNorm rn,
   const int i = threadIdx.x % half;
   const int slot = row_slot[row];
   const int b = row_seq[row];
-  if (head >= H + 2 * KV || (head >= H && slot < 0)) return;
+  if (head >= heads || (head >= H && slot < 0)) return;
   // every load (sums of squares, table row, partials) issued before the
   // first use
   float sq[PART_GROUP];
@@ -252,6 +253,46 @@ __global__ __launch_bounds__(ROPE_THREADS) void k_rope_kv(Parts qkv, RowNorm rn,
     kr[i] = f2bf(y0);
     kr[i + half] = f2bf(y1);
   }
+}
+
+// The value heads of many rows.  A workgroup takes V_ROWS rows of 64 head dims
+// (one kv head) through LDS, so that the transposed cache is written along its
+// slots: consecutive rows have consecutive slots, 64 contiguous bytes per half
+// wave.  k_rope_kv writes two bytes per row there; at 624 rows (7B-shaped) it
+// took 33 us, the two kernels take 17 + 6 us.  Below V_MIN_ROWS the extra launch
+// costs more than the scattered writes.
+constexpr int V_ROWS = 32, V_MIN_ROWS = 128;
+template <int PG>
+__global__ __launch_bounds__(256) void k_v_cache(Parts qkv, RowNorm rn, int rows, int col0, int KV,
+                                                 int hd, const int* row_seq, const int* row_slot,
+                                                 uint16_t* vc, int S) {
+  __shared__ uint16_t sh[64][V_ROWS + 2];
+  const int r0 = blockIdx.x * V_ROWS;
+  const int c0 = blockIdx.y * 64;  // of the value columns; 64 divides hd
+#pragma unroll
+  for (int k = 0; k < V_ROWS * 16 / 256; ++k) {
+    const int q = threadIdx.x + 256 * k;
+    const int r = q >> 4, c = (q & 15) * 4;
+    const int row = min(r0 + r, rows - 1);
+    float sq[PART_GROUP];
+    ssq_begin(rn, row, sq);
+    const float4 v = part_sum4<PG>(qkv, row, col0 + c0 + c);
+    const float s = ssq_end(rn, row, sq);
+    sh[c][r] = f2bf(s * v.x);
+    sh[c + 1][r] = f2bf(s * v.y);
+    sh[c + 2][r] = f2bf(s * v.z);
+    sh[c + 3][r] = f2bf(s * v.w);
+  }
+  __syncthreads();
+  const int r = threadIdx.x & (V_ROWS - 1);
+  const int row = r0 + r;
+  if (row >= rows) return;
+  const int slot = row_slot[row];
+  if (slot < 0) return;
+  const int g = c0 / hd, e0 = c0 - g * hd;
+  uint16_t* const vr = vc + ((size_t)(row_seq[row] * KV + g) * hd + e0) * S + slot;
+#pragma unroll
+  for (int e = threadIdx.x / V_ROWS; e < 64; e += 256 / V_ROWS) vr[(size_t)e * S] = sh[e][r];
 }
 
 MSD_DEV float block_sum_1024(float v, float* sh) {
@@ -651,9 +692,14 @@ void launch_rope_kv(Parts qkv, RowNorm rn, int rows, int H, int KV, int hd, cons
                     uint16_t* q, uint16_t* kc, uint16_t* vc, int S, hipStream_t st) {
   if (rows <= 0) return;
   const int per_block = ROPE_THREADS / (hd / 2);
-  const dim3 grid(rows, (H + 2 * KV + per_block - 1) / per_block);
-  PG_DISPATCH(qkv.S, k_rope_kv, grid, dim3(ROPE_THREADS), 0, st, qkv, rn, H, KV, hd, pos, row_seq,
-              row_slot, rope_tab, q, kc, vc, S);
+  const bool many = rows > V_MIN_ROWS;
+  const int heads = many ? H + KV : H + 2 * KV;
+  const dim3 grid(rows, (heads + per_block - 1) / per_block);
+  PG_DISPATCH(qkv.S, k_rope_kv, grid, dim3(ROPE_THREADS), 0, st, qkv, rn, heads, H, KV, hd, pos,
+              row_seq, row_slot, rope_tab, q, kc, vc, S);
+  if (many)
+    PG_DISPATCH(qkv.S, k_v_cache, dim3((rows + V_ROWS - 1) / V_ROWS, KV * hd / 64), dim3(256), 0, st,
+                qkv, rn, rows, (H + KV) * hd, KV, hd, row_seq, row_slot, vc, S);
 }
 
 void launch_resid_norm(Parts pt, int col0, int rows, int d, int mode, float* x,
