@@ -592,7 +592,9 @@ __global__ __launch_bounds__(64 * NWV, 2) void k_tree_attn(AttnArgs a) {
 // last row) are split into contiguous quarters, one per wave, each with its
 // own online softmax; the waves' states merge through LDS (weights
 // exp(m_w - max)) and the workgroup writes the tile's output rows.  Tiles
-// are dealt longest first (the last query tiles see the most keys).
+// are dealt longest first (the last query tiles see the most keys).  Where
+// only some queries' outputs are wanted (the last layer of a pass over a
+// prompt), tiles without one end at once and the outputs are packed.
 constexpr int CAUSAL_WAVES = 4;
 template <int HD>
 __global__ __launch_bounds__(64 * CAUSAL_WAVES, 2) void k_causal_attn(AttnArgs a) {
@@ -615,6 +617,7 @@ __global__ __launch_bounds__(64 * CAUSAL_WAVES, 2) void k_causal_attn(AttnArgs a
   int node = qt * 32 + j;
   const bool valid = node < a.nq;
   if (!valid) node = a.nq - 1;
+  if (a.out_row && !__any(a.out_row[node] < 0)) return;  // the same rows in every wave
   const int HH = a.H * HD;
   bf16x8 qh[HD / 16], ql[HD / 16];
   load_q<HD>(qh, ql, a.q + (size_t)(sidx * a.nq + node) * 2 * HH + (size_t)head * HD, HH);
@@ -665,6 +668,8 @@ __global__ __launch_bounds__(64 * CAUSAL_WAVES, 2) void k_causal_attn(AttnArgs a
     const int jj = u & 31, d0 = 8 * (u >> 5);
     const int nd = qt * 32 + jj;
     if (nd >= a.nq) continue;
+    const int orow = a.out_row ? -1 - a.out_row[nd] : sidx * a.nq + nd - a.row0;
+    if (orow < 0) continue;
     float v[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -674,7 +679,7 @@ __global__ __launch_bounds__(64 * CAUSAL_WAVES, 2) void k_causal_attn(AttnArgs a
       for (int q = 0; q < NWV; ++q) o += wgt[q][jj] * so[q * E + e];
       v[i] = o * colm[jj];
     }
-    store_split8(a.out + (size_t)(sidx * a.nq + nd) * 2 * HH + (size_t)head * HD + d0, HH, v);
+    store_split8(a.out + (size_t)orow * 2 * HH + (size_t)head * HD + d0, HH, v);
   }
 }
 
@@ -705,7 +710,7 @@ void launch_tree_attention(AttnArgs a, hipStream_t st, hipEvent_t ev0, hipEvent_
 }
 
 void launch_causal_attention(AttnArgs a, hipStream_t st) {
-  const int items = a.n_seq * a.H * a.qtiles;
+  const int items = a.n_seq * a.H * (a.qtiles - a.row0 / 32);
   dim3 grid(items);
   if (a.hd == 128)
     hipLaunchKernelGGL(k_causal_attn<128>, grid, dim3(256), 0, st, a);

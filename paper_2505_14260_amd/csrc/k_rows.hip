@@ -46,24 +46,30 @@ __global__ __launch_bounds__(256) void k_embed(const uint16_t* E, const int* tok
   }
 }
 
-// Overwrites the visual rows of x with their embeddings (draft input rule for
-// visual positions: the embedding itself, no down-projection).
-__global__ __launch_bounds__(256) void k_visual_rows(const uint16_t* visual, const int* vis_idx,
-                                                     int d, float* x) {
+// The draft's layer input over a prompt.  Text rows come from f_down, which
+// runs over them alone (f: its output, packed).  Visual rows are their
+// embeddings (no down-projection), or with h the target's features of those
+// rows (the Visual Feature variant).
+__global__ __launch_bounds__(256) void k_draft_rows(const float* f, const uint16_t* visual,
+                                                    const uint16_t* h, const int* vis, int d,
+                                                    float* x) {
   const int row = blockIdx.x;
-  const int v = vis_idx[row];
-  if (v < 0) return;
-  for (int e = threadIdx.x; e < d; e += 256) x[(size_t)row * d + e] = bf2f(visual[(size_t)v * d + e]);
+  const int v = vis[row];
+  float* const xr = x + (size_t)row * d;
+  for (int e = threadIdx.x; e < d; e += 256) {
+    if (v < 0) xr[e] = f[(size_t)(-1 - v) * d + e];
+    else if (h) xr[e] = get_split(h + (size_t)row * 2 * d, d, e);
+    else xr[e] = bf2f(visual[(size_t)v * d + e]);
+  }
 }
 
-// Overwrites the visual rows of x with the target's features of those rows
-// (h: split rows of d): the draft input of the Visual Feature variant.
-__global__ __launch_bounds__(256) void k_visual_feature_rows(const uint16_t* h, const int* vis_idx,
-                                                             int d, float* x) {
-  const int row = blockIdx.x;
-  if (vis_idx[row] < 0) return;
-  const uint16_t* hr = h + (size_t)row * 2 * d;
-  for (int e = threadIdx.x; e < d; e += 256) x[(size_t)row * d + e] = get_split(hr, d, e);
+// out[i] = x[list[i]]; d is a multiple of 4.
+__global__ __launch_bounds__(256) void k_gather_rows(const float* x, const int* list, int d,
+                                                     float* out) {
+  const float* const src = x + (size_t)list[blockIdx.x] * d;
+  float* const dst = out + (size_t)blockIdx.x * d;
+  for (int e = 4 * threadIdx.x; e < d; e += 1024)
+    *reinterpret_cast<float4*>(dst + e) = *reinterpret_cast<const float4*>(src + e);
 }
 
 // cos/sin of pos * theta^(-2i/hd), evaluated in float64.
@@ -451,7 +457,7 @@ __global__ __launch_bounds__(256) void k_fc_input(const uint16_t* h, const float
                                                   const int* next_tok, const uint16_t* visual,
                                                   int d, uint16_t* out) {
   const int row = blockIdx.x;
-  const int hr = h_row[row];
+  const int hr = h_row ? h_row[row] : row;
   const int nt = next_tok[row];
   const uint16_t* e = (nt >= 0) ? E + (size_t)nt * d : visual + (size_t)(-1 - nt) * d;
   uint16_t* o = out + (size_t)row * 4 * d;
@@ -669,16 +675,16 @@ void launch_embed(const uint16_t* E, const int* tokens, const int* vis_idx,
   hipLaunchKernelGGL(k_embed, dim3(rows), dim3(256), 0, st, E, tokens, vis_idx, visual, d, x);
 }
 
-void launch_visual_rows(const uint16_t* visual, const int* vis_idx, int rows, int d, float* x,
-                        hipStream_t st) {
+void launch_draft_rows(const float* f, const uint16_t* visual, const uint16_t* h, const int* vis,
+                       int rows, int d, float* x, hipStream_t st) {
   if (rows <= 0) return;
-  hipLaunchKernelGGL(k_visual_rows, dim3(rows), dim3(256), 0, st, visual, vis_idx, d, x);
+  hipLaunchKernelGGL(k_draft_rows, dim3(rows), dim3(256), 0, st, f, visual, h, vis, d, x);
 }
 
-void launch_visual_feature_rows(const uint16_t* h, const int* vis_idx, int rows, int d, float* x,
-                                hipStream_t st) {
+void launch_gather_rows(const float* x, const int* list, int rows, int d, float* out,
+                        hipStream_t st) {
   if (rows <= 0) return;
-  hipLaunchKernelGGL(k_visual_feature_rows, dim3(rows), dim3(256), 0, st, h, vis_idx, d, x);
+  hipLaunchKernelGGL(k_gather_rows, dim3(rows), dim3(256), 0, st, x, list, d, out);
 }
 
 void launch_rope_table(float2* tab, int max_pos, int hd, double theta, hipStream_t st) {

@@ -575,20 +575,33 @@ RowNorm row_norm(const msd_ctx* c, int m0) {
   return RowNorm{c->ssq + (size_t)m0 * nblk, nblk, c->m.d_model, c->m.norm_eps};
 }
 
+// Rows of a prompt whose outputs are wanted of the last layer (its keys and
+// values are written for all): n rows, row0 on, or those of list (device;
+// out_row: their places, as AttnArgs takes them).
+struct Wanted {
+  int n, row0;
+  const int *list, *out_row;
+};
+
 // One decoder stack (the target's layers or the draft's single layer) over
 // n_seq * nq rows of c->x described by c->rows; c->xn must hold the first
 // layer's input norm.  tree_R < 0 selects causal attention, otherwise tree
-// attention over a region of tree_R slots.  After the last layer the rows
+// attention over a region of tree_R slots (want: causal attention of one
+// sequence).  After the last layer the rows
 // get x += ..., then final_xn = rmsnorm(x) * final_g when final_g and
 // final_xb = x when final_xb.
 int forward_layers(msd_ctx* c, bool draft, int n_seq, int nq, int tree_R, int max_ltot,
                    const uint16_t* final_g, uint16_t* final_xn, uint16_t* final_xb,
-                   const int* feat_dst = nullptr, float* feat = nullptr) {
+                   const int* feat_dst = nullptr, float* feat = nullptr,
+                   const Wanted* want = nullptr) {
   const msd_model_desc& m = c->m;
   const int rows = n_seq * nq;
   const int d = m.d_model, H = m.n_heads, KV = m.n_kv_heads, hd = m.head_dim, F = m.ffn_dim;
   const int nl = draft ? 1 : m.n_layers;
   const int ch = row_chunk(m, rows, call_cap(c, rows));
+  // the rows after the attention: all of them but in a last layer with want
+  int r = rows, rch = ch;
+  float* x = c->x;
   const int B = c->lim.max_batch, S = c->lim.max_seq;
   const size_t layer_kv = (size_t)B * KV * S * hd;
   for (int l = 0; l < nl; ++l) {
@@ -630,6 +643,19 @@ int forward_layers(msd_ctx* c, bool draft, int n_seq, int nq, int tree_R, int ma
     if (tree_R < 0) {
       a.qtiles = (nq + 31) / 32;
       a.n_chunks = 1;
+      if (want && l + 1 == nl) {
+        a.row0 = want->row0;
+        a.out_row = want->out_row;
+        r = want->n;
+        rch = row_chunk(m, r, call_cap(c, r));
+        if (want->list) {
+          x = reinterpret_cast<float*>(c->fcin);  // 4d bf16 a row: free until the draft's pass
+          launch_gather_rows(c->x, want->list, r, d, x, c->st);
+          LAUNCHED(c);
+        } else {
+          x = c->x + (size_t)want->row0 * d;
+        }
+      }
       launch_causal_attention(a, c->st);
     } else {
       const TreeChunks tc = plan_tree_chunks(m, n_seq, nq, max_ltot, c->plan.attn_floats);
@@ -641,31 +667,31 @@ int forward_layers(msd_ctx* c, bool draft, int n_seq, int nq, int tree_R, int ma
       launch_tree_attention(a, c->st, e0, e1);
     }
     LAUNCHED(c);
-    for (int m0 = 0; m0 < rows; m0 += ch) {
-      const int mc = std::min(ch, rows - m0);
+    for (int m0 = 0; m0 < r; m0 += rch) {
+      const int mc = std::min(rch, r - m0);
       TRY(gemm(c, GK_O, c->ao + (size_t)m0 * 2 * H * hd, 2 * H * hd, mc, pw.o, nullptr, d, H * hd,
                &pt));
-      launch_resid(pt, mc, d, RN_ADD, c->x + (size_t)m0 * d, w.n2, c->xn + (size_t)m0 * 2 * d, nullptr,
+      launch_resid(pt, mc, d, RN_ADD, x + (size_t)m0 * d, w.n2, c->xn + (size_t)m0 * 2 * d, nullptr,
                    c->ssq + (size_t)m0 * ssq_blocks(d), c->st);
       LAUNCHED(c);
     }
-    for (int m0 = 0; m0 < rows; m0 += ch) {
-      const int mc = std::min(ch, rows - m0);
+    for (int m0 = 0; m0 < r; m0 += rch) {
+      const int mc = std::min(rch, r - m0);
       TRY(gemm(c, GK_GATEUP, c->xn + (size_t)m0 * 2 * d, 2 * d, mc, pw.g, pw.u, F, d, &pt));
       launch_silu(pt, row_norm(c, m0), mc, F, c->act + (size_t)m0 * 2 * F, c->st);
       LAUNCHED(c);
     }
     const bool last = (l + 1 == nl);
     const uint16_t* g_next = last ? final_g : c->layers[l + 1].n1;
-    for (int m0 = 0; m0 < rows; m0 += ch) {
-      const int mc = std::min(ch, rows - m0);
+    for (int m0 = 0; m0 < r; m0 += rch) {
+      const int mc = std::min(rch, r - m0);
       TRY(gemm(c, GK_DOWN, c->act + (size_t)m0 * 2 * F, 2 * F, mc, pw.d, nullptr, d, F, &pt));
       if (last && final_g) {
         // the final feature h is materialised (LM head input, draft input)
-        launch_resid_norm(pt, 0, mc, d, RN_ADD, c->x + (size_t)m0 * d, final_g, m.norm_eps,
+        launch_resid_norm(pt, 0, mc, d, RN_ADD, x + (size_t)m0 * d, final_g, m.norm_eps,
                           final_xn + (size_t)m0 * 2 * d, nullptr, c->st);
       } else {
-        launch_resid(pt, mc, d, RN_ADD, c->x + (size_t)m0 * d, last ? nullptr : g_next,
+        launch_resid(pt, mc, d, RN_ADD, x + (size_t)m0 * d, last ? nullptr : g_next,
                      last ? nullptr : c->xn + (size_t)m0 * 2 * d,
                      (last && final_xb) ? final_xb + (size_t)m0 * 2 * d : nullptr,
                      last ? nullptr : c->ssq + (size_t)m0 * ssq_blocks(d), c->st,
@@ -678,10 +704,9 @@ int forward_layers(msd_ctx* c, bool draft, int n_seq, int nq, int tree_R, int ma
 }
 
 // Draft head on rows whose f_down input is in c->fcin (split rows of 2d):
-// f = f_down(concat), visual rows replaced by their embeddings, then the
-// decoder layer; features in c->x and c->xb, and in the feature slots
-// c->rows.dst names (-1: none).
-int draft_pass(msd_ctx* c, int n_seq, int nq, int tree_R, int max_ltot, const uint16_t* visual) {
+// f = f_down(concat), then the decoder layer; features in c->x and c->xb, and
+// in the feature slots c->rows.dst names (-1: none).
+int draft_pass(msd_ctx* c, int n_seq, int nq, int tree_R, int max_ltot) {
   const int d = c->m.d_model;
   const int rows = n_seq * nq;
   const int ch = row_chunk(c->m, rows, part_cap(rows));
@@ -689,31 +714,60 @@ int draft_pass(msd_ctx* c, int n_seq, int nq, int tree_R, int max_ltot, const ui
   for (int m0 = 0; m0 < rows; m0 += ch) {
     const int mc = std::min(ch, rows - m0);
     TRY(gemm(c, GK_FC, c->fcin + (size_t)m0 * 4 * d, 4 * d, mc, c->fc_p, nullptr, d, 2 * d, &pt));
-    launch_resid(pt, mc, d, RN_SET, c->x + (size_t)m0 * d, visual ? nullptr : c->dlayer.n1,
-                 visual ? nullptr : c->xn + (size_t)m0 * 2 * d, nullptr,
-                 visual ? nullptr : c->ssq + (size_t)m0 * ssq_blocks(d), c->st);
+    launch_resid(pt, mc, d, RN_SET, c->x + (size_t)m0 * d, c->dlayer.n1, c->xn + (size_t)m0 * 2 * d,
+                 nullptr, c->ssq + (size_t)m0 * ssq_blocks(d), c->st);
     LAUNCHED(c);
-  }
-  if (visual) {
-    if (c->visual_input == MSD_DRAFT_VISUAL_FEATURE)
-      launch_visual_feature_rows(c->h, c->rows.vis, rows, d, c->x, c->st);
-    else
-      launch_visual_rows(visual, c->rows.vis, rows, d, c->x, c->st);
-    LAUNCHED(c);
-    TRY(norm_rows(c, rows, c->dlayer.n1));
   }
   // the final features also go to their draft feature slots (rows.dst)
   return forward_layers(c, true, n_seq, nq, tree_R, max_ltot, nullptr, nullptr, c->xb,
                         c->rows.dst, c->dfeat);
 }
 
+// Draft head over the n rows of a prompt: f_down on its n_text text rows
+// (their inputs packed in c->fcin), visual rows as they are (their
+// embeddings, or the features c->h of the Visual Feature input), and the
+// decoder layer.  A prompt leaves the layer's keys and values of every row
+// and the feature of its last one, so the layer goes on past its cache with
+// that row alone.
+int draft_prompt(msd_ctx* c, int n, int n_text, const uint16_t* visual) {
+  const int d = c->m.d_model;
+  const int ch = row_chunk(c->m, n_text, part_cap(n_text));
+  const bool mixed = n_text != n;
+  float* f = mixed ? reinterpret_cast<float*>(c->xb) : c->x;  // xb: 2d bf16 a row
+  Parts pt;
+  for (int m0 = 0; m0 < n_text; m0 += ch) {
+    const int mc = std::min(ch, n_text - m0);
+    TRY(gemm(c, GK_FC, c->fcin + (size_t)m0 * 4 * d, 4 * d, mc, c->fc_p, nullptr, d, 2 * d, &pt));
+    launch_resid(pt, mc, d, RN_SET, f + (size_t)m0 * d, mixed ? nullptr : c->dlayer.n1,
+                 mixed ? nullptr : c->xn + (size_t)m0 * 2 * d, nullptr,
+                 mixed ? nullptr : c->ssq + (size_t)m0 * ssq_blocks(d), c->st);
+    LAUNCHED(c);
+  }
+  if (mixed) {
+    const bool feature = c->visual_input == MSD_DRAFT_VISUAL_FEATURE;
+    launch_draft_rows(f, visual, feature ? c->h : nullptr, c->rows.vis, n, d, c->x, c->st);
+    LAUNCHED(c);
+    TRY(norm_rows(c, n, c->dlayer.n1));
+  }
+  const Wanted want{1, n - 1, nullptr, nullptr};
+  return forward_layers(c, true, 1, n, -1, n, nullptr, nullptr, nullptr, c->rows.dst + (n - 1),
+                        c->dfeat, &want);
+}
+
 // The target over a prompt (or training sequence) of n rows in sequence slot
 // seq: row descriptors (the draft's next-token rows included), the slot's
-// KV cache rows [0, n) and the final features of every row in c->h.
+// KV cache rows [0, n) and the final features in c->h, of every row (all) or
+// packed of the text rows, the only ones that a draft without the Visual
+// Feature input reads.  The last layer then goes on past its cache with those
+// alone.  That and the same in the draft (draft_prompt) took a prompt of 576
+// visual and 48 text rows (7B-shaped, 32 layers) from 16.9 to 16.1 ms, of
+// 2,880 and 256 rows (4 layers) from 14.1 to 10.2 ms, of 93 text rows (4
+// layers) from 954 to 889 us.
 int prompt_target(msd_ctx* c, int seq, int n, const int32_t* tokens_h,
-                  const uint8_t* is_visual_h, const void* visual_d) {
+                  const uint8_t* is_visual_h, const void* visual_d, bool all) {
   const int d = c->m.d_model;
-  // row descriptors: tok, vis, pos, slot, seq, hrow, dst, nxt
+  // row descriptors: tok, vis (a text row: -1 - its place among them), pos,
+  // slot, seq, dst; per text row: hrow (its row), nxt
   std::vector<int> a(8 * (size_t)n);
   int* tok = a.data();
   int* vis = tok + n;
@@ -723,16 +777,19 @@ int prompt_target(msd_ctx* c, int seq, int n, const int32_t* tokens_h,
   int* hrow = sq + n;
   int* dst = hrow + n;
   int* nxt = dst + n;
+  int n_text = 0;
   for (int i = 0, v = 0; i < n; ++i) {
     tok[i] = is_visual_h[i] ? 0 : tokens_h[i];
-    vis[i] = is_visual_h[i] ? v++ : -1;
+    vis[i] = is_visual_h[i] ? v++ : -1 - n_text;
+    if (!is_visual_h[i]) hrow[n_text++] = i;
     pos[i] = slot[i] = i;
     sq[i] = seq;
-    hrow[i] = i;
     dst[i] = (i == n - 1) ? seq * FEAT : -1;
   }
-  for (int i = 0; i < n; ++i)
-    nxt[i] = (i + 1 < n) ? (is_visual_h[i + 1] ? -1 - vis[i + 1] : tokens_h[i + 1]) : 0;
+  for (int j = 0; j < n_text; ++j) {
+    const int i = hrow[j];
+    nxt[j] = (i + 1 < n) ? (is_visual_h[i + 1] ? -1 - vis[i + 1] : tokens_h[i + 1]) : 0;
+  }
   int hdr[2] = {0, seq};
   const size_t nb = sizeof(int) * (size_t)n;
   TRY(upload_many(c, {{c->rows.tok, tok, nb}, {c->rows.vis, vis, nb}, {c->rows.pos, pos, nb},
@@ -745,7 +802,9 @@ int prompt_target(msd_ctx* c, int seq, int n, const int32_t* tokens_h,
   launch_embed(c->embed, c->rows.tok, c->rows.vis, (const uint16_t*)visual_d, n, d, c->x, c->st);
   LAUNCHED(c);
   TRY(norm_rows(c, n, c->layers[0].n1));
-  return forward_layers(c, false, 1, n, -1, n, c->final_norm, c->h, nullptr);
+  const Wanted want{n_text, 0, c->rows.hrow, c->rows.vis};
+  return forward_layers(c, false, 1, n, -1, n, c->final_norm, c->h, nullptr, nullptr, nullptr,
+                        all || n_text == n ? nullptr : &want);
 }
 
 // LM head + top-k (and log-sum-exp) over the rows of c->xb: no final norm.
@@ -1383,18 +1442,20 @@ int msd_prefill(msd_ctx* c, int seq, int n, const int32_t* tokens_h, const uint8
     n_vis += is_visual_h[i] ? 1 : 0;
   }
   if (n_vis && !visual_d) return fail(c, MSD_ERR_INVALID_ARG, "visual rows missing");
-  TRY(prompt_target(c, seq, n, tokens_h, is_visual_h, visual_d));
+  const bool all = c->visual_input == MSD_DRAFT_VISUAL_FEATURE;  // features wanted of every row
+  TRY(prompt_target(c, seq, n, tokens_h, is_visual_h, visual_d, all));
   const int d = m.d_model;
-  TRY(lm_argmax(c, c->h + (size_t)(n - 1) * 2 * d, 1, c->tk_idx, nullptr));
+  const int n_text = n - n_vis;
+  TRY(lm_argmax(c, c->h + (size_t)((all ? n : n_text) - 1) * 2 * d, 1, c->tk_idx, nullptr));
   launch_set_int(c->d_root, seq, c->tk_idx, 0, c->st);
-  launch_set_int(c->nxt, n - 1, c->tk_idx, 0, c->st);
+  launch_set_int(c->nxt, n_text - 1, c->tk_idx, 0, c->st);
   LAUNCHED(c);
   // draft over the prompt: text rows f_down(Concat(h_i, e_{i+1})), visual rows
   // e_i (or h_i for the Visual Feature input)
-  launch_fc_input(c->h, nullptr, c->rows.hrow, c->embed, c->nxt, (const uint16_t*)visual_d, n, d,
-                  c->fcin, c->st);
+  launch_fc_input(c->h, nullptr, all ? c->rows.hrow : nullptr, c->embed, c->nxt,
+                  (const uint16_t*)visual_d, n_text, d, c->fcin, c->st);
   LAUNCHED(c);
-  TRY(draft_pass(c, 1, n, -1, n, n_vis ? (const uint16_t*)visual_d : nullptr));
+  TRY(draft_prompt(c, n, n_text, (const uint16_t*)visual_d));
   int st_len[2] = {n, 0};
   TRY(upload_many(c, {{c->d_len + seq, st_len, sizeof(int)}, {c->pend_n + seq, st_len + 1, sizeof(int)}}));
   int* back = c->stage + STAGE_INTS - 64;
@@ -1483,7 +1544,7 @@ int msd_draft_tree(msd_ctx* c, int n_seq, const int32_t* seqs_h, const msd_tree_
     launch_catchup_next(n_seq, c->seq_ids, c->d_len, c->pend_n, c->pend_next, r_max, PEND, FEAT,
                         c->rows, c->prefix, c->pend_h, c->embed, d, c->fcin, c->st);
     LAUNCHED(c);
-    TRY(draft_pass(c, n_seq, r_max, r_max, max_l + r_max, nullptr));
+    TRY(draft_pass(c, n_seq, r_max, r_max, max_l + r_max));
     for (int i = 0; i < n_seq; ++i) c->pend[seqs_h[i]] = 0;
   }
   for (int i = 0; i < n_seq; ++i) c->att_pre[i] = c->L[seqs_h[i]];
@@ -1507,7 +1568,7 @@ int msd_draft_tree(msd_ctx* c, int n_seq, const int32_t* seqs_h, const msd_tree_
       LAUNCHED(c);
       const int R = c->round_exp_end[dd];
       for (int i = 0; i < n_seq; ++i) c->att_keys[i] = c->L[seqs_h[i]] + R;
-      TRY(draft_pass(c, n_seq, nr, R, max_l + R, nullptr));
+      TRY(draft_pass(c, n_seq, nr, R, max_l + R));
       TRY(draft_head(c, n_seq * nr, c->round_k[dd]));
       prev_n = nr;
       prev_k = c->round_k[dd];
@@ -1529,7 +1590,7 @@ int msd_draft_tree(msd_ctx* c, int n_seq, const int32_t* seqs_h, const msd_tree_
       LAUNCHED(c);
       const int R = exp_base;
       for (int i = 0; i < n_seq; ++i) c->att_keys[i] = c->L[seqs_h[i]] + R;
-      TRY(draft_pass(c, n_seq, K, R, max_l + R, nullptr));
+      TRY(draft_pass(c, n_seq, K, R, max_l + R));
       TRY(draft_head(c, n_seq * K, K));
       launch_dyn_expand(c->pool, n_seq, c->tk_idx, c->tk_val, c->tk_lse, K, n_pool, exp_base, c->st);
       LAUNCHED(c);
@@ -1750,7 +1811,7 @@ int msd_train_accumulate(msd_ctx* c, int seq, int n, const int32_t* tokens_h,
   // the slot's cache now holds the training sequence: no longer a decode state
   c->ready[seq] = 0;
   c->L[seq] = 0;
-  TRY(prompt_target(c, seq, n, tokens_h, is_visual_h, visual_d));
+  TRY(prompt_target(c, seq, n, tokens_h, is_visual_h, visual_d, true));
   return train_pass(c, n, visual_d, loss_h);
 }
 

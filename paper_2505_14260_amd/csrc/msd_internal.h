@@ -174,6 +174,11 @@ struct AttnArgs {
   int S, H, KV, hd, nq, n_seq;
   int n_chunks, chunk_keys, qtiles;  // chunk_keys: multiple of 128 (tree mode)
   int xrep;               // XCDs per (sequence, kv head) pair (set by the launcher)
+  // causal mode (one sequence): the queries whose output is wanted.  out_row:
+  // per query -1 - its output row, or >= 0 for none; null: the queries from
+  // row0 on, whose output rows count from row0.
+  int row0;
+  const int* out_row;
   float* part_o;          // [items][32*hd] float16 partial outputs (tree mode, n_chunks > 1)
   float* part_ml;         // [items][32][2]
   int* att_cnt;           // [items] chunk arrivals per XCD (zero between launches)
@@ -212,15 +217,18 @@ void launch_rope_kv(Parts qkv, RowNorm rn, int rows, int H, int KV, int hd, cons
                     uint16_t* q, uint16_t* kc, uint16_t* vc, int S, hipStream_t st);
 void launch_rope_table(float2* tab, int max_pos, int hd, double theta, hipStream_t st);
 // out[row] = split row of [h | e] (2d values); h rows are split rows of d
-// (target features) when h, else float32 rows of hf (draft features).
+// (target features) when h, else float32 rows of hf (draft features); row
+// h_row[row] of them, or row itself when h_row is null.
 void launch_fc_input(const uint16_t* h, const float* hf, const int* h_row, const uint16_t* E,
                      const int* next_tok, const uint16_t* visual, int rows, int d, uint16_t* out,
                      hipStream_t st);
-void launch_visual_rows(const uint16_t* visual, const int* vis_idx, int rows, int d,
-                        float* x, hipStream_t st);
-// x rows with vis_idx >= 0 = the split rows h (the target features).
-void launch_visual_feature_rows(const uint16_t* h, const int* vis_idx, int rows, int d, float* x,
-                                hipStream_t st);
+// The draft's layer input over a prompt: a text row (vis < 0) is row -1 - vis
+// of f; a visual row is row vis of visual, or its own split row of h when h.
+void launch_draft_rows(const float* f, const uint16_t* visual, const uint16_t* h, const int* vis,
+                       int rows, int d, float* x, hipStream_t st);
+// out[i] = x[list[i]] (rows of d)
+void launch_gather_rows(const float* x, const int* list, int rows, int d, float* out,
+                        hipStream_t st);
 
 // -------------------------------------------------------- selection ----
 // scratch: topk_scratch_floats(rows, V) floats (8-byte aligned); it also

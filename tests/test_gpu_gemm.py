@@ -17,7 +17,7 @@ import synth
 from synth.configs import TINY, WIDE
 from oracle import model as M
 from oracle import msd as O
-from parity import row_close
+from parity import argmax_ok, compare_static_tree, oracle_draft_static, row_close
 
 pytestmark = pytest.mark.gpu
 
@@ -91,6 +91,53 @@ def test_prompt_of_several_launches():
             for view, ref, tr in ((tk, st.kv.k, False), (tv, st.kv.v, True)):
                 ok, err = row_close(rows_of(view, l, n, tr), ref[l, :n].reshape(n, -1), RTOL)
                 assert ok, (l, tr, err)
+    finally:
+        eng.close()
+
+
+@pytest.mark.parametrize("mode", ["embedding", "feature"])
+@pytest.mark.parametrize("runs", [
+    [1, 4, 1],                   # text, visual, text, ...: one row on either side
+    [3, 70, 40, 33, 2],          # tiles with both kinds, text between the visual rows
+    [0, 64, 96, 31, 1],          # tiles of visual rows only; the last row alone
+    [33],                        # no visual row
+], ids=["1-4-1", "3-70-40-33-2", "0-64-96-31-1", "33"])
+def test_prompt_of_text_and_visual_runs(runs, mode):
+    """A prompt's last layer runs over the rows whose features are read: the
+    text rows in any order, or all with the Visual Feature input.  The draft's
+    rows carry features of the whole target: 2e-2, as in the parity tests."""
+    from paper_2505_14260_amd.msd import Engine, make_static_spec
+    dims = dataclasses.replace(TINY.dims, n_layers=2)
+    n = sum(runs)
+    vis = np.concatenate([np.full(r, i & 1, dtype=np.uint8) for i, r in enumerate(runs)])
+    rng = np.random.default_rng(n)
+    tokens = np.where(vis, 0, rng.integers(0, dims.vocab, n)).astype(np.int32)
+    w = synth.make_target_weights(dims, TINY.seed)
+    dr = synth.make_draft_weights(dims, w, TINY.seed, "random")
+    rows = w["embed"][rng.integers(0, dims.vocab, int(vis.sum()))].copy()
+    m = O.Models(dims, w, dr)
+    st, first, _, logits = O.prefill(m, tokens, vis, rows, n + 64, visual_input=mode)
+    eng = Engine(dims, w, dr, max_batch=1, max_seq=(n + 160) // 64 * 64, max_tree=64, max_prompt=n)
+    try:
+        print(f"case: runs {runs}, {mode} input", flush=True)
+        eng.set_draft_input(mode)
+        got = eng.prefill(0, tokens, vis, rows)
+        assert got == first or argmax_ok(got, logits[n - 1])
+        tk, tv, dk, dv = eng.kv_views()
+        torch.cuda.synchronize()
+        parent, rank, _ = synth.static_tree_arrays(TINY.tree.paths)
+        spec = make_static_spec(parent[1:], rank[1:])
+        ref, logs, ranks = oracle_draft_static(m, st, TINY.tree.paths)  # catch-up + tree
+        caches = [(tk, tv, st.kv, dims.n_layers, RTOL), (dk, dv, st.dkv, 1, 2e-2)]
+        for k, v, kv, nl, tol in caches:
+            for l in range(nl):
+                for view, r, tr in ((k, kv.k, False), (v, kv.v, True)):
+                    ok, err = row_close(rows_of(view, l, n, tr), r[l, :n].reshape(n, -1), tol)
+                    assert ok, (nl, l, tr, err)
+        if got == first:
+            dev = eng.new_trees(1)
+            eng.draft_tree([0], spec, dev)
+            assert compare_static_tree(eng.trees_to_host(dev, 1)[0], ref, logs, ranks) >= ref.n // 2
     finally:
         eng.close()
 
