@@ -683,6 +683,216 @@ __global__ __launch_bounds__(64 * CAUSAL_WAVES, 2) void k_causal_attn(AttnArgs a
   }
 }
 
+// Causal attention of many queries: one workgroup per (sequence, head,
+// 128-row query tile), 32 rows per wave, every wave over all of its keys.  The
+// four waves share the tile's keys: blocks of WIDE_KEYS go to LDS by direct
+// loads, whole 128-byte lines, the next block while this one is used, so a
+// key is read from the L2 once per 128 queries instead of once per 32 (at
+// 3,136 rows and 32 heads the narrow kernel reads 2.5 GB, more than the L2s
+// hold of it; 370 us there, this kernel 180).  Two waves per SIMD; the matrix
+// work of a 32 x 32 block (two products, each with a hi and a lo half) is
+// 1,024 cycles, the chain scores - softmax - output about 1,750 a wave.
+// Blocks that every query of a wave sees skip the masks.  The
+// 16-byte units of a key row (of a value dim) are stored at
+// unit ^ swizzle(row), so that 16 lanes reading one unit of 16 rows take
+// distinct banks.
+constexpr int WIDE_KEYS = 64;
+template <int HD>
+struct WideState {
+  f32x16 o[HD / 32];
+  float m, l;  // running maximum of the raw scores; the lane's sum (its half of the keys)
+};
+
+template <int HD>
+MSD_DEV int wide_k_unit(int row, int chunk) {
+  constexpr int U = HD / 8;
+  return row * U + (chunk ^ (U == 16 ? row & 15 : (row >> 1) & 7));
+}
+MSD_DEV int wide_v_unit(int dim, int chunk) { return dim * 8 + (chunk ^ ((dim >> 1) & 7)); }
+
+// 32 keys from kb on, rows 32 sub.. of the LDS block.  MASK: some key is past
+// the query's own (my_last) or past k_valid.  c: scale * log2(e).
+template <int HD, bool MASK>
+MSD_DEV void wide_step(WideState<HD>& st, const bf16x8 (&qh)[HD / 16], const bf16x8 (&ql)[HD / 16],
+                       const uint4* ks, const uint4* vs, int sub, int kb, int my_last, int k_valid,
+                       float c) {
+  const int lane = threadIdx.x & 63;
+  const int i = lane & 31, h = lane >> 5;
+  const int row = sub * 32 + perm_key(i);
+  f32x16 s = {};
+#pragma unroll
+  for (int t = 0; t < HD / 16; ++t) {
+    const bf16x8 k = as_bf16x8(ks[wide_k_unit<HD>(row, HD / 16 * h + t)]);
+    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k, qh[t], s, 0, 0, 0);
+    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k, ql[t], s, 0, 0, 0);
+  }
+  float bm = -INFINITY;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    if (MASK) s[r] = kb + perm_key(8 * (r >> 2) + 4 * h + (r & 3)) <= my_last ? s[r] : -INFINITY;
+    bm = fmaxf(bm, s[r]);
+  }
+  bm = wave_xor32_max(bm);
+  const bool raise = bm * c > st.m * c + RESCALE_SLACK * 1.4426950408889634f;
+  if (__any(raise)) {
+    const float m_new = raise ? bm : st.m;
+    const float alpha = st.m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((st.m - m_new) * c);
+    st.l *= alpha;
+#pragma unroll
+    for (int dt = 0; dt < HD / 32; ++dt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) st.o[dt][r] *= alpha;
+    st.m = m_new;
+  }
+  const float off = st.m == -INFINITY ? 0.f : -st.m * c;  // all scores -inf: all weights 0
+  float p[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], c, off));
+    st.l += p[r];
+  }
+  uint4 pb[2], pl[2];
+#pragma unroll
+  for (int pk = 0; pk < 2; ++pk) {
+    uint32_t w[4], wl[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float p0 = p[pk * 8 + 2 * e], p1 = p[pk * 8 + 2 * e + 1];
+      w[e] = pack_bf16(p0, p1);
+      wl[e] = pack_bf16(p0 - __uint_as_float(w[e] << 16), p1 - __uint_as_float(w[e] & 0xFFFF0000u));
+    }
+    pb[pk] = make_uint4(w[0], w[1], w[2], w[3]);
+    pl[pk] = make_uint4(wl[0], wl[1], wl[2], wl[3]);
+  }
+  uint4 vf[HD / 32][2];
+#pragma unroll
+  for (int dt = 0; dt < HD / 32; ++dt)
+#pragma unroll
+    for (int pk = 0; pk < 2; ++pk) vf[dt][pk] = vs[wide_v_unit(dt * 32 + i, sub * 4 + pk * 2 + h)];
+  if (MASK) mask_v<HD>(vf, vf, kb, k_valid);
+#pragma unroll
+  for (int dt = 0; dt < HD / 32; ++dt)
+#pragma unroll
+    for (int pk = 0; pk < 2; ++pk) {
+      st.o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vf[dt][pk]), as_bf16x8(pb[pk]),
+                                                         st.o[dt], 0, 0, 0);
+      st.o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vf[dt][pk]), as_bf16x8(pl[pk]),
+                                                         st.o[dt], 0, 0, 0);
+    }
+}
+
+template <int HD>
+__global__ __launch_bounds__(256, 2) void k_causal_wide(AttnArgs a) {
+  constexpr int U = HD / 8, RPG = 64 / U;  // units of a key row; key rows per 1 KB load
+  constexpr int UNITS = WIDE_KEYS * U;     // of a block of keys (and of values)
+  __shared__ uint4 k0[UNITS], v0[UNITS], k1[UNITS], v1[UNITS];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int n_sh = a.n_seq * a.H;
+  const int tiles = (a.nq + 127) / 128;
+  const int qt = tiles - 1 - (int)blockIdx.x / n_sh;  // longest tiles first
+  const int sh = (int)blockIdx.x % n_sh;
+  const int head = sh % a.H, sidx = sh / a.H;
+  const int b = a.seq[sidx], P = a.prefix[sidx];
+  const int g = head / (a.H / a.KV);
+  if (a.out_row) {  // the same 128 rows in every wave
+    const int r0 = min(qt * 128 + lane, a.nq - 1), r1 = min(qt * 128 + 64 + lane, a.nq - 1);
+    if (!__any(a.out_row[r0] < 0 || a.out_row[r1] < 0)) return;
+  }
+  const int q0 = qt * 128 + 32 * w;
+  const int i = lane & 31, h = lane >> 5;
+  const int node = min(q0 + i, a.nq - 1);
+  const int HH = a.H * HD;
+  bf16x8 qh[HD / 16], ql[HD / 16];
+  load_q<HD>(qh, ql, a.q + (size_t)(sidx * a.nq + node) * 2 * HH + (size_t)head * HD, HH);
+  const size_t cache = (size_t)(b * a.KV + g) * a.S * HD;
+  const int bytes = a.S * HD * 2;
+  const __amdgpu_buffer_rsrc_t rk =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(a.kc + cache), 0, bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rv =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(a.vc + cache), 0, bytes, 0x00020000);
+  // Load q of a wave fills group w + 4 q of a block: RPG key rows, or eight
+  // value dims.  What lies past the buffer reads as zero; keys past the cache
+  // of all dims but the last read the next dim's first ones (masked).
+  const int krow = w * RPG + lane / U;
+  const int kvo = krow * HD * 2 + ((wide_k_unit<HD>(krow, lane % U) & (U - 1)) * 16);
+  const int vdim = w * 8 + (lane >> 3);
+  const int vvo = vdim * a.S * 2 + ((wide_v_unit(vdim, lane & 7) & 7) * 16);
+  const auto load = [&](uint4* ks, uint4* vs, int kb) {
+#pragma unroll
+    for (int q = 0; q < HD / 32; ++q) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rk, (__attribute__((address_space(3))) void*)(ks + (w + 4 * q) * 64), 16, kvo + q * 4096,
+          kb * HD * 2, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rv, (__attribute__((address_space(3))) void*)(vs + (w + 4 * q) * 64), 16,
+          vvo + q * 64 * a.S, kb * 2, 0, 0);
+    }
+  };
+  const int k_valid = P + a.nq;
+  const int k_end = P + min(qt * 128 + 128, a.nq);  // keys of the tile: [0, k_end)
+  // of the wave: none where it has no row
+  const int my_last = P + node;
+  const int w_end = q0 < a.nq ? P + min(q0 + 32, a.nq) : 0;
+  const float c = a.scale * 1.4426950408889634f;
+  WideState<HD> st;
+#pragma unroll
+  for (int dt = 0; dt < HD / 32; ++dt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) st.o[dt][r] = 0.f;
+  st.m = -INFINITY;
+  st.l = 0.f;
+  // One block: its loads have arrived (they are all that is in flight) and
+  // every wave is done with the other buffer, which the next block then fills.
+  const auto block = [&](uint4* ks, uint4* vs, uint4* kn, uint4* vn, int kb) {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    if (kb + WIDE_KEYS < k_end) load(kn, vn, kb + WIDE_KEYS);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int sub = 0; sub < WIDE_KEYS / 32; ++sub) {
+      const int k = kb + 32 * sub;
+      if (k >= w_end) continue;
+      if (k + 31 <= P + q0)
+        wide_step<HD, false>(st, qh, ql, ks, vs, sub, k, my_last, k_valid, c);
+      else
+        wide_step<HD, true>(st, qh, ql, ks, vs, sub, k, my_last, k_valid, c);
+    }
+  };
+  load(k0, v0, 0);
+#pragma unroll 1
+  for (int kb = 0; kb < k_end; kb += 2 * WIDE_KEYS) {
+    block(k0, v0, k1, v1, kb);
+    if (kb + WIDE_KEYS < k_end) block(k1, v1, k0, v0, kb + WIDE_KEYS);
+  }
+  if (q0 + i >= a.nq) return;
+  const int orow = a.out_row ? -1 - a.out_row[node] : sidx * a.nq + node - a.row0;
+  const float l = wave_xor32_sum(st.l);
+  if (orow < 0) return;
+  const float inv = l > 0.f ? 1.f / l : 0.f;
+  uint16_t* const out = a.out + (size_t)orow * 2 * HH + (size_t)head * HD;
+  // the lane's registers hold four consecutive dims at a time
+#pragma unroll
+  for (int dt = 0; dt < HD / 32; ++dt)
+#pragma unroll
+    for (int r = 0; r < 16; r += 4) {
+      const float v[4] = {st.o[dt][r] * inv, st.o[dt][r + 1] * inv, st.o[dt][r + 2] * inv,
+                          st.o[dt][r + 3] * inv};
+      uint32_t hw[2], lw[2];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        hw[e] = pack_bf16(v[2 * e], v[2 * e + 1]);
+        lw[e] = pack_bf16(v[2 * e] - __uint_as_float(hw[e] << 16),
+                          v[2 * e + 1] - __uint_as_float(hw[e] & 0xFFFF0000u));
+      }
+      const int d0 = dt * 32 + 2 * r + 4 * h;
+      *reinterpret_cast<uint2*>(out + d0) = make_uint2(hw[0], hw[1]);
+      *reinterpret_cast<uint2*>(out + HH + d0) = make_uint2(lw[0], lw[1]);
+    }
+}
+
 }  // namespace
 
 size_t attn_partial_floats(int n_seq, int KV, int qtiles, int n_chunks, int hd) {
@@ -709,9 +919,19 @@ void launch_tree_attention(AttnArgs a, hipStream_t st, hipEvent_t ev0, hipEvent_
   else launch_tree_hd<64>(a, st, ev0, ev1);
 }
 
-void launch_causal_attention(AttnArgs a, hipStream_t st) {
-  const int items = a.n_seq * a.H * (a.qtiles - a.row0 / 32);
-  dim3 grid(items);
+// wanted: the queries whose output is wanted.  The wide kernel walks a query's
+// keys in one chain, the narrow one in four: they meet at about 640 rows (32
+// heads of 128: 28.4 us wide and 28.8 narrow at 624 rows, 180 and 370 at
+// 3,136), and where few queries are wanted the narrow one has more workgroups.
+constexpr int WIDE_MIN_ROWS = 640;
+void launch_causal_attention(AttnArgs a, int wanted, hipStream_t st) {
+  if (wanted >= WIDE_MIN_ROWS) {
+    const dim3 grid(a.n_seq * a.H * ((a.nq + 127) / 128 - a.row0 / 128));
+    if (a.hd == 128) hipLaunchKernelGGL(k_causal_wide<128>, grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(k_causal_wide<64>, grid, dim3(256), 0, st, a);
+    return;
+  }
+  const dim3 grid(a.n_seq * a.H * (a.qtiles - a.row0 / 32));
   if (a.hd == 128)
     hipLaunchKernelGGL(k_causal_attn<128>, grid, dim3(256), 0, st, a);
   else

@@ -656,7 +656,7 @@ int forward_layers(msd_ctx* c, bool draft, int n_seq, int nq, int tree_R, int ma
           x = c->x + (size_t)want->row0 * d;
         }
       }
-      launch_causal_attention(a, c->st);
+      launch_causal_attention(a, r, c->st);
     } else {
       const TreeChunks tc = plan_tree_chunks(m, n_seq, nq, max_ltot, c->plan.attn_floats);
       a.qtiles = tc.qtiles;

@@ -191,7 +191,7 @@ struct AttnArgs {
 // the attention kernel and after the last kernel of the pass.
 void launch_tree_attention(AttnArgs a, hipStream_t st, hipEvent_t ev0 = nullptr,
                            hipEvent_t ev1 = nullptr);
-void launch_causal_attention(AttnArgs a, hipStream_t st);
+void launch_causal_attention(AttnArgs a, int wanted, hipStream_t st);
 size_t attn_partial_floats(int n_seq, int KV, int qtiles, int n_chunks, int hd);
 
 // ------------------------------------------------------------ row ops ----
