@@ -487,29 +487,43 @@ constexpr int TOPK_SLICE = 2048;
 constexpr int TOPK_PER = TOPK_SLICE / 256;  // logits per thread of a slice block
 constexpr int TOPK_MERGE_PER = 8;           // slice candidates per thread of the merge
 
-// The wave's best (value, id) over its lanes' offers.
-MSD_DEV void wave_best(float& v, int& id) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float ov = __shfl_xor(v, o);
-    const int oi = __shfl_xor(id, o);
-    if (better(ov, oi, v, id)) {
-      v = ov;
-      id = oi;
-    }
-  }
+// Floats as unsigned integers of the same order (-0 as +0; no NaN).
+MSD_DEV uint32_t order_key(float v) {
+  const uint32_t u = __float_as_uint(v + 0.f);
+  return u ^ ((int)u < 0 ? 0xFFFFFFFFu : 0x80000000u);
+}
+
+// The maximum over the wave, by lane moves inside the registers: rows of 16
+// lanes first, then row 0 into 1 and 2 into 3, then rows 1 into 2 and 3.
+MSD_DEV uint32_t wave_max(uint32_t x) {
+#define MSD_MAX_STEP(ctrl, rows) \
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, ctrl, rows, 0xf, false))
+  MSD_MAX_STEP(0x111, 0xf);  // row_shr:1
+  MSD_MAX_STEP(0x112, 0xf);
+  MSD_MAX_STEP(0x114, 0xf);
+  MSD_MAX_STEP(0x118, 0xf);
+  MSD_MAX_STEP(0x142, 0xa);  // row_bcast:15
+  MSD_MAX_STEP(0x143, 0xc);  // row_bcast:31
+#undef MSD_MAX_STEP
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
 }
 
 // The k best of the wave's candidates (N per lane, ids unique apart from
-// NO_ID), best first: k rounds of a wave-wide argmax in which the owner of
-// the winner retires it.  Lane 0 writes them to out_v / out_i.
+// NO_ID), best first: k rounds of a wave-wide maximum in which the owner of
+// the winner writes it to out_v / out_i and retires it.  The maximum runs in
+// registers and ids are compared only on a tie: with shuffles of (value, id)
+// pairs through LDS the k = 10 kernels below (10 rows, 151,936 ids) took
+// 15.8 and 13.9 us, so 12.1 and 11.6 us.
 template <int N>
 MSD_DEV void wave_select(const float (&cv)[N], const int (&ci)[N], int k, float* out_v,
                          int* out_i) {
   uint32_t taken = 0;
-  for (int q = 0; q < k; ++q) {
-    float bv = -INFINITY;
-    int bi = NO_ID, bj = -1;
+  float bv;
+  int bi, bj;
+  const auto best = [&] {
+    bv = -INFINITY;
+    bi = NO_ID;
+    bj = -1;
 #pragma unroll
     for (int j = 0; j < N; ++j) {
       if (!((taken >> j) & 1u) && better(cv[j], ci[j], bv, bi)) {
@@ -518,13 +532,21 @@ MSD_DEV void wave_select(const float (&cv)[N], const int (&ci)[N], int k, float*
         bj = j;
       }
     }
-    float wv = bv;
-    int wi = bi;
-    wave_best(wv, wi);
-    if (bj >= 0 && bi == wi) taken |= 1u << bj;
-    if ((threadIdx.x & 63) == 0) {
-      out_v[q] = wv;
-      out_i[q] = wi;
+  };
+  best();
+  for (int q = 0; q < k; ++q) {
+    const uint32_t key = order_key(bv);
+    const uint32_t top = wave_max(key);
+    uint64_t own = __ballot(key == top);
+    if (own & (own - 1)) {  // the lowest id of equal values
+      const uint32_t nid = key == top ? ~(uint32_t)bi : 0u;
+      own = __ballot(nid == wave_max(nid) && key == top);
+    }
+    if ((int)(threadIdx.x & 63) == __builtin_ctzll(own)) {
+      out_v[q] = bv;
+      out_i[q] = bi;
+      if (bj >= 0) taken |= 1u << bj;
+      best();
     }
   }
 }
