@@ -195,7 +195,6 @@ def host_tree(B, wl, first_token=1):
     return bytes(t), T
 
 
-FP32_PEAK_TFLOPS = 157.3   # MI355X dense fp32 matrix peak
 BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 matrix peak
 
 
@@ -230,7 +229,6 @@ def train_step_bench(args, wl, w, dr):
     n = len(prompt[0])
     eng = B.Engine(dims, w, dr, max_batch=1, max_seq=(n + 64 + 255) // 256 * 256, max_tree=64,
                    max_prompt=n)
-    eng.use_caller_weights(True)  # the target forward's rocBLAS products, as in the decode bench
     vis_t = torch.from_numpy(np.ascontiguousarray(prompt[2]).view(np.int16)).cuda()
     stream = torch.cuda.current_stream()
     acc, app, losses = [], [], []
@@ -261,9 +259,10 @@ def train_step_bench(args, wl, w, dr):
     a_ms, p_ms = float(np.median(acc)), float(np.median(app))
     step_ms = a_ms + p_ms
     achieved = (tf + tgt) / (step_ms * 1e-3) / 1e12
-    # the step's mix of work at the two peaks: the draft's fp32 training
-    # products and the target's bf16 forward
-    t_peak = tf / (FP32_PEAK_TFLOPS * 1e12) + tgt / (BF16_PEAK_TFLOPS * 1e12)
+    # the step's work at the bf16 peak: the draft's training products take six
+    # bf16 products each (three terms per operand), the target's forward two
+    # (counted in tgt)
+    t_peak = (6 * tf + tgt) / (BF16_PEAK_TFLOPS * 1e12)
     peak = (tf + tgt) / t_peak / 1e12
     print(json.dumps({
         "metric": "draft training step (Sec. 4.2), one sequence",
@@ -275,10 +274,10 @@ def train_step_bench(args, wl, w, dr):
         "roofline": {"bound": "mfma", "achieved": round(achieved, 2), "peak": round(peak, 2),
                      "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
                      "note": "all matrix work of the step over its time; the peak is the rate "
-                             "of this work mix with the draft's fp32 training products at the "
-                             "fp32 peak (157.3) and the target's bf16 forward (hi + lo "
+                             "of this work mix with six bf16 products for each of the draft's "
+                             "training products and the target's bf16 forward (hi + lo "
                              "products) at the bf16 peak (2500)"},
-        "dtype": "f32 (training), bf16 hi+lo (target forward)", "data": "synthetic",
+        "dtype": "f32 as three bf16 terms (training), bf16 hi+lo (target forward)", "data": "synthetic",
     }), flush=True)
 
 
@@ -396,9 +395,6 @@ def main():
     max_seq = (max_seq + 255) // 256 * 256
     eng = B.Engine(dims, w, dr, max_batch=1, max_seq=max_seq, max_tree=64,
                    max_prompt=wl.prompt_len)
-    # the engine keeps the row-major target weights it uploaded: the prompt's
-    # rocBLAS products read them in place instead of unpacking the packed copies
-    eng.use_caller_weights(True)
     if wl.tree.kind == "static":
         parent, rank, _ = synth.static_tree_arrays(wl.tree.paths)
         spec = B.make_static_spec(parent[1:], rank[1:])
@@ -580,7 +576,7 @@ def main():
                      "accept no drafted token here",
         },
         "prefill_ms": round(prefill_ms, 2),
-        "prefill_weights": "row-major target matrices read in place (msd_use_caller_weights)",
+        "prefill_weights": "packed target matrices, as every other pass",
         "cpu_baseline": None,
     }
     eng.close()

@@ -338,9 +338,7 @@ class Engine:
         msd_set_draft_input(self.ctx, DRAFT_VISUAL_INPUTS[visual_input])
 
     def use_caller_weights(self, enable=True):
-        """Prompt products read the row-major target weights this engine
-        uploaded (it keeps them until it is closed) instead of unpacking the
-        packed copies."""
+        """Accepted and without effect: every product reads the packed weights."""
         msd_use_caller_weights(self.ctx, enable)
 
     def train_accumulate(self, seq, tokens, is_visual, visual_bits):
