@@ -185,8 +185,29 @@ constexpr int TRAIN_PARAMS = 10;
 constexpr float TRAIN_CLS_WEIGHT = 0.1f;  // weight of the token term
 constexpr float ADAM_B1 = 0.9f, ADAM_B2 = 0.999f, ADAM_EPS = 1e-8f;
 
+// Scratch of the target's pass over a training sequence, whose products have
+// their own order of summation (k_feature.hip).
+struct FeatureScratch {
+  float* part = nullptr;        // partial sums
+  size_t part_floats = 0;
+  uint16_t* w[2] = {};          // row-major weights (rocBLAS)
+  size_t w_elems = 0;
+  const uint16_t* src[2] = {};  // the packed weight that each holds
+  void* blas_ws = nullptr;      // rocBLAS's workspace
+  rocblas_handle blas = nullptr;
+};
+constexpr int FEATURE_ROWS = 64;           // rows of a launch on the library's own kernel
+constexpr int FEATURE_BLAS_MIN_ROWS = 128; // passes over more rows run on rocBLAS,
+constexpr int FEATURE_BLAS_ROWS = 1024;    // in launches of up to so many
+constexpr size_t FEATURE_BLAS_WS = (size_t)32 << 20;
+// results of the hi and lo rows together up to which a launch (of fewer than
+// FEATURE_BLAS_ROWS rows; of as many) runs as one product over both
+constexpr size_t FEATURE_ONE_PRODUCT_BYTES = (size_t)192 << 20;
+constexpr size_t FEATURE_ONE_PRODUCT_FULL_BYTES = (size_t)128 << 20;
+
 struct TrainState {
   rocblas_handle blas = nullptr;
+  FeatureScratch feature;
   int Rmax = 0;
   size_t off[TRAIN_PARAMS + 1] = {};  // float offsets of the parameters
   float *w = nullptr, *g = nullptr, *m = nullptr, *v = nullptr;
@@ -505,6 +526,84 @@ int gemm(msd_ctx* c, int kind, const uint16_t* X, int ldx, int M, const uint16_t
   return MSD_OK;
 }
 
+// A product of the target's pass over a training sequence, M > FEATURE_ROWS
+// rows, on rocBLAS against row-major bf16 weights, each unpacked into a slot of
+// the scratch (kept for the pass's further launches).  bf16 products with
+// float32 sums and results, issued column-major (C^T = W X^T), give the consumer
+// X_hi[m] . W[n] + X_lo[m] . W[n] (at column w * off2 + n) as
+//  - one product over the 2M rows of K elements that the split rows are (row 2m
+//    the hi half of row m, row 2m + 1 its lo half; X's row stride is 2K), two
+//    partials per row.  Few output tiles are filled up with K slices, one strided
+//    batch each (2 ns partials per row: the hi rows of every slice, then the lo);
+//  - or two products over the views X and X + K, the second added to the first.
+int feature_blas(msd_ctx* c, const uint16_t* X, int M, const uint16_t* W, const uint16_t* W2, int N,
+                 int K, Parts* out) {
+  FeatureScratch& f = c->tr->feature;
+  const int nw = W2 ? 2 : 1, npad = (N + 63) / 64 * 64, ldp = npad * nw;
+  const bool one = 2 * (size_t)M * ldp * sizeof(float) <=
+                   (M < FEATURE_BLAS_ROWS ? FEATURE_ONE_PRODUCT_BYTES
+                                          : FEATURE_ONE_PRODUCT_FULL_BYTES);
+  const size_t rows = one ? 2 * (size_t)M : (size_t)M;
+  if (!f.blas || (size_t)N * K > f.w_elems || rows * ldp > f.part_floats)
+    return fail(c, MSD_ERR_INVALID_ARG, "internal: training product exceeds its buffers");
+  // slices of at least 1024 columns and a multiple of 8, output tiles counted
+  // at 256 x 256
+  int ns = 1;
+  if (one) {
+    const int tiles = (int)((rows + 255) / 256) * ((N + 255) / 256);
+    ns = std::max(1, std::min({8, 256 / std::max(tiles, 1), K / 1024}));
+    while (ns > 1 && (K % ns != 0 || (K / ns) % 8 != 0 || rows * ldp * ns > f.part_floats)) --ns;
+  }
+  const float plus = 1.f, zero = 0.f;
+  const auto bf16 = rocblas_datatype_bf16_r;
+  const auto f32 = rocblas_datatype_f32_r;
+  const auto tr = rocblas_operation_transpose, no = rocblas_operation_none;
+  for (int w = 0; w < nw; ++w) {
+    const uint16_t* const src = w ? W2 : W;
+    const uint16_t* const A = f.w[w];
+    if (f.src[w] != src) {
+      launch_unpack(src, N, K, f.w[w], c->st);
+      LAUNCHED(c);
+      f.src[w] = src;
+    }
+    rocblas_status st = rocblas_status_success;
+    if (ns > 1) {
+      // slice s of weight w at column (s nw + w) npad of rows of nw ns npad
+      const int ks = K / ns, ldc = nw * ns * npad;
+      float* const C = f.part + (size_t)w * npad;
+      st = rocblas_gemm_strided_batched_ex(f.blas, tr, no, N, (int)rows, ks, &plus, A, bf16, K, ks,
+                                           X, bf16, K, ks, &zero, C, f32, ldc,
+                                           (rocblas_stride)nw * npad, C, f32, ldc,
+                                           (rocblas_stride)nw * npad, ns, f32,
+                                           rocblas_gemm_algo_standard, 0, 0);
+    } else {
+      float* const C = f.part + (size_t)w * npad;
+      for (int h = 0; h < (one ? 1 : 2) && st == rocblas_status_success; ++h)
+        st = rocblas_gemm_ex(f.blas, tr, no, N, (int)rows, K, &plus, A, bf16, K, X + (size_t)h * K,
+                             bf16, one ? K : 2 * K, h ? &plus : &zero, C, f32, ldp, C, f32, ldp,
+                             f32, rocblas_gemm_algo_standard, 0, 0);
+    }
+    if (st != rocblas_status_success)
+      return fail(c, MSD_ERR_HIP, std::string("rocblas (training): ") + rocblas_status_to_string(st));
+  }
+  *out = ns > 1 ? Parts{f.part, 2 * ns, (size_t)nw * npad, 2 * nw * ns * npad, npad}
+         : one  ? Parts{f.part, 2, (size_t)ldp, 2 * ldp, npad}
+                : Parts{f.part, 1, (size_t)M * ldp, ldp, npad};
+  return MSD_OK;
+}
+
+// A product of the target's pass over a training sequence (its order of
+// summation: k_feature.hip).
+int feature_gemm(msd_ctx* c, const uint16_t* X, int M, const uint16_t* W, const uint16_t* W2, int N,
+                 int K, Parts* out) {
+  if (M > FEATURE_ROWS) return feature_blas(c, X, M, W, W2, N, K, out);
+  if (feature_part_floats(M, N, K, W2 ? 2 : 1) > c->tr->feature.part_floats)
+    return fail(c, MSD_ERR_INVALID_ARG, "internal: training product exceeds its buffers");
+  *out = launch_feature_gemm(X, 2 * K, M, W, W2, N, K, c->tr->feature.part, c->st);
+  LAUNCHED(c);
+  return MSD_OK;
+}
+
 // LM head and argmax over rows [0, M) of the split rows X: the best id of
 // each row (lowest on ties) to idx, the logits to logits ([M][V]) when given.
 // K is one chunk, so the GEMM reduces its columns itself and nothing of the
@@ -587,18 +686,25 @@ struct Wanted {
 // n_seq * nq rows of c->x described by c->rows; c->xn must hold the first
 // layer's input norm.  tree_R < 0 selects causal attention, otherwise tree
 // attention over a region of tree_R slots (want: causal attention of one
-// sequence).  After the last layer the rows
+// sequence; training: its products keep their own order of summation).  After the last layer the rows
 // get x += ..., then final_xn = rmsnorm(x) * final_g when final_g and
 // final_xb = x when final_xb.
 int forward_layers(msd_ctx* c, bool draft, int n_seq, int nq, int tree_R, int max_ltot,
                    const uint16_t* final_g, uint16_t* final_xn, uint16_t* final_xb,
                    const int* feat_dst = nullptr, float* feat = nullptr,
-                   const Wanted* want = nullptr) {
+                   const Wanted* want = nullptr, bool training = false) {
   const msd_model_desc& m = c->m;
   const int rows = n_seq * nq;
   const int d = m.d_model, H = m.n_heads, KV = m.n_kv_heads, hd = m.head_dim, F = m.ffn_dim;
   const int nl = draft ? 1 : m.n_layers;
-  const int ch = row_chunk(m, rows, call_cap(c, rows));
+  const int ch = !training ? row_chunk(m, rows, call_cap(c, rows))
+                 : rows > FEATURE_BLAS_MIN_ROWS ? FEATURE_BLAS_ROWS
+                                                : FEATURE_ROWS;
+  const auto product = [&](int kind, const uint16_t* X, int mc, const uint16_t* W,
+                           const uint16_t* W2, int N, int K, Parts* pt) {
+    return training ? feature_gemm(c, X, mc, W, W2, N, K, pt)
+                    : gemm(c, kind, X, 2 * K, mc, W, W2, N, K, pt);
+  };
   // the rows after the attention: all of them but in a last layer with want
   int r = rows, rch = ch;
   float* x = c->x;
@@ -612,8 +718,8 @@ int forward_layers(msd_ctx* c, bool draft, int n_seq, int nq, int tree_R, int ma
     Parts pt;
     for (int m0 = 0; m0 < rows; m0 += ch) {
       const int mc = std::min(ch, rows - m0);
-      TRY(gemm(c, GK_QKV, c->xn + (size_t)m0 * 2 * d, 2 * d, mc, pw.qkv, nullptr, (H + 2 * KV) * hd,
-               d, &pt));
+      TRY(product(GK_QKV, c->xn + (size_t)m0 * 2 * d, mc, pw.qkv, nullptr, (H + 2 * KV) * hd, d,
+                  &pt));
       launch_rope_kv(pt, row_norm(c, m0), mc, H, KV, hd, c->rows.pos + m0, c->rows.seq + m0,
                      c->rows.slot + m0, c->rope, c->q + (size_t)m0 * 2 * H * hd, kc, vc, S, c->st);
       LAUNCHED(c);
@@ -656,7 +762,8 @@ int forward_layers(msd_ctx* c, bool draft, int n_seq, int nq, int tree_R, int ma
           x = c->x + (size_t)want->row0 * d;
         }
       }
-      launch_causal_attention(a, r, c->st);
+      // training: the narrow kernel at every length, for its order of summation
+      launch_causal_attention(a, training ? 0 : r, c->st);
     } else {
       const TreeChunks tc = plan_tree_chunks(m, n_seq, nq, max_ltot, c->plan.attn_floats);
       a.qtiles = tc.qtiles;
@@ -669,15 +776,14 @@ int forward_layers(msd_ctx* c, bool draft, int n_seq, int nq, int tree_R, int ma
     LAUNCHED(c);
     for (int m0 = 0; m0 < r; m0 += rch) {
       const int mc = std::min(rch, r - m0);
-      TRY(gemm(c, GK_O, c->ao + (size_t)m0 * 2 * H * hd, 2 * H * hd, mc, pw.o, nullptr, d, H * hd,
-               &pt));
+      TRY(product(GK_O, c->ao + (size_t)m0 * 2 * H * hd, mc, pw.o, nullptr, d, H * hd, &pt));
       launch_resid(pt, mc, d, RN_ADD, x + (size_t)m0 * d, w.n2, c->xn + (size_t)m0 * 2 * d, nullptr,
                    c->ssq + (size_t)m0 * ssq_blocks(d), c->st);
       LAUNCHED(c);
     }
     for (int m0 = 0; m0 < r; m0 += rch) {
       const int mc = std::min(rch, r - m0);
-      TRY(gemm(c, GK_GATEUP, c->xn + (size_t)m0 * 2 * d, 2 * d, mc, pw.g, pw.u, F, d, &pt));
+      TRY(product(GK_GATEUP, c->xn + (size_t)m0 * 2 * d, mc, pw.g, pw.u, F, d, &pt));
       launch_silu(pt, row_norm(c, m0), mc, F, c->act + (size_t)m0 * 2 * F, c->st);
       LAUNCHED(c);
     }
@@ -685,7 +791,7 @@ int forward_layers(msd_ctx* c, bool draft, int n_seq, int nq, int tree_R, int ma
     const uint16_t* g_next = last ? final_g : c->layers[l + 1].n1;
     for (int m0 = 0; m0 < r; m0 += rch) {
       const int mc = std::min(rch, r - m0);
-      TRY(gemm(c, GK_DOWN, c->act + (size_t)m0 * 2 * F, 2 * F, mc, pw.d, nullptr, d, F, &pt));
+      TRY(product(GK_DOWN, c->act + (size_t)m0 * 2 * F, mc, pw.d, nullptr, d, F, &pt));
       if (last && final_g) {
         // the final feature h is materialised (LM head input, draft input)
         launch_resid_norm(pt, 0, mc, d, RN_ADD, x + (size_t)m0 * d, final_g, m.norm_eps,
@@ -764,7 +870,8 @@ int draft_prompt(msd_ctx* c, int n, int n_text, const uint16_t* visual) {
 // 2,880 and 256 rows (4 layers) from 14.1 to 10.2 ms, of 93 text rows (4
 // layers) from 954 to 889 us.
 int prompt_target(msd_ctx* c, int seq, int n, const int32_t* tokens_h,
-                  const uint8_t* is_visual_h, const void* visual_d, bool all) {
+                  const uint8_t* is_visual_h, const void* visual_d, bool all,
+                  bool training = false) {
   const int d = c->m.d_model;
   // row descriptors: tok, vis (a text row: -1 - its place among them), pos,
   // slot, seq, dst; per text row: hrow (its row), nxt
@@ -804,7 +911,7 @@ int prompt_target(msd_ctx* c, int seq, int n, const int32_t* tokens_h,
   TRY(norm_rows(c, n, c->layers[0].n1));
   const Wanted want{n_text, 0, c->rows.hrow, c->rows.vis};
   return forward_layers(c, false, 1, n, -1, n, c->final_norm, c->h, nullptr, nullptr, nullptr,
-                        all || n_text == n ? nullptr : &want);
+                        all || n_text == n ? nullptr : &want, training);
 }
 
 // LM head + top-k (and log-sum-exp) over the rows of c->xb: no final norm.
@@ -971,6 +1078,7 @@ void train_free(TrainState* t) {
   if (!t) return;
   for (void* p : t->allocs) (void)hipFree(p);
   if (t->blas) (void)rocblas_destroy_handle(t->blas);
+  if (t->feature.blas) (void)rocblas_destroy_handle(t->feature.blas);
   delete t;
 }
 
@@ -1050,47 +1158,15 @@ void train_shapes(const msd_model_desc& m, int (*sh)[2]) {
   for (int i = 0; i < TRAIN_PARAMS; ++i) sh[i][0] = s[i][0], sh[i][1] = s[i][1];
 }
 
-int train_init(msd_ctx* c) {
-  if (c->tr) return MSD_OK;
-  const msd_model_desc& m = c->m;
+// Lays out the activations of one training pass and, over the same bytes, the
+// scratch of the target's pass before it (base == nullptr: only measures them).
+size_t train_carve(TrainState* t, const msd_model_desc& m, const msd_limits& lim, char* base) {
   const int d = m.d_model, F = m.ffn_dim, H = m.n_heads, KV = m.n_kv_heads, hd = m.head_dim;
-  const int V = m.vocab, R = c->lim.max_prompt - 1;
-  TrainState* t = new TrainState;
-  t->Rmax = R;
-  int sh[TRAIN_PARAMS][2];
-  train_shapes(m, sh);
-  for (int i = 0; i < TRAIN_PARAMS; ++i) t->off[i + 1] = t->off[i] + (size_t)sh[i][0] * sh[i][1];
-  const size_t np = t->off[TRAIN_PARAMS];
-  auto take = [&](size_t bytes) -> void* {
-    void* p = nullptr;
-    if (hipMalloc(&p, std::max<size_t>(bytes, 256)) != hipSuccess) p = nullptr;
-    t->allocs.push_back(p);  // a null entry fails the call below
-    return p;
-  };
-  auto f32 = [&](size_t n) { return static_cast<float*>(take(n * sizeof(float))); };
-  t->w = f32(np);
-  t->g = f32(np);
-  t->m = f32(np);
-  t->v = f32(np);
-  t->wb = static_cast<uint16_t*>(take(np * sizeof(uint16_t)));
-  const int qd = H * hd, nq = qd + 2 * KV * hd;
+  const int V = m.vocab, R = lim.max_prompt - 1, qd = H * hd, nq = qd + 2 * KV * hd;
   const int Vp = (V + 63) / 64 * 64, Rp = (R + 63) / 64 * 64;
-  t->Vp = Vp;
-  auto u16 = [&](size_t n) { return static_cast<uint16_t*>(take(n * sizeof(uint16_t))); };
-  auto planes = [&](TrainState::Planes& p, int N, int K) {
-    p.plane = packed_elems(N, K);
-    p.p = u16(3 * p.plane);
-  };
-  planes(t->fc, d, 2 * d);
-  planes(t->qkv, nq, d);
-  planes(t->o, d, qd);
-  planes(t->gu, 2 * F, d);
-  planes(t->dn, d, F);
-  planes(t->qkv_t, d, nq);
-  planes(t->o_t, qd, d);
-  planes(t->gu_t, d, 2 * F);
-  planes(t->dn_t, F, d);
-  t->lm_t = u16(packed_elems(d, Vp));
+  Carver cv{base};
+  auto u16 = [&](size_t n) { return cv.take<uint16_t>(n); };
+  auto f32 = [&](size_t n) { return cv.take<float>(n); };
   t->xs = u16((size_t)R * 3 * std::max({2 * d, nq, 2 * F, Vp}));
   t->xt = u16((size_t)3 * Rp * std::max({d, nq, 2 * F}));
   t->wt = u16(3 * std::max({packed_elems(2 * d, Rp), packed_elems(F, Rp), packed_elems(qd, Rp)}));
@@ -1125,6 +1201,73 @@ int train_init(msd_ctx* c) {
   t->gain = f32(tr_gain_scratch(d));
   t->reg = f32(R);
   t->ce = f32(R);
+  // the target's pass: partial sums of the widest product in either form
+  // (feature_blas, launch_feature_gemm); the LM head and f_down are counted too,
+  // since the K slices of feature_blas are as many as fit
+  FeatureScratch& f = t->feature;
+  Carver fv{base};
+  const int rows = std::max(lim.max_prompt, lim.max_batch * MSD_MAX_TREE);
+  for (int mm : {16, 32, 64}) {
+    mm = std::min(mm, rows);
+    for (size_t n : {feature_part_floats(mm, nq, d, 1), feature_part_floats(mm, d, qd, 1),
+                     feature_part_floats(mm, F, d, 2), feature_part_floats(mm, d, F, 1),
+                     feature_part_floats(mm, d, 2 * d, 1), feature_part_floats(mm, V, d, 1)})
+      f.part_floats = std::max(f.part_floats, n);
+  }
+  if (lim.max_prompt > FEATURE_BLAS_MIN_ROWS) {
+    const size_t big = (size_t)std::min(FEATURE_BLAS_ROWS, rows) * layer_ldp(m);
+    f.part_floats = std::max({f.part_floats, big,
+                              std::min(2 * big, FEATURE_ONE_PRODUCT_BYTES / sizeof(float))});
+    f.w_elems = std::max({(size_t)nq * d, (size_t)d * qd, (size_t)F * d});
+    for (uint16_t*& w : f.w) w = fv.take<uint16_t>(f.w_elems);
+    f.blas_ws = fv.take<char>(FEATURE_BLAS_WS);
+  }
+  f.part = fv.take<float>(f.part_floats);
+  return std::max(cv.off, fv.off);
+}
+
+int train_init(msd_ctx* c) {
+  if (c->tr) return MSD_OK;
+  const msd_model_desc& m = c->m;
+  const int d = m.d_model, F = m.ffn_dim, H = m.n_heads, KV = m.n_kv_heads, hd = m.head_dim;
+  const int V = m.vocab, R = c->lim.max_prompt - 1;
+  TrainState* t = new TrainState;
+  t->Rmax = R;
+  int sh[TRAIN_PARAMS][2];
+  train_shapes(m, sh);
+  for (int i = 0; i < TRAIN_PARAMS; ++i) t->off[i + 1] = t->off[i] + (size_t)sh[i][0] * sh[i][1];
+  const size_t np = t->off[TRAIN_PARAMS];
+  auto take = [&](size_t bytes) -> void* {
+    void* p = nullptr;
+    if (hipMalloc(&p, std::max<size_t>(bytes, 256)) != hipSuccess) p = nullptr;
+    t->allocs.push_back(p);  // a null entry fails the call below
+    return p;
+  };
+  auto f32 = [&](size_t n) { return static_cast<float*>(take(n * sizeof(float))); };
+  t->w = f32(np);
+  t->g = f32(np);
+  t->m = f32(np);
+  t->v = f32(np);
+  t->wb = static_cast<uint16_t*>(take(np * sizeof(uint16_t)));
+  const int qd = H * hd, nq = qd + 2 * KV * hd;
+  const int Vp = (V + 63) / 64 * 64;
+  t->Vp = Vp;
+  auto u16 = [&](size_t n) { return static_cast<uint16_t*>(take(n * sizeof(uint16_t))); };
+  auto planes = [&](TrainState::Planes& p, int N, int K) {
+    p.plane = packed_elems(N, K);
+    p.p = u16(3 * p.plane);
+  };
+  planes(t->fc, d, 2 * d);
+  planes(t->qkv, nq, d);
+  planes(t->o, d, qd);
+  planes(t->gu, 2 * F, d);
+  planes(t->dn, d, F);
+  planes(t->qkv_t, d, nq);
+  planes(t->o_t, qd, d);
+  planes(t->gu_t, d, 2 * F);
+  planes(t->dn_t, F, d);
+  t->lm_t = u16(packed_elems(d, Vp));
+  train_carve(t, m, c->lim, static_cast<char*>(take(train_carve(t, m, c->lim, nullptr))));
   for (void* p : t->allocs)
     if (!p) {
       train_free(t);
@@ -1134,6 +1277,14 @@ int train_init(msd_ctx* c) {
       rocblas_set_stream(t->blas, c->st) != rocblas_status_success) {
     train_free(t);
     return fail(c, MSD_ERR_HIP, "rocblas handle");
+  }
+  FeatureScratch& f = t->feature;
+  if (f.blas_ws && (rocblas_create_handle(&f.blas) != rocblas_status_success ||
+                    rocblas_set_stream(f.blas, c->st) != rocblas_status_success ||
+                    rocblas_set_workspace(f.blas, f.blas_ws, FEATURE_BLAS_WS) !=
+                        rocblas_status_success)) {
+    train_free(t);
+    return fail(c, MSD_ERR_HIP, "rocblas handle of the target's pass");
   }
   c->tr = t;
   // the draft's parameters from the packed copies the decoder uses (and the
@@ -1811,7 +1962,9 @@ int msd_train_accumulate(msd_ctx* c, int seq, int n, const int32_t* tokens_h,
   // the slot's cache now holds the training sequence: no longer a decode state
   c->ready[seq] = 0;
   c->L[seq] = 0;
-  TRY(prompt_target(c, seq, n, tokens_h, is_visual_h, visual_d, true));
+  // the slots' bytes were activations of the last sequence
+  c->tr->feature.src[0] = c->tr->feature.src[1] = nullptr;
+  TRY(prompt_target(c, seq, n, tokens_h, is_visual_h, visual_d, true, true));
   return train_pass(c, n, visual_d, loss_h);
 }
 

@@ -151,6 +151,13 @@ struct RowNorm {
   float eps;
 };
 
+// Products of the target's pass over a training sequence (k_feature.hip): up to
+// 64 rows, partial sums over chunks of feature_chunk blocks.
+int feature_chunk(int M, int N, int K, int nw, int wgs = 256);
+size_t feature_part_floats(int M, int N, int K, int nw);
+Parts launch_feature_gemm(const uint16_t* X, int ldx, int M, const uint16_t* W, const uint16_t* W2,
+                          int N, int K, float* part, hipStream_t st);
+
 // ----------------------------------------------------------- attention ----
 constexpr int ATT_MAX_SEQ = 8;
 #ifndef MSD_TREE_WAVES
