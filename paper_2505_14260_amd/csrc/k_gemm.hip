@@ -40,6 +40,7 @@ struct GemmArgs {
   int n_tiles, nkt;    // 64-row tiles and 128-column blocks of W
   int n_mt, n_nt, nw;  // row tiles, column tiles per weight, weights
   int S, bps;          // K chunks, blocks per chunk
+  int fold;            // blocks per sum (see the kernel)
   float* part;
   size_t part_split;
   int ldp, off2;
@@ -96,23 +97,34 @@ MSD_DEV constexpr int vmcnt_imm(int n) { return 0x0f70 | (n & 15) | ((n >> 4) <<
 // outside is in voffset: rows past M (the record count ends at row M),
 // columns past K and blocks past the chunk (voffset 2^31) read zeros.
 //
-// The sum of a row takes its products in the same order whatever MT and NTW
-// are; K chunks are summed by the consumer in chunk order.
+// Sums.  Every add to a float32 sum rounds at the sum's size, so the error of a
+// product grows with the root of the adds that one accumulator takes (2.5e-8 of
+// the result's root mean square per root of an add of 16 columns, measured).
+// The accumulators therefore take `fold` blocks of 128 columns (sum_blocks) and
+// are then added to sums of their own.  Where the registers allow it (tiles of up
+// to 32 x 256 or 64 x 128 per workgroup, where K can be as short as a block) the
+// lo products, 2^-8 of the hi ones, have accumulators of their own too.
+// Against float64, K = 4096, one chunk: 5.7e-7 in one accumulator, 2.0e-7 folded
+// every four blocks, 2.65e-7 every seven; K = 256: 1.4e-7 -> 0.7e-7; K = 11008:
+// 9.7e-7 -> 2.0e-7 and 2.65e-7.  The fold costs a tile of 128 x 256 (accumulators
+// in the upper half of the register file, three moves and an add each) 3 to 6%,
+// the smaller ones up to 2%.  Tiles with more sums than 128 registers a lane have
+// no room for a second set.
+//
+// K chunks are summed by the consumer in chunk order.
 //
 // POL: cache policy of the weight loads.  A weight that only one row tile
 // reads is streamed non-temporally (policy 2: 27 rows, 7B-shaped gate+up
 // 35 -> 32 us); with more row tiles their reads meet in L2 (policy 0).
 //
-// Measured (one launch, weights from HBM; us), 7B-shaped q/k/v, output,
-// gate+up, down; before: weight-streaming kernels of up to 64 rows a launch,
-// rocBLAS from 129 prompt rows on (without unpacking its weights):
-//    27 rows   20.2,  9.3, 34.8, 19.1 -> 18.4,  7.7,  31.6, 16.8
-//    61 rows   25.2, 12.6, 38.5, 23.5 -> 22.4,  9.7,  38.0, 20.7
-//   108 rows   50,   25,   77,   47   -> 29,   15,    43,   31
-//   624 rows   77,   41,  218,  112   -> 100,  39,   172,   92  (1.1-1.3 PFLOP/s)
-//  1024 rows                             148,  55,   277,  138  (1.25-1.39 PFLOP/s)
-// Bound: HBM up to about 100 rows, then the matrix cores: at 624 rows they
-// are 82% busy inside a workgroup, at about 2.15 GHz.
+// Measured (one launch, weights from HBM; us), 7B-shaped q/k/v, output, gate+up,
+// down, unfolded (with tiles of up to 128 x 512) -> folded:
+//    27 rows    18.9,  8.6,  31.7,  18.0 ->  19.6,  9.1,  32.1,  17.7
+//    61 rows    24.1, 10.5,  38.0,  21.5 ->  24.4, 11.5,  38.8,  21.3
+//   108 rows    30.5, 11.9,  51.0,  30.2 ->  36.2, 12.2,  55.7,  29.6
+//   624 rows   109.9, 41.4, 188.4, 102.9 -> 112.1, 42.2, 208.4,  98.2  (0.99-1.15 PFLOP/s)
+//  1600 rows   282,   99,   460,   231   -> 269,  101,   527,   267    (1.06-1.20 PFLOP/s)
+// Bound: HBM up to about 100 rows, then the matrix cores.
 //
 // TX, TW: terms of X and of W.  The decode and prompt paths have TX = 2 (hi and
 // lo) and bf16 weights (TW = 1).  The training products have float32 operands
@@ -194,11 +206,12 @@ __global__ __launch_bounds__(256, OCC) void k_gemm(GemmArgs a) {
   };
   constexpr int NW = NTW * TW;  // weight loads per step
   u32x4 wr[RD][4][NW];
-  // acc: the sums; with three terms, the products below the first go to sums of
-  // their own (low), whose rounding is as much smaller, added at the end (256
-  // columns: relative error 2.4e-7 in one sum, 0.8e-7 in two; a float32 GEMM 1.5e-7)
-  constexpr bool LOW = TX == 3;
-  f32x16 acc[NTW][MT], low[LOW ? NTW : 1][LOW ? MT : 1];
+  // acc: the running sums; low: those of the products below the first, where
+  // they have their own (256 columns of three terms: relative error 2.4e-7 in one
+  // sum, 0.8e-7 in two; a float32 GEMM 1.5e-7); sum: what has been folded
+  constexpr bool LOW = TX == 3 || MT * NTW <= 2;
+  constexpr bool FOLD = EPI != EPI_SUM && TX == 2;
+  f32x16 acc[NTW][MT], low[LOW ? NTW : 1][LOW ? MT : 1], sum[FOLD ? NTW : 1][FOLD ? MT : 1];
 #pragma unroll
   for (int j = 0; j < NTW; ++j)
 #pragma unroll
@@ -207,6 +220,7 @@ __global__ __launch_bounds__(256, OCC) void k_gemm(GemmArgs a) {
       for (int e = 0; e < 16; ++e) {
         acc[j][m][e] = 0.f;
         if constexpr (LOW) low[j][m][e] = 0.f;
+        if constexpr (FOLD) sum[j][m][e] = 0.f;
       }
 #pragma unroll
   for (int q = 0; q < ND; ++q) load_x(xs0, q, kb0, 0);
@@ -263,10 +277,10 @@ __global__ __launch_bounds__(256, OCC) void k_gemm(GemmArgs a) {
           for (int m = 0; m < MT; ++m)
 #pragma unroll
             for (int j = 0; j < NTW; ++j) {
-              f32x16& sum = LOW && t + p > 0 ? low[LOW ? j : 0][LOW ? m : 0] : acc[j][m];
-              sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+              f32x16& to = LOW && t + p > 0 ? low[LOW ? j : 0][LOW ? m : 0] : acc[j][m];
+              to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                   __builtin_bit_cast(bf16x8, wr[rd][c][p * NTW + j]),
-                  __builtin_bit_cast(bf16x8, fx[c & 1][t][m]), sum, 0, 0, 0);
+                  __builtin_bit_cast(bf16x8, fx[c & 1][t][m]), to, 0, 0, 0);
             }
         }
       // one LDS read and at most one load between groups of MFMAs
@@ -291,29 +305,55 @@ __global__ __launch_bounds__(256, OCC) void k_gemm(GemmArgs a) {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
   };
+  int left = a.fold;  // blocks until the sums are folded
+  const auto fold = [&] {
+    if constexpr (FOLD) {
+      if (--left > 0) return;
+      left = a.fold;
+#pragma unroll
+      for (int j = 0; j < NTW; ++j)
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            if constexpr (LOW) {
+              acc[j][m][e] += low[j][m][e];
+              low[j][m][e] = 0.f;
+            }
+            sum[j][m][e] += acc[j][m][e];
+            acc[j][m][e] = 0.f;
+          }
+    }
+  };
   if constexpr (NB == 2) {
 #pragma unroll 1
     for (int kb = kb0; kb < kb1; ++kb) {
       half(xs0, xs1, 0, kb, 0);
       half(xs1, xs0, 1 % RD, kb, 1);
+      fold();
     }
   } else {
 #pragma unroll 1
     for (int kb = kb0; kb < kb1; kb += 2) {
       half(xs0, xs3, 0, kb, 0);
       half(xs1, xs0, 1, kb, 1);
+      fold();
       if (kb + 1 >= kb1) break;
       half(xs2, xs1, 2 % RD, kb + 1, 0);
       half(xs3, xs2, 3 % RD, kb + 1, 1);
+      fold();
     }
   }
-  if constexpr (LOW) {
+  if constexpr (LOW || FOLD) {
 #pragma unroll
     for (int j = 0; j < NTW; ++j)
 #pragma unroll
       for (int m = 0; m < MT; ++m)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[j][m][e] += low[j][m][e];
+        for (int e = 0; e < 16; ++e) {
+          if constexpr (LOW) acc[j][m][e] += low[j][m][e];
+          if constexpr (FOLD) acc[j][m][e] += sum[j][m][e];
+        }
   }
   // C layout of the 32x32 MFMA: lane holds row m = lane & 31, register e the
   // column 8 (e / 4) + 4 (lane / 32) + e % 4
@@ -506,22 +546,32 @@ void launch_cfg(const GemmArgs& a, int wgs, const GemmScratch& sc, hipStream_t s
 }
 
 // The variants.  eff: the share of a CU's matrix peak that one workgroup
-// reaches on it, fitted to back-to-back launches of 14 weight shapes at 15 row
-// counts (1 to 1568); larger tiles wait for less per MFMA.
+// reaches on it, fitted to back-to-back launches of nine weight shapes at 17 row
+// counts (1 to 2048); larger tiles wait for less per MFMA, but the folds of the
+// largest are not hidden by a second workgroup.
 struct Config {
   int MT, NTW;
   float eff;
   void (*launch)(const GemmArgs&, int, const GemmScratch&, hipStream_t);
 };
 constexpr Config CONFIGS[] = {
-    {1, 1, 0.24f, launch_cfg<1, 1, 4, 2, 4>}, {1, 2, 0.37f, launch_cfg<1, 2, 2, 2, 4>},
-    {2, 1, 0.46f, launch_cfg<2, 1, 2, 2, 4>}, {2, 2, 0.56f, launch_cfg<2, 2, 2, 2, 2>},
-    {2, 4, 0.69f, launch_cfg<2, 4, 1, 1, 2>}, {3, 2, 0.67f, launch_cfg<3, 2, 2, 1, 2>},
-    {4, 1, 0.53f, launch_cfg<4, 1, 2, 1, 2>}, {4, 2, 0.74f, launch_cfg<4, 2, 1, 1, 2>},
-    {4, 3, 0.81f, launch_cfg<4, 3, 1, 1, 2>}, {4, 4, 0.82f, launch_cfg<4, 4, 1, 1, 2>},
-    {5, 2, 0.67f, launch_cfg<5, 2, 1, 1, 2>}, {5, 3, 0.77f, launch_cfg<5, 3, 1, 1, 2>}};
+    {1, 1, 0.271f, launch_cfg<1, 1, 4, 2, 4>}, {1, 2, 0.37f, launch_cfg<1, 2, 2, 2, 4>},
+    {2, 1, 0.511f, launch_cfg<2, 1, 2, 2, 4>}, {2, 2, 0.566f, launch_cfg<2, 2, 2, 2, 2>},
+    {2, 4, 0.602f, launch_cfg<2, 4, 1, 1, 2>}, {3, 2, 0.639f, launch_cfg<3, 2, 1, 1, 2>},
+    {4, 1, 0.505f, launch_cfg<4, 1, 2, 1, 2>}, {4, 2, 0.652f, launch_cfg<4, 2, 1, 1, 2>}};
 constexpr int N_CONFIGS = sizeof(CONFIGS) / sizeof(CONFIGS[0]);
 constexpr int CUS = 256;
+
+// Blocks per accumulator: an eighth of K, four to eight for the widest weights
+// (1.4e-7 to 2.0e-7 against float64); from 320 rows on, where folds are the least
+// hidden, a quarter of K and up to seven (2.0e-7 to 2.9e-7).  The library products
+// that prompts of more than 128 rows once ran on kept hi and lo sums apart and cut
+// K in slices of 1,024 columns or more: 1.9e-7 (output, 320 rows) to 6.3e-7 (down,
+// K = 18,944, 624 rows).
+int sum_blocks(const Config& c, int M, int nkt) {
+  if (M > 320) return std::clamp(nkt / 4, 1, 7);
+  return std::clamp(nkt / 8, 1, c.MT * c.NTW <= 2 ? 8 : 4);
+}
 
 }  // namespace
 
@@ -550,14 +600,13 @@ void launch_pack(const uint16_t* src, int N, int K, uint16_t* dst, hipStream_t s
                      nkt, units, dst);
 }
 
-
 // Picks the tile and the number of K chunks with the least estimated time:
 // the larger of the busiest CU's time (whole workgroups, each its MFMA cycles
-// at 2.4 GHz over the variant's eff plus 1.9 us to fill and drain), the
-// matrix rate of the whole chip (about 1.9 PFLOP/s) and the weight stream,
-// plus the partials' writing and their reading by the consumer.  On the 210
-// (shape, rows) pairs it was fitted to, its choice costs 0.6% over the best
-// variant measured for the pair on average, 8% at worst.
+// at 2.4 GHz over the variant's eff plus 1.65 us to fill and drain), the
+// matrix rate of the whole chip (about 2 PFLOP/s) and the weight stream,
+// plus the partials' writing and their reading by the consumer.  On the 153
+// (shape, rows) pairs it was fitted to, its choice costs 0.9% over the best
+// variant measured for the pair on average, 10% at worst.
 GemmPlan plan_gemm(int M, int N, int K, int nw, size_t max_part) {
   GemmPlan best{};
   float best_us = 0.f;
@@ -567,12 +616,11 @@ GemmPlan plan_gemm(int M, int N, int K, int nw, size_t max_part) {
   for (int ci = 0; ci < N_CONFIGS; ++ci) {
     const Config& c = CONFIGS[ci];
     const int n_mt = (M + 32 * c.MT - 1) / (32 * c.MT);
+    const int fold = sum_blocks(c, M, nkt);
     // up to 64 rows the one row tile that just holds them, so that the weights
-    // pass through a CU once; up to 160 rows that one or tiles of 64 rows (108
-    // rows, 7B-shaped output projection 15 us in one tile, 12 in two)
+    // pass through a CU once
     const int fit = (M + 31) / 32;
-    if (M <= 160 ? c.MT != fit && (c.MT != 2 || M <= 64) : c.MT < 2) continue;
-    if (c.MT == 3 && M > 320) continue;  // measured up to 320 rows; above, 4x3 reads less LDS
+    if (M <= 64 ? c.MT != fit : c.MT < 2) continue;
     // 32-bit byte offsets within a row tile
     if (c.MT > 2 && (size_t)32 * c.MT * 4 * K >= ((size_t)1 << 31)) continue;
     const int n_nt = (n_tiles * TILE_ROWS + 128 * c.NTW - 1) / (128 * c.NTW);
@@ -581,14 +629,14 @@ GemmPlan plan_gemm(int M, int N, int K, int nw, size_t max_part) {
       if (S != s) continue;
       if (s > 1 && (bps < 3 || (size_t)s * M * ldp > max_part)) break;
       const int items = n_mt * n_nt * nw * s;
-      const float wg_us = bps * 8 * 2 * c.MT * c.NTW * 32 / (2400.f * c.eff) + 1.9f;
+      const float wg_us = bps * 8 * 2 * c.MT * c.NTW * 32 / (2400.f * c.eff) + 1.65f;
       const float cu_us = (items + CUS - 1) / CUS * wg_us;
-      const float chip_us = (float)items * (c.MT * 32) * (c.NTW * 128) * (bps * 128.f) * 4e-6f / 1877.f;
+      const float chip_us = (float)items * (c.MT * 32) * (c.NTW * 128) * (bps * 128.f) * 4e-6f / 2006.f;
       const float part_us = (float)s * M * ldp * (1.0e-6f + 0.8e-6f) + 0.13f * s;
       const float us = std::max({cu_us, chip_us, weight_us}) + part_us;
       if (best_us == 0.f || us < best_us) {
         best_us = us;
-        best = GemmPlan{ci, n_mt, n_nt, n_tiles, nkt, S, bps, items, ldp, n_tiles * TILE_ROWS};
+        best = GemmPlan{ci, n_mt, n_nt, n_tiles, nkt, S, bps, fold, items, ldp, n_tiles * TILE_ROWS};
       }
     }
   }
@@ -613,6 +661,7 @@ void launch_gemm(const GemmPlan& pl, const uint16_t* X, int ldx, int M, const ui
   a.nw = W2 ? 2 : 1;
   a.S = pl.S;
   a.bps = pl.bps;
+  a.fold = pl.fold;
   a.part = part;
   a.part_split = (size_t)M * pl.ldp;
   a.ldp = pl.ldp;
@@ -656,7 +705,8 @@ void launch_sum_terms(int MT, const GemmArgs& a, int items, bool part, hipStream
 }  // namespace
 
 // The training products: two tile heights, K split while the tiles leave CUs
-// idle and the partials fit.  The estimate is plan_gemm's (its eff values).
+// idle and the partials fit.  The estimate is plan_gemm's, with the eff of kernels
+// that do not fold.
 void launch_gemm_sum(const SumGemm& g, hipStream_t st) {
   const int nkt = (g.K + KB - 1) / KB;
   // a plane's byte offsets are 32-bit: wider matrices go in column ranges

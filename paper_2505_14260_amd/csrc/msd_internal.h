@@ -63,6 +63,7 @@ struct GemmPlan {
   int n_mt, n_nt;     // row tiles; column tiles per weight
   int n_tiles, nkt;   // 64-row tiles and 128-column blocks of a weight
   int S, bps;         // K chunks, blocks per chunk
+  int fold;           // blocks per sum
   int items;          // workgroups
   int ldp, off2;      // floats between partial rows; column offset of W2
 };
