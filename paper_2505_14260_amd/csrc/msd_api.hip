@@ -1129,8 +1129,7 @@ int train_wgrad(msd_ctx* c, const float* dY, int N, const float* A, int K, int R
 }
 
 // The packed terms of the master weights, after they changed.
-int train_pack(msd_ctx* c) {
-  TrainState* t = c->tr;
+int train_pack(msd_ctx* c, TrainState* t) {
   const msd_model_desc& m = c->m;
   const int d = m.d_model, F = m.ffn_dim, qd = m.n_heads * m.head_dim;
   const int nq = qd + 2 * m.n_kv_heads * m.head_dim;
@@ -1226,13 +1225,13 @@ size_t train_carve(TrainState* t, const msd_model_desc& m, const msd_limits& lim
   return std::max(cv.off, fv.off);
 }
 
-int train_init(msd_ctx* c) {
-  if (c->tr) return MSD_OK;
+// Fills t: buffers, rocBLAS handles, and the parameters as the decoder holds
+// them.  Nothing in c changes.
+int train_setup(msd_ctx* c, TrainState* t) {
   const msd_model_desc& m = c->m;
   const int d = m.d_model, F = m.ffn_dim, H = m.n_heads, KV = m.n_kv_heads, hd = m.head_dim;
-  const int V = m.vocab, R = c->lim.max_prompt - 1;
-  TrainState* t = new TrainState;
-  t->Rmax = R;
+  const int V = m.vocab;
+  t->Rmax = c->lim.max_prompt - 1;
   int sh[TRAIN_PARAMS][2];
   train_shapes(m, sh);
   for (int i = 0; i < TRAIN_PARAMS; ++i) t->off[i + 1] = t->off[i] + (size_t)sh[i][0] * sh[i][1];
@@ -1267,28 +1266,22 @@ int train_init(msd_ctx* c) {
   planes(t->gu_t, d, 2 * F);
   planes(t->dn_t, F, d);
   t->lm_t = u16(packed_elems(d, Vp));
-  train_carve(t, m, c->lim, static_cast<char*>(take(train_carve(t, m, c->lim, nullptr))));
+  const size_t lm_bytes = (size_t)V * d * sizeof(uint16_t);
+  void* const arena = take(std::max(train_carve(t, m, c->lim, nullptr), lm_bytes));
+  train_carve(t, m, c->lim, static_cast<char*>(arena));
   for (void* p : t->allocs)
-    if (!p) {
-      train_free(t);
-      return fail(c, MSD_ERR_HIP, "training buffers: hipMalloc failed");
-    }
+    if (!p) return fail(c, MSD_ERR_HIP, "training buffers: hipMalloc failed");
   if (rocblas_create_handle(&t->blas) != rocblas_status_success ||
-      rocblas_set_stream(t->blas, c->st) != rocblas_status_success) {
-    train_free(t);
+      rocblas_set_stream(t->blas, c->st) != rocblas_status_success)
     return fail(c, MSD_ERR_HIP, "rocblas handle");
-  }
   FeatureScratch& f = t->feature;
   if (f.blas_ws && (rocblas_create_handle(&f.blas) != rocblas_status_success ||
                     rocblas_set_stream(f.blas, c->st) != rocblas_status_success ||
                     rocblas_set_workspace(f.blas, f.blas_ws, FEATURE_BLAS_WS) !=
-                        rocblas_status_success)) {
-    train_free(t);
+                        rocblas_status_success))
     return fail(c, MSD_ERR_HIP, "rocblas handle of the target's pass");
-  }
-  c->tr = t;
   // the draft's parameters from the packed copies the decoder uses (and the
-  // norm gains); from here on the decoder reads the gains from wb
+  // norm gains)
   const PackedLayer& pl = c->pdlayer;
   const size_t pq = packed_elems(H * hd, d), pk = packed_elems(KV * hd, d);
   const uint16_t* packed[7] = {c->fc_p, pl.qkv, pl.qkv + pq, pl.qkv + pq + pk, pl.o, pl.g, pl.u};
@@ -1302,21 +1295,29 @@ int train_init(msd_ctx* c) {
   tr_widen(t->wb, np, t->w, c->st);
   tr_fill(t->m, np, 0.f, c->st);
   tr_fill(t->v, np, 0.f, c->st);
-  TRY(train_pack(c));
-  // the LM head's transpose, from its rows (a temporary copy)
-  uint16_t* lm16 = nullptr;
-  HIPC(c, hipMalloc((void**)&lm16, (size_t)V * d * sizeof(uint16_t)));
+  TRY(train_pack(c, t));
+  // the LM head's transpose, from its rows (in the activations' place)
+  uint16_t* const lm16 = static_cast<uint16_t*>(arena);
   launch_unpack(c->lm_p, V, d, lm16, c->st);
   tr_pack_t16(lm16, V, d, Vp, t->lm_t, c->st);
-  const hipError_t e1 = hipGetLastError();
-  const hipError_t e2 = hipStreamSynchronize(c->st);
-  (void)hipFree(lm16);
-  if (e1 != hipSuccess || e2 != hipSuccess)
-    return fail(c, MSD_ERR_HIP,
-                std::string("training set-up: ") + hipGetErrorString(e1 != hipSuccess ? e1 : e2));
+  LAUNCHED(c);
+  HIPC(c, hipStreamSynchronize(c->st));
+  return MSD_OK;
+}
+
+// The training state, from the first training call that can set it up.
+int train_init(msd_ctx* c) {
+  if (c->tr) return MSD_OK;
+  TrainState* t = new TrainState;
+  const int r = train_setup(c, t);
+  if (r != MSD_OK) {
+    train_free(t);
+    return r;
+  }
+  c->tr = t;
+  // from here on the decoder reads the draft's norm gains from wb
   c->dlayer.n1 = t->wb + t->off[8];
   c->dlayer.n2 = t->wb + t->off[9];
-  HIPC(c, hipStreamSynchronize(c->st));
   return MSD_OK;
 }
 
@@ -1994,7 +1995,7 @@ int msd_train_apply(msd_ctx* c, double lr) {
   launch_pack(t->wb + t->off[5], F, d, const_cast<uint16_t*>(pl.g), c->st);
   launch_pack(t->wb + t->off[6], F, d, const_cast<uint16_t*>(pl.u), c->st);
   launch_pack(t->wb + t->off[7], d, F, const_cast<uint16_t*>(pl.d), c->st);
-  TRY(train_pack(c));
+  TRY(train_pack(c, t));
   LAUNCHED(c);
   t->rows = 0;  // the next sequence's gradients replace g
   HIPC(c, hipStreamSynchronize(c->st));
