@@ -117,12 +117,12 @@ size_t layer_ldp(const msd_model_desc& m) {
                    2 * pad(m.ffn_dim)});
 }
 
-// Rows per GEMM launch for a pass over `rows` rows, with partials of at most
-// cap floats (part_cap(rows)).  Passes that msd_verify_noalloc may run keep
+// Rows per GEMM launch for a pass over `rows` rows.  Passes that msd_verify_noalloc may run keep
 // one launch's partials within the cap, but never take fewer than 64 rows a
 // launch.
-int row_chunk(const msd_model_desc& m, int rows, size_t cap) {
+int row_chunk(const msd_model_desc& m, int rows) {
   if (rows <= NOALLOC_MAX_ROWS) {
+    const size_t cap = part_cap(rows);
     if (rows <= 64 || rows * layer_ldp(m) <= cap) return rows;
     return std::max(64, (int)(cap / layer_ldp(m)) / 32 * 32);
   }
@@ -251,7 +251,6 @@ struct msd_ctx {
     int M, N, K, nw;
     size_t cap;
   };
-  size_t cap_now = 0;  // > 0: the cap of this call's partials instead of part_cap
   std::vector<std::pair<PlanKey, GemmPlan>> gemm_plans;
   float* ssq;
   Rows rows;
@@ -507,15 +506,12 @@ const GemmPlan& gemm_plan(msd_ctx* c, int M, int N, int K, int nw, size_t cap) {
   return c->gemm_plans.back().second;
 }
 
-// The cap of a launch's partials in this call.
-size_t call_cap(const msd_ctx* c, int rows) { return c->cap_now ? c->cap_now : part_cap(rows); }
-
 // Partial products of rows [0, M) of the split rows X (row stride
 // ldx = 2K) against the packed weight W [N][K] (and W2); returns the view the
 // consumer sums.
 int gemm(msd_ctx* c, int kind, const uint16_t* X, int ldx, int M, const uint16_t* W,
          const uint16_t* W2, int N, int K, Parts* out) {
-  const GemmPlan& pl = gemm_plan(c, M, N, K, W2 ? 2 : 1, call_cap(c, M));
+  const GemmPlan& pl = gemm_plan(c, M, N, K, W2 ? 2 : 1, part_cap(M));
   if ((size_t)pl.S * M * pl.ldp > c->plan.part_floats)
     return fail(c, MSD_ERR_INVALID_ARG, "internal: GEMM partials exceed their buffer");
   GemmScratch gs{};
@@ -697,7 +693,7 @@ int forward_layers(msd_ctx* c, bool draft, int n_seq, int nq, int tree_R, int ma
   const int rows = n_seq * nq;
   const int d = m.d_model, H = m.n_heads, KV = m.n_kv_heads, hd = m.head_dim, F = m.ffn_dim;
   const int nl = draft ? 1 : m.n_layers;
-  const int ch = !training ? row_chunk(m, rows, call_cap(c, rows))
+  const int ch = !training ? row_chunk(m, rows)
                  : rows > FEATURE_BLAS_MIN_ROWS ? FEATURE_BLAS_ROWS
                                                 : FEATURE_ROWS;
   const auto product = [&](int kind, const uint16_t* X, int mc, const uint16_t* W,
@@ -753,7 +749,7 @@ int forward_layers(msd_ctx* c, bool draft, int n_seq, int nq, int tree_R, int ma
         a.row0 = want->row0;
         a.out_row = want->out_row;
         r = want->n;
-        rch = row_chunk(m, r, call_cap(c, r));
+        rch = row_chunk(m, r);
         if (want->list) {
           x = reinterpret_cast<float*>(c->fcin);  // 4d bf16 a row: free until the draft's pass
           launch_gather_rows(c->x, want->list, r, d, x, c->st);
@@ -815,7 +811,7 @@ int forward_layers(msd_ctx* c, bool draft, int n_seq, int nq, int tree_R, int ma
 int draft_pass(msd_ctx* c, int n_seq, int nq, int tree_R, int max_ltot) {
   const int d = c->m.d_model;
   const int rows = n_seq * nq;
-  const int ch = row_chunk(c->m, rows, part_cap(rows));
+  const int ch = row_chunk(c->m, rows);
   Parts pt;
   for (int m0 = 0; m0 < rows; m0 += ch) {
     const int mc = std::min(ch, rows - m0);
@@ -837,7 +833,7 @@ int draft_pass(msd_ctx* c, int n_seq, int nq, int tree_R, int max_ltot) {
 // that row alone.
 int draft_prompt(msd_ctx* c, int n, int n_text, const uint16_t* visual) {
   const int d = c->m.d_model;
-  const int ch = row_chunk(c->m, n_text, part_cap(n_text));
+  const int ch = row_chunk(c->m, n_text);
   const bool mixed = n_text != n;
   float* f = mixed ? reinterpret_cast<float*>(c->xb) : c->x;  // xb: 2d bf16 a row
   Parts pt;
@@ -1795,27 +1791,24 @@ int verify_impl(msd_ctx* c, int n_seq, const int32_t* seqs_h, const msd_tree* tr
   LAUNCHED(c);
   TRY(norm_rows(c, rows, c->layers[0].n1));
   TRY(forward_layers(c, false, n_seq, T, T, max_l + T, c->final_norm, c->h, nullptr));
-  const int lm = c->cap_now ? std::min(LM_ROWS, rows) : rows;
-  for (int m0 = 0; m0 < rows; m0 += lm)
-    TRY(lm_argmax(c, c->h + (size_t)m0 * 2 * d, std::min(lm, rows - m0), argmax_d + m0,
-                  logits_d ? logits_d + (size_t)m0 * V : nullptr));
+  TRY(lm_argmax(c, c->h, rows, argmax_d, logits_d));
   c->verified_T = T;
   c->verified_seqs.assign(seqs_h, seqs_h + n_seq);
   return MSD_OK;
 }
 
 // Floats of GEMM partials a verify of `rows` tree rows writes (the largest
-// of its launches: q/k/v, output, gate+up and down) under the call's cap.
+// of its launches: q/k/v, output, gate+up and down).
 size_t verify_part_floats(msd_ctx* c, int rows) {
   const msd_model_desc& m = c->m;
   const int d = m.d_model, F = m.ffn_dim, hh = m.n_heads * m.head_dim;
   const int qkv = (m.n_heads + 2 * m.n_kv_heads) * m.head_dim;
   size_t need = 0;
   const auto add = [&](int M, int N, int K, int nw) {
-    const GemmPlan& p = gemm_plan(c, M, N, K, nw, call_cap(c, M));
+    const GemmPlan& p = gemm_plan(c, M, N, K, nw, part_cap(M));
     need = std::max(need, (size_t)p.S * M * p.ldp);
   };
-  const int ch = row_chunk(m, rows, call_cap(c, rows));
+  const int ch = row_chunk(m, rows);
   for (int M : {std::min(ch, rows), rows % ch}) {
     if (M <= 0) continue;
     add(M, qkv, d, 1);
@@ -1856,19 +1849,9 @@ int msd_verify_noalloc(msd_ctx* c, int n_seq, const int32_t* seqs_h, const msd_t
   const size_t att_ml = att_o / m.head_dim * 2 + 64;
   auto up = [](size_t f) { return (f + 63) / 64 * 64; };  // 256-byte steps
   const size_t have = MSD_NOALLOC_SCRATCH_BYTES / sizeof(float);
-  size_t rest = up(att_o) + up(att_ml) + up(topk_scratch_floats(rows, m.vocab));
-  size_t part = verify_part_floats(c, rows);
-  struct Cap {  // the call's cap on partials ends with the call
-    msd_ctx* c;
-    ~Cap() { c->cap_now = 0; }
-  } cap_guard{c};
-  if (up(part) + rest > have) {
-    // fewer rows a launch and fewer K chunks, as the scratch allows
-    rest = up(att_o) + up(att_ml) + up(topk_scratch_floats(std::min(LM_ROWS, rows), m.vocab));
-    c->cap_now = have > rest + 64 ? have - rest - 64 : 1;
-    part = verify_part_floats(c, rows);
-  }
-  const size_t need = up(part) + rest;
+  const size_t part = verify_part_floats(c, rows);
+  const size_t need =
+      up(part) + up(att_o) + up(att_ml) + up(topk_scratch_floats(rows, m.vocab));
   if (need > have)
     return fail(c, MSD_ERR_INVALID_ARG,
                 "this verify needs " + std::to_string(need * sizeof(float)) +
