@@ -689,7 +689,7 @@ __global__ __launch_bounds__(64 * CAUSAL_WAVES, 2) void k_causal_attn(AttnArgs a
 // loads, whole 128-byte lines, the next block while this one is used, so a
 // key is read from the L2 once per 128 queries instead of once per 32 (at
 // 3,136 rows and 32 heads the narrow kernel reads 2.5 GB, more than the L2s
-// hold of it; 370 us there, this kernel 180).  Two waves per SIMD; the matrix
+// hold of it; 319 us there, this kernel 166).  Two waves per SIMD; the matrix
 // work of a 32 x 32 block (two products, each with a hi and a lo half) is
 // 1,024 cycles, the chain scores - softmax - output about 1,750 a wave.
 // Blocks that every query of a wave sees skip the masks.  The
@@ -919,13 +919,27 @@ void launch_tree_attention(AttnArgs a, hipStream_t st, hipEvent_t ev0, hipEvent_
   else launch_tree_hd<64>(a, st, ev0, ev1);
 }
 
-// wanted: the queries whose output is wanted.  The wide kernel walks a query's
-// keys in one chain, the narrow one in four: they meet at about 640 rows (32
-// heads of 128: 28.4 us wide and 28.8 narrow at 624 rows, 180 and 370 at
-// 3,136), and where few queries are wanted the narrow one has more workgroups.
+// wanted: the queries whose output is wanted (0: the narrow kernel).  The wide
+// kernel walks a query's keys in one chain, the narrow one in four, on four times
+// the workgroups: wide pays once its own workgroups fill most of the chip.  640
+// rows and more, narrow / wide, us:
+//   head dim 128:  4 heads, 1,200 rows ( 40 workgroups)  24 /  41
+//                  8 heads, 2,200      (144)             63 /  73
+//                 16 heads, 1,200      (160)             42 /  42
+//                 32 heads,   640      (160)             29 /  27
+//                 32 heads, 3,136      (800)            319 / 166
+//   head dim 64:   8 heads, 2,200      (144)             35 /  49
+//                 20 heads, 1,600      (260)             38 /  39
+//                 32 heads,   900      (256)             25 /  23
+//                 32 heads, 3,136      (800)            174 / 102
 constexpr int WIDE_MIN_ROWS = 640;
+bool wide_pays(const AttnArgs& a, int wanted) {
+  const int wgs = a.n_seq * a.H * ((wanted + 127) / 128);
+  return wanted >= WIDE_MIN_ROWS && wgs >= (a.hd == 128 ? 160 : 240);
+}
+
 void launch_causal_attention(AttnArgs a, int wanted, hipStream_t st) {
-  if (wanted >= WIDE_MIN_ROWS) {
+  if (wide_pays(a, wanted)) {
     const dim3 grid(a.n_seq * a.H * ((a.nq + 127) / 128 - a.row0 / 128));
     if (a.hd == 128) hipLaunchKernelGGL(k_causal_wide<128>, grid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL(k_causal_wide<64>, grid, dim3(256), 0, st, a);

@@ -46,12 +46,17 @@ def rows_of(view, layer, n, transposed):
     # K smaller than a block, one 40-wide remainder
     (dataclasses.replace(WIDE.dims, d_model=168, n_heads=3, n_kv_heads=1, head_dim=64,
                          ffn_dim=296, vocab=512), [3, 32, 65, 161]),
-    # from 640 rows on the attention takes 128 queries a workgroup, 64 keys a block
+    # long prompts of few heads: 32 queries a workgroup, keys in four chains
     (dataclasses.replace(TINY.dims, n_layers=2, n_heads=2, n_kv_heads=1, head_dim=128, ffn_dim=296,
                          vocab=512), [639, 640, 641, 672, 703, 705, 767, 769]),
     (dataclasses.replace(TINY.dims, n_layers=2, n_heads=3, n_kv_heads=3, head_dim=64, ffn_dim=296,
                          vocab=512), [640, 673, 704, 769]),
-], ids=["wide", "tiny", "narrow", "long-128", "long-64"])
+    # of many: from 640 rows on 128 queries a workgroup, 64 keys a block
+    (dataclasses.replace(TINY.dims, n_layers=2, n_heads=32, n_kv_heads=4, head_dim=128,
+                         ffn_dim=296, vocab=512), [639, 640, 641, 672, 703, 705, 767, 769]),
+    (dataclasses.replace(TINY.dims, n_layers=2, n_heads=48, n_kv_heads=3, head_dim=64,
+                         ffn_dim=296, vocab=512), [640, 673, 704, 769]),
+], ids=["wide", "tiny", "narrow", "long-128", "long-64", "long-heads-128", "long-heads-64"])
 def test_prompt_rows_at_tile_edges(dims_of, counts):
     from paper_2505_14260_amd.msd import Engine
     wl = dataclasses.replace(TINY, dims=dims_of)
@@ -101,19 +106,20 @@ def test_prompt_of_several_launches():
 
 
 @pytest.mark.parametrize("mode", ["embedding", "feature"])
-@pytest.mark.parametrize("runs", [
-    [1, 4, 1],                   # text, visual, text, ...: one row on either side
-    [3, 70, 40, 33, 2],          # tiles with both kinds, text between the visual rows
-    [0, 64, 96, 31, 1],          # tiles of visual rows only; the last row alone
-    [33],                        # no visual row
-    [300, 161, 380],             # 680 rows wanted of 841: tiles of 128 with and without
-], ids=["1-4-1", "3-70-40-33-2", "0-64-96-31-1", "33", "300-161-380"])
-def test_prompt_of_text_and_visual_runs(runs, mode):
+@pytest.mark.parametrize("runs, heads", [
+    ([1, 4, 1], 4),              # text, visual, text, ...: one row on either side
+    ([3, 70, 40, 33, 2], 4),     # tiles with both kinds, text between the visual rows
+    ([0, 64, 96, 31, 1], 4),     # tiles of visual rows only; the last row alone
+    ([33], 4),                   # no visual row
+    ([300, 161, 380], 4),        # 680 rows wanted of 841
+    ([300, 161, 380], 48),       # with tiles of 128 queries, some without a wanted one
+], ids=["1-4-1", "3-70-40-33-2", "0-64-96-31-1", "33", "300-161-380", "300-161-380-48"])
+def test_prompt_of_text_and_visual_runs(runs, heads, mode):
     """A prompt's last layer runs over the rows whose features are read: the
     text rows in any order, or all with the Visual Feature input.  The draft's
     rows carry features of the whole target: 2e-2, as in the parity tests."""
     from paper_2505_14260_amd.msd import Engine, make_static_spec
-    dims = dataclasses.replace(TINY.dims, n_layers=2)
+    dims = dataclasses.replace(TINY.dims, n_layers=2, n_heads=heads, n_kv_heads=4)
     n = sum(runs)
     vis = np.concatenate([np.full(r, i & 1, dtype=np.uint8) for i, r in enumerate(runs)])
     rng = np.random.default_rng(n)
