@@ -90,11 +90,9 @@ def test_prefill_kv_and_first_token(setup):
 
 @pytest.mark.parametrize("n_visual", [136, 256, 480, 1036])
 def test_prefill_many_rows_wide(n_visual):
-    """200-, 320-, 544- and 1100-row prompts through the rocBLAS path (single
-    hi+lo products of 400, 640 and 1088 rows; 1100 rows = one 1024-row
-    launch of two products plus a 76-row one; an odd FFN tile count and a
-    partial last K block of the packed layout): every layer's K/V, the first
-    token and the draft cache against the oracle."""
+    """200-, 320-, 544- and 1100-row prompts, one launch per product (an odd FFN
+    tile count and a partial last K block of the packed layout): every layer's
+    K/V, the first token and the draft cache against the oracle."""
     import dataclasses
     from paper_2505_14260_amd.msd import Engine
     wl = dataclasses.replace(WIDE, n_visual=n_visual)
@@ -131,70 +129,77 @@ def test_prefill_many_rows_wide(n_visual):
         eng.close()
 
 
-def test_prefill_caller_row_major_weights():
-    """msd_use_caller_weights: a 1100-row prompt (one 1024-row rocBLAS pass
-    plus a 76-row one) whose output, gate, up and down products read the
-    uploaded row-major matrices: every layer's K/V, the first token and the
-    draft cache against the oracle, and the K/V bit for bit against the
-    default (unpacking) engine's, before and after switching back."""
+def cache_close(views, st, n_layers, n, what):
+    """Largest relative error of the target's K/V rows [0, n) of slot 0."""
+    tk, tv = views[:2]
+    worst = 0.0
+    for l in range(n_layers):
+        kg = bits_to_f64(tk[l, 0, :, :n, :].permute(1, 0, 2).reshape(n, -1))
+        vg = bits_to_f64(tv[l, 0, :, :, :n].permute(2, 0, 1).reshape(n, -1))
+        for got, ref in ((kg, st.kv.k), (vg, st.kv.v)):
+            ok, err = row_close(got, ref[l, :n].reshape(n, -1))
+            assert ok, (what, l, err)
+            worst = max(worst, err)
+    return worst
+
+
+@pytest.mark.parametrize("n_visual", [20, 40, 136, 1036])
+def test_target_pass_of_training(n_visual):
+    """The target's pass over a training sequence has products of its own: of
+    84, 104, 200 and 1100 rows (64-row launches and a remainder of 20 or 40;
+    one rocBLAS launch; one of 1024 rows and one of 76).  Every layer's K/V
+    against the oracle, as a prompt of the same rows leaves them."""
     import dataclasses
     from paper_2505_14260_amd.msd import Engine
-    wl = dataclasses.replace(WIDE, n_visual=1036)
+    wl = dataclasses.replace(WIDE, n_visual=n_visual)
     dims = wl.dims
-    print(f"case: prefill on caller weights {wl.name} n={wl.prompt_len}", flush=True)
+    n = wl.prompt_len
+    print(f"case: training pass {wl.name} n={n}", flush=True)
     w = synth.make_target_weights(dims, wl.seed)
     dr = synth.make_draft_weights(dims, w, wl.seed, wl.draft_fc_mode)
     prompt = synth.make_prompt(wl)
-    m = O.Models(dims, w, dr)
-    n = wl.prompt_len
     max_seq = (n + 64 + 255) // 256 * 256
-    st, f_ref, _, logits = O.prefill(m, *prompt, max_slots=max_seq)
-    O.draft_catch_up(m, st)
-    engines = [Engine(dims, w, dr, max_batch=1, max_seq=max_seq, max_tree=64, max_prompt=n)
-               for _ in range(2)]
+    st, _, _, _ = O.prefill(O.Models(dims, w, dr), *prompt, max_slots=max_seq)
+    eng = Engine(dims, w, dr, max_batch=1, max_seq=max_seq, max_tree=64, max_prompt=n)
     try:
-        engines[1].use_caller_weights(True)
-        firsts = [e.prefill(0, *prompt) for e in engines]
+        eng.train_accumulate(0, *prompt)
         torch.cuda.synchronize()
-        assert argmax_ok(firsts[1], logits[-1]), (firsts, f_ref)
-        assert firsts[1] == firsts[0]
-        views = [e.kv_views() for e in engines]
-        worst = 0.0
-        for l in range(dims.n_layers):
-            for which in ("K", "V"):
-                got = []
-                for tk, tv, _, _ in views:
-                    if which == "K":
-                        got.append(bits_to_f64(tk[l, 0, :, :n, :].permute(1, 0, 2).reshape(n, -1)))
-                    else:
-                        got.append(bits_to_f64(tv[l, 0, :, :, :n].permute(2, 0, 1).reshape(n, -1)))
-                ref = (st.kv.k if which == "K" else st.kv.v)[l, :n].reshape(n, -1)
-                ok, err = row_close(got[1], ref)
-                assert ok, (l, which, err)
-                assert np.array_equal(got[1], got[0]), (l, which, "differs from the unpacking path")
-                worst = max(worst, err)
-        dk = views[1][2]
-        kg = bits_to_f64(dk[0, 0, :, :n, :].permute(1, 0, 2).reshape(n, -1))
-        ok, err = row_close(kg, st.dkv.k[0, :n].reshape(n, -1))
-        assert ok, ("draft K", err)
-        print(f"caller weights: target K/V max rel err {worst:.2e}, draft K {err:.2e}")
-        # back to unpacking: the same prompt again gives the default engine's
-        # cache bit for bit
-        engines[1].use_caller_weights(False)
-        assert engines[1].prefill(0, *prompt) == firsts[0]
+        err = cache_close(eng.kv_views(), st, dims.n_layers, n, "training")
+        eng.prefill(0, *prompt)
         torch.cuda.synchronize()
-        tk0, tk1 = views[0][0], views[1][0]
-        assert torch.equal(tk0[:, 0, :, :n, :], tk1[:, 0, :, :n, :])
+        err2 = cache_close(eng.kv_views(), st, dims.n_layers, n, "prompt")
+        print(f"target K/V max rel err {err:.2e} in training, {err2:.2e} over the prompt")
     finally:
-        for e in engines:
-            e.close()
+        eng.close()
+
+
+def test_caller_weights_change_nothing():
+    """msd_use_caller_weights has no effect on results: a prompt's caches with
+    it, bit for bit."""
+    from paper_2505_14260_amd.msd import Engine
+    wl = TINY
+    w = synth.make_target_weights(wl.dims, wl.seed)
+    dr = synth.make_draft_weights(wl.dims, w, wl.seed, wl.draft_fc_mode)
+    prompt = synth.make_prompt(wl)
+    eng = Engine(wl.dims, w, dr, max_batch=1, max_seq=256, max_tree=64, max_prompt=wl.prompt_len)
+    try:
+        kept = []
+        for on in (False, True, False):
+            eng.use_caller_weights(on)
+            first = eng.prefill(0, *prompt)
+            torch.cuda.synchronize()
+            kept.append((first, [v.clone() for v in eng.kv_views()]))
+        for first, views in kept[1:]:
+            assert first == kept[0][0]
+            assert all(torch.equal(x, y) for x, y in zip(views, kept[0][1]))
+    finally:
+        eng.close()
 
 
 def test_wide_vocab_lm_head_full_k():
     """A 152,064-word vocabulary at d_model 1024: three sequences' 15-node
-    trees make a 45-row verify whose LM head takes the full-K GEMM (ten
-    tiles per workgroup, X restaged for each of two K chunks, one partial per
-    tile); its logits and argmax against the oracle on the GPU's trees."""
+    trees make a 45-row verify whose LM head reduces its columns in the GEMM
+    (1,188 candidates a row); its logits and argmax against the oracle on the GPU's trees."""
     import dataclasses
     from paper_2505_14260_amd.msd import Engine
     from parity import oracle_tree_of
@@ -236,20 +241,20 @@ def test_wide_vocab_lm_head_full_k():
 
 
 @pytest.mark.timeout(240)
-def test_prefill_k_sliced_products_max_width():
-    """A 224-row prompt at d_model 8192 (one layer, FFN 2048): its rocBLAS
-    products take one GEMM over the 448 hi and lo rows, split along K into
-    strided batches (the gate+up pair into eight slices, q|k|v and down into
-    two, the output into four), on the uploaded row-major weights.  Layer
-    0's K/V, the first token and the draft cache (whose text rows carry the
-    whole target layer) against the oracle, and bit for bit against an
-    engine that unpacks the weights instead."""
+def test_prefill_and_training_pass_at_max_width():
+    """A 224-row prompt at d_model 8192 (one layer, FFN 2048): layer 0's K/V,
+    the first token and the draft cache (whose text rows carry the whole
+    target layer) against the oracle; then a training sequence of the same
+    rows, whose products over the 448 hi and lo rows are cut along K into
+    strided batches (the gate+up pair into eight, q|k|v and down into two,
+    the output into four): the same K/V, and its loss against the oracle's."""
     import dataclasses
     from paper_2505_14260_amd.msd import Engine
+    from oracle import train as TR
     wl = dataclasses.replace(MAXW, n_visual=200)
     dims = wl.dims
     n = wl.prompt_len
-    print(f"case: {wl.name} prefill of {n} rows, K-sliced rocBLAS products", flush=True)
+    print(f"case: {wl.name} prefill and training pass of {n} rows", flush=True)
     w = synth.make_target_weights(dims, wl.seed)
     dr = synth.make_draft_weights(dims, w, wl.seed, wl.draft_fc_mode)
     prompt = synth.make_prompt(wl)
@@ -257,30 +262,28 @@ def test_prefill_k_sliced_products_max_width():
     max_seq = 512
     st, f_ref, _, logits = O.prefill(m, *prompt, max_slots=max_seq)
     O.draft_catch_up(m, st)
-    engines = [Engine(dims, w, dr, max_batch=1, max_seq=max_seq, max_tree=64, max_prompt=n)
-               for _ in range(2)]
+    eng = Engine(dims, w, dr, max_batch=1, max_seq=max_seq, max_tree=64, max_prompt=n)
     try:
-        engines[1].use_caller_weights(True)
-        firsts = [e.prefill(0, *prompt) for e in engines]
+        first = eng.prefill(0, *prompt)
         torch.cuda.synchronize()
-        assert argmax_ok(firsts[1], logits[-1]), (firsts, f_ref)
-        assert firsts[0] == firsts[1]
-        views = [e.kv_views() for e in engines]
-        tk, tv, dk, _ = views[1]
-        kg = bits_to_f64(tk[0, 0, :, :n, :].permute(1, 0, 2).reshape(n, -1))
-        vg = bits_to_f64(tv[0, 0, :, :, :n].permute(2, 0, 1).reshape(n, -1))
-        ok, ek = row_close(kg, st.kv.k[0, :n].reshape(n, -1))
-        ok2, ev = row_close(vg, st.kv.v[0, :n].reshape(n, -1))
-        assert ok and ok2, (ek, ev)
-        dkg = bits_to_f64(dk[0, 0, :, :n, :].permute(1, 0, 2).reshape(n, -1))
-        ok3, ed = row_close(dkg, st.dkv.k[0, :n].reshape(n, -1))
-        assert ok3, ed
-        for a_, b_ in zip(views[0], views[1]):
-            assert torch.equal(a_, b_)
-        print(f"K-sliced prefill: K/V rel err {ek:.2e} / {ev:.2e}, draft K {ed:.2e}")
+        assert argmax_ok(first, logits[-1]), (first, f_ref)
+        views = eng.kv_views()
+        e1 = cache_close(views, st, 1, n, "prompt")
+        dkg = bits_to_f64(views[2][0, 0, :, :n, :].permute(1, 0, 2).reshape(n, -1))
+        ok, ed = row_close(dkg, st.dkv.k[0, :n].reshape(n, -1))
+        assert ok, ed
+        h, e, pt = TR.sequence_inputs(m, *prompt)
+        views[0].zero_()
+        loss = eng.train_accumulate(0, *prompt)
+        torch.cuda.synchronize()
+        e2 = cache_close(views, st, 1, n, "training")
+        # the regression term reads every row's features: 1e-2, as the training tests
+        params = TR.draft_params(m.draft)
+        ref = TR.batch_grads(m, params, [(h, e, prompt[1], pt)])[0]
+        assert abs(loss[0] / (n - 1) - ref) <= 1e-2 * abs(ref)
+        print(f"K/V rel err {e1:.2e} (prompt), {e2:.2e} (training), draft K {ed:.2e}")
     finally:
-        for e in engines:
-            e.close()
+        eng.close()
 
 
 def test_max_width_model():
