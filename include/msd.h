@@ -199,13 +199,9 @@ enum { MSD_DRAFT_VISUAL_EMBEDDING = 0, MSD_DRAFT_VISUAL_FEATURE = 1 };
 int msd_set_draft_input(msd_ctx* ctx, int visual_input);
 
 /*
- * Tells the library that the row-major matrices given to msd_create (wo,
- * w_gate, w_up and w_down of every target layer) stay valid and unchanged
- * until msd_destroy or a call with enable = 0, so that products may read them
- * in place.  Every product of this library reads the packed copies, whose
- * layout its GEMM takes at every row count, so the call changes neither
- * results nor time.  Default: disabled.  Errors: MSD_ERR_INVALID_ARG for a
- * NULL ctx.
+ * Without effect on results, time or what the library reads: every product
+ * reads the packed copies, whose layout its GEMM takes at every row count.
+ * Kept for programs that call it.  Errors: MSD_ERR_INVALID_ARG for a NULL ctx.
  */
 int msd_use_caller_weights(msd_ctx* ctx, int enable);
 
@@ -352,14 +348,20 @@ int msd_set_state(msd_ctx* ctx, int seq, int L, const void* h_d, int32_t next_to
  * and two norm gains (float32 master copies); the embedding table and the
  * LM head stay frozen.  Arithmetic in float32; in the products over weights
  * every float32 operand enters the bf16 matrix units as three terms that hold
- * its 24 bits, with float32 sums.
+ * its 24 bits, with float32 sums (a product with an infinite operand is NaN).
+ * The target's pass keeps one order of summation for each row count, so that
+ * gradients do not move with the prompt's kernels.
  *
  * msd_train_accumulate adds one sequence's gradient sums and writes its
  * loss sums to loss_h[3] (total, regression part, token part, each summed
  * over its n - 1 rows).  It runs the target over the sequence in slot `seq`
  * (2 <= n <= max_prompt): the slot's cache is overwritten and the slot must
  * be prefilled again before decoding.  The first training call allocates
- * the training state (device memory of its own, freed by msd_destroy).
+ * the training state (device memory of its own, freed by msd_destroy): 30 bytes
+ * per trained parameter (masters, sums, moments, a bf16 copy, the packed terms of
+ * the weights and of their transposes), a bf16 copy of the LM head, and one
+ * sequence's activations; 8 GB at the LLaVA-1.5-7B shape with max_prompt 640.
+ * A set-up that fails (MSD_ERR_HIP) is done again by the next training call.
  * msd_train_apply performs one AdamW step (beta1 0.9, beta2 0.999, eps 1e-8,
  * no weight decay) with the mean gradient over the accumulated rows and
  * learning rate lr, refreshes the draft the decoder uses (its packed

@@ -279,7 +279,11 @@ __global__ __launch_bounds__(TB) void k_tr_fill(float* p, size_t n, float v) {
   if (k < n) p[k] = v;
 }
 
-// The three bf16 terms of eight floats, one 16-byte unit each.
+// The three bf16 terms of eight floats, one 16-byte unit each.  An infinite value
+// (or a finite one past the largest bf16) is infinite in its first term only, and
+// its product with an operand whose lower terms are zero is NaN where one float32
+// product would be infinite.  No finite loss reaches that: such a row's RMSNorm is
+// NaN, or its regression loss infinite, already.
 MSD_DEV void split8(const float (&x)[8], uint4 (&t)[3]) {
   uint32_t w[3][4];
 #pragma unroll
