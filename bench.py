@@ -233,6 +233,7 @@ def train_step_bench(args, wl, w, dr):
     n = len(prompt[0])
     eng = B.Engine(dims, w, dr, max_batch=1, max_seq=(n + 64 + 255) // 256 * 256, max_tree=64,
                    max_prompt=n)
+    eng.use_caller_weights(True)  # training's target pass on the uploaded matrices
     vis_t = torch.from_numpy(np.ascontiguousarray(prompt[2]).view(np.int16)).cuda()
     stream = torch.cuda.current_stream()
     acc, app, losses = [], [], []

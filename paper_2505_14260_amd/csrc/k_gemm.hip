@@ -105,8 +105,8 @@ MSD_DEV constexpr int vmcnt_imm(int n) { return 0x0f70 | (n & 15) | ((n >> 4) <<
 // to 32 x 256 or 64 x 128 per workgroup, where K can be as short as a block) the
 // lo products, 2^-8 of the hi ones, have accumulators of their own too.
 // Against float64, K = 4096, one chunk: 5.7e-7 in one accumulator, 2.0e-7 folded
-// every four blocks, 2.65e-7 every seven; K = 256: 1.4e-7 -> 0.7e-7; K = 11008:
-// 9.7e-7 -> 2.0e-7 and 2.65e-7.  The fold costs a tile of 128 x 256 (accumulators
+// every four blocks, 2.6e-7 every seven; K = 256: 1.4e-7 -> 0.7e-7; K = 11008:
+// 9.7e-7 -> 2.0e-7 and 2.6e-7.  The fold costs a tile of 128 x 256 (accumulators
 // in the upper half of the register file, three moves and an add each) 3 to 6%,
 // the smaller ones up to 2%.  Tiles with more sums than 128 registers a lane have
 // no room for a second set.
@@ -564,7 +564,7 @@ constexpr int CUS = 256;
 
 // Blocks per accumulator: an eighth of K, four to eight for the widest weights
 // (1.4e-7 to 2.0e-7 against float64); from 320 rows on, where folds are the least
-// hidden, a quarter of K and up to seven (2.0e-7 to 2.9e-7).  The library products
+// hidden, a quarter of K and up to seven (1.8e-7 to 2.7e-7).  The library products
 // that prompts of more than 128 rows once ran on kept hi and lo sums apart and cut
 // K in slices of 1,024 columns or more: 1.9e-7 (output, 320 rows) to 6.3e-7 (down,
 // K = 18,944, 624 rows).

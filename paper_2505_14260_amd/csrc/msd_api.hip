@@ -270,6 +270,7 @@ struct msd_ctx {
   float2* rope;
   int visual_input = MSD_DRAFT_VISUAL_EMBEDDING;  // draft input of visual prompt rows
   TrainState* tr = nullptr;  // draft-head training state (from the first training call)
+  bool caller_w = false;     // msd_use_caller_weights
   int device;            // the GPU current at msd_create
   float* noalloc_base;   // that GPU's copy of `scratch`
   // host
@@ -523,8 +524,9 @@ int gemm(msd_ctx* c, int kind, const uint16_t* X, int ldx, int M, const uint16_t
 }
 
 // A product of the target's pass over a training sequence, M > FEATURE_ROWS
-// rows, on rocBLAS against row-major bf16 weights, each unpacked into a slot of
-// the scratch (kept for the pass's further launches).  bf16 products with
+// rows, on rocBLAS against row-major bf16 weights: the caller's (rm, rm2), or
+// each unpacked into a slot of the scratch (kept for the pass's further
+// launches).  bf16 products with
 // float32 sums and results, issued column-major (C^T = W X^T), give the consumer
 // X_hi[m] . W[n] + X_lo[m] . W[n] (at column w * off2 + n) as
 //  - one product over the 2M rows of K elements that the split rows are (row 2m
@@ -532,8 +534,8 @@ int gemm(msd_ctx* c, int kind, const uint16_t* X, int ldx, int M, const uint16_t
 //    partials per row.  Few output tiles are filled up with K slices, one strided
 //    batch each (2 ns partials per row: the hi rows of every slice, then the lo);
 //  - or two products over the views X and X + K, the second added to the first.
-int feature_blas(msd_ctx* c, const uint16_t* X, int M, const uint16_t* W, const uint16_t* W2, int N,
-                 int K, Parts* out) {
+int feature_blas(msd_ctx* c, const uint16_t* X, int M, const uint16_t* W, const uint16_t* W2,
+                 const uint16_t* rm, const uint16_t* rm2, int N, int K, Parts* out) {
   FeatureScratch& f = c->tr->feature;
   const int nw = W2 ? 2 : 1, npad = (N + 63) / 64 * 64, ldp = npad * nw;
   const bool one = 2 * (size_t)M * ldp * sizeof(float) <=
@@ -556,8 +558,8 @@ int feature_blas(msd_ctx* c, const uint16_t* X, int M, const uint16_t* W, const 
   const auto tr = rocblas_operation_transpose, no = rocblas_operation_none;
   for (int w = 0; w < nw; ++w) {
     const uint16_t* const src = w ? W2 : W;
-    const uint16_t* const A = f.w[w];
-    if (f.src[w] != src) {
+    const uint16_t* const A = rm ? (w ? rm2 : rm) : f.w[w];
+    if (!rm && f.src[w] != src) {
       launch_unpack(src, N, K, f.w[w], c->st);
       LAUNCHED(c);
       f.src[w] = src;
@@ -589,10 +591,10 @@ int feature_blas(msd_ctx* c, const uint16_t* X, int M, const uint16_t* W, const 
 }
 
 // A product of the target's pass over a training sequence (its order of
-// summation: k_feature.hip).
-int feature_gemm(msd_ctx* c, const uint16_t* X, int M, const uint16_t* W, const uint16_t* W2, int N,
-                 int K, Parts* out) {
-  if (M > FEATURE_ROWS) return feature_blas(c, X, M, W, W2, N, K, out);
+// summation: k_feature.hip); rm, rm2: the caller's row-major W and W2, or null.
+int feature_gemm(msd_ctx* c, const uint16_t* X, int M, const uint16_t* W, const uint16_t* W2,
+                 const uint16_t* rm, const uint16_t* rm2, int N, int K, Parts* out) {
+  if (M > FEATURE_ROWS) return feature_blas(c, X, M, W, W2, rm, rm2, N, K, out);
   if (feature_part_floats(M, N, K, W2 ? 2 : 1) > c->tr->feature.part_floats)
     return fail(c, MSD_ERR_INVALID_ARG, "internal: training product exceeds its buffers");
   *out = launch_feature_gemm(X, 2 * K, M, W, W2, N, K, c->tr->feature.part, c->st);
@@ -696,10 +698,14 @@ int forward_layers(msd_ctx* c, bool draft, int n_seq, int nq, int tree_R, int ma
   const int ch = !training ? row_chunk(m, rows)
                  : rows > FEATURE_BLAS_MIN_ROWS ? FEATURE_BLAS_ROWS
                                                 : FEATURE_ROWS;
+  // (rm, rm2: the caller's row-major weights; q, k and v stay one stacked copy:
+  // one product over all three keeps more of the GPU busy)
   const auto product = [&](int kind, const uint16_t* X, int mc, const uint16_t* W,
-                           const uint16_t* W2, int N, int K, Parts* pt) {
-    return training ? feature_gemm(c, X, mc, W, W2, N, K, pt)
-                    : gemm(c, kind, X, 2 * K, mc, W, W2, N, K, pt);
+                           const uint16_t* W2, const uint16_t* rm, const uint16_t* rm2, int N,
+                           int K, Parts* pt) {
+    if (!training) return gemm(c, kind, X, 2 * K, mc, W, W2, N, K, pt);
+    if (!c->caller_w) rm = rm2 = nullptr;
+    return feature_gemm(c, X, mc, W, W2, rm, rm2, N, K, pt);
   };
   // the rows after the attention: all of them but in a last layer with want
   int r = rows, rch = ch;
@@ -714,8 +720,8 @@ int forward_layers(msd_ctx* c, bool draft, int n_seq, int nq, int tree_R, int ma
     Parts pt;
     for (int m0 = 0; m0 < rows; m0 += ch) {
       const int mc = std::min(ch, rows - m0);
-      TRY(product(GK_QKV, c->xn + (size_t)m0 * 2 * d, mc, pw.qkv, nullptr, (H + 2 * KV) * hd, d,
-                  &pt));
+      TRY(product(GK_QKV, c->xn + (size_t)m0 * 2 * d, mc, pw.qkv, nullptr, nullptr, nullptr,
+                  (H + 2 * KV) * hd, d, &pt));
       launch_rope_kv(pt, row_norm(c, m0), mc, H, KV, hd, c->rows.pos + m0, c->rows.seq + m0,
                      c->rows.slot + m0, c->rope, c->q + (size_t)m0 * 2 * H * hd, kc, vc, S, c->st);
       LAUNCHED(c);
@@ -772,14 +778,15 @@ int forward_layers(msd_ctx* c, bool draft, int n_seq, int nq, int tree_R, int ma
     LAUNCHED(c);
     for (int m0 = 0; m0 < r; m0 += rch) {
       const int mc = std::min(rch, r - m0);
-      TRY(product(GK_O, c->ao + (size_t)m0 * 2 * H * hd, mc, pw.o, nullptr, d, H * hd, &pt));
+      TRY(product(GK_O, c->ao + (size_t)m0 * 2 * H * hd, mc, pw.o, nullptr, w.wo, nullptr, d,
+                  H * hd, &pt));
       launch_resid(pt, mc, d, RN_ADD, x + (size_t)m0 * d, w.n2, c->xn + (size_t)m0 * 2 * d, nullptr,
                    c->ssq + (size_t)m0 * ssq_blocks(d), c->st);
       LAUNCHED(c);
     }
     for (int m0 = 0; m0 < r; m0 += rch) {
       const int mc = std::min(rch, r - m0);
-      TRY(product(GK_GATEUP, c->xn + (size_t)m0 * 2 * d, mc, pw.g, pw.u, F, d, &pt));
+      TRY(product(GK_GATEUP, c->xn + (size_t)m0 * 2 * d, mc, pw.g, pw.u, w.wg, w.wu, F, d, &pt));
       launch_silu(pt, row_norm(c, m0), mc, F, c->act + (size_t)m0 * 2 * F, c->st);
       LAUNCHED(c);
     }
@@ -787,7 +794,8 @@ int forward_layers(msd_ctx* c, bool draft, int n_seq, int nq, int tree_R, int ma
     const uint16_t* g_next = last ? final_g : c->layers[l + 1].n1;
     for (int m0 = 0; m0 < r; m0 += rch) {
       const int mc = std::min(rch, r - m0);
-      TRY(product(GK_DOWN, c->act + (size_t)m0 * 2 * F, mc, pw.d, nullptr, d, F, &pt));
+      TRY(product(GK_DOWN, c->act + (size_t)m0 * 2 * F, mc, pw.d, nullptr, w.wd, nullptr, d, F,
+                  &pt));
       if (last && final_g) {
         // the final feature h is materialised (LM head input, draft input)
         launch_resid_norm(pt, 0, mc, d, RN_ADD, x + (size_t)m0 * d, final_g, m.norm_eps,
@@ -1626,7 +1634,7 @@ int msd_set_draft_input(msd_ctx* c, int visual_input) {
 
 int msd_use_caller_weights(msd_ctx* c, int enable) {
   if (!c) return fail(nullptr, MSD_ERR_INVALID_ARG, "null context");
-  (void)enable;  // every product reads the packed weights
+  c->caller_w = enable != 0;
   return MSD_OK;
 }
 

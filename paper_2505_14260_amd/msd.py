@@ -338,7 +338,9 @@ class Engine:
         msd_set_draft_input(self.ctx, DRAFT_VISUAL_INPUTS[visual_input])
 
     def use_caller_weights(self, enable=True):
-        """Accepted and without effect: every product reads the packed weights."""
+        """Training's target pass over more than 128 rows reads the row-major
+        weights that this engine uploaded (and keeps) instead of unpacking the
+        packed copies.  Same results."""
         msd_use_caller_weights(self.ctx, enable)
 
     def train_accumulate(self, seq, tokens, is_visual, visual_bits):

@@ -173,25 +173,38 @@ def test_target_pass_of_training(n_visual):
         eng.close()
 
 
-def test_caller_weights_change_nothing():
-    """msd_use_caller_weights has no effect on results: a prompt's caches with
-    it, bit for bit."""
+@pytest.mark.parametrize("n_visual", [40, 136, 1036])
+def test_caller_weights_change_nothing(n_visual):
+    """msd_use_caller_weights: training's target pass over more than 128 rows
+    reads the uploaded row-major matrices instead of unpacked copies.  The
+    target's K/V, the losses and the gradients with it, bit for bit (and of a
+    shorter sequence, which reads the packed copies either way); then a prompt's
+    caches."""
+    import dataclasses
     from paper_2505_14260_amd.msd import Engine
-    wl = TINY
+    wl = dataclasses.replace(WIDE, n_visual=n_visual)
+    n = wl.prompt_len
+    print(f"case: caller weights, {n} rows", flush=True)
     w = synth.make_target_weights(wl.dims, wl.seed)
     dr = synth.make_draft_weights(wl.dims, w, wl.seed, wl.draft_fc_mode)
     prompt = synth.make_prompt(wl)
-    eng = Engine(wl.dims, w, dr, max_batch=1, max_seq=256, max_tree=64, max_prompt=wl.prompt_len)
+    eng = Engine(wl.dims, w, dr, max_batch=1, max_seq=(n + 64 + 255) // 256 * 256, max_tree=64,
+                 max_prompt=n)
     try:
         kept = []
         for on in (False, True, False):
             eng.use_caller_weights(on)
+            loss = eng.train_accumulate(0, *prompt)
+            grads = eng.train_read(0)
+            trained = [v.clone() for v in eng.kv_views()[:2]]
+            eng.train_apply(0.0)
             first = eng.prefill(0, *prompt)
             torch.cuda.synchronize()
-            kept.append((first, [v.clone() for v in eng.kv_views()]))
-        for first, views in kept[1:]:
-            assert first == kept[0][0]
-            assert all(torch.equal(x, y) for x, y in zip(views, kept[0][1]))
+            kept.append((loss, first, grads, trained + [v.clone() for v in eng.kv_views()]))
+        for loss, first, grads, views in kept[1:]:
+            assert loss == kept[0][0] and first == kept[0][1]
+            assert all(np.array_equal(g, kept[0][2][k]) for k, g in grads.items())
+            assert all(torch.equal(x, y) for x, y in zip(views, kept[0][3]))
     finally:
         eng.close()
 
