@@ -15,6 +15,11 @@
 // Bound: the weight stream; X (32 KB a block at 64 rows) goes through LDS once
 // per workgroup of two 64-row tiles, so L2 serves as many bytes of X as of W.
 // The next block's loads are in flight while this one is used.
+// Measured (weights from HBM; us), 7B-shaped q/k/v, output, gate+up, down:
+//    32 rows   24.2, 11.4, 41.7, 24.2   (2.9-4.3 TB/s of weights)
+//    64 rows   29.4, 16.4, 52.8, 30.1   (2.1-3.4 TB/s)
+// k_gemm takes 19.6, 9.1, 32.1, 17.7 at 27 rows and 24.4, 11.5, 38.8, 21.3 at 61; a
+// training step of 70 rows (two 7B-shaped layers) takes 5.4 ms as a whole.
 #include <algorithm>
 
 #include "msd_internal.h"
