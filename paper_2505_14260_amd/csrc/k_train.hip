@@ -35,6 +35,23 @@ MSD_DEV float bmax(float v, float* sh) {
   return fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]));
 }
 
+// The three bf16 terms x = h + m + l of a float (see split8).
+MSD_DEV void split3(float v, uint16_t (&t)[3]) {
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    t[q] = f2bf(v);
+    // an infinite or NaN value has no remainder
+    v = fabsf(bf2f(t[q])) < INFINITY ? v - bf2f(t[q]) : 0.f;
+  }
+}
+// Element k of a row of three terms, K elements each.
+MSD_DEV void put_terms(uint16_t* row, int K, int k, float v) {
+  uint16_t t[3];
+  split3(v, t);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) row[(size_t)q * K + k] = t[q];
+}
+
 // Row i < n: H[i] = target feature (split row hi + lo); for i < R also
 // X0[i] = [h_i | e_{i+1}] and E0[i] = the draft input of a visual row i:
 // e_i, or h_i with visual_feature (the Visual Feature variant), where e is
@@ -44,7 +61,7 @@ __global__ __launch_bounds__(TB) void k_tr_inputs(const uint16_t* h, const uint1
                                                   const int* tok, const int* vis_idx,
                                                   const uint16_t* visual, int n, int d,
                                                   int visual_feature, float* H, float* X0,
-                                                  float* E0) {
+                                                  float* E0, uint16_t* xs) {
   const int i = blockIdx.x;
   const int R = n - 1;
   const uint16_t* hr = h + (size_t)i * 2 * d;
@@ -55,9 +72,13 @@ __global__ __launch_bounds__(TB) void k_tr_inputs(const uint16_t* h, const uint1
     H[(size_t)i * d + k] = hv;
     if (i < R) {
       X0[(size_t)i * 2 * d + k] = hv;
+      put_terms(xs + (size_t)i * 6 * d, 2 * d, k, hv);
       E0[(size_t)i * d + k] = visual_feature ? hv : bf2f(er[k]);
     }
-    if (i > 0) X0[(size_t)(i - 1) * 2 * d + d + k] = bf2f(er[k]);
+    if (i > 0) {
+      X0[(size_t)(i - 1) * 2 * d + d + k] = bf2f(er[k]);
+      put_terms(xs + (size_t)(i - 1) * 6 * d, 2 * d, d + k, bf2f(er[k]));
+    }
   }
 }
 
@@ -77,9 +98,9 @@ __global__ __launch_bounds__(TB) void k_tr_zero_visual(float* dF, const int* vis
   for (int k = threadIdx.x; k < d; k += TB) dF[(size_t)i * d + k] = 0.f;
 }
 
-// Y = x / sqrt(mean(x^2) + eps) * g, rstd[i] saved.  Grid (R).
+// Y = x / sqrt(mean(x^2) + eps) * g and its terms, rstd[i] saved.  Grid (R).
 __global__ __launch_bounds__(TB) void k_tr_rmsnorm(const float* X, const float* g, float eps,
-                                                   int d, float* Y, float* rstd) {
+                                                   int d, float* Y, float* rstd, uint16_t* xs) {
   __shared__ float sh[4];
   const int i = blockIdx.x;
   const float* x = X + (size_t)i * d;
@@ -88,7 +109,11 @@ __global__ __launch_bounds__(TB) void k_tr_rmsnorm(const float* X, const float* 
   s = bsum(s, sh);
   const float r = rsqrtf(s / (float)d + eps);
   if (threadIdx.x == 0) rstd[i] = r;
-  for (int k = threadIdx.x; k < d; k += TB) Y[(size_t)i * d + k] = x[k] * r * g[k];
+  for (int k = threadIdx.x; k < d; k += TB) {
+    const float y = x[k] * r * g[k];
+    Y[(size_t)i * d + k] = y;
+    put_terms(xs + (size_t)i * 3 * d, d, k, y);
+  }
 }
 
 // dX = base + the gradient of the RMSNorm input given dY (per row), with
@@ -178,13 +203,16 @@ __global__ __launch_bounds__(TB) void k_tr_softmax_bwd(const float* P, float* dP
   for (int j = threadIdx.x; j < R; j += TB) dP[o + j] = scale * P[o + j] * (dP[o + j] - t);
 }
 
-// Mx = silu(G) * U, with G and U the halves of GU's rows; grid (F / TB, R).
-__global__ __launch_bounds__(TB) void k_tr_silu(const float* GU, int F, float* Mx) {
+// Mx = silu(G) * U and its terms, with G and U the halves of GU's rows; grid
+// (F / TB, R).
+__global__ __launch_bounds__(TB) void k_tr_silu(const float* GU, int F, float* Mx, uint16_t* xs) {
   const int f = blockIdx.x * TB + threadIdx.x;
   if (f >= F) return;
   const float* row = GU + (size_t)blockIdx.y * 2 * F;
   const float g = row[f];
-  Mx[(size_t)blockIdx.y * F + f] = g / (1.f + __expf(-g)) * row[F + f];
+  const float m = g / (1.f + __expf(-g)) * row[F + f];
+  Mx[(size_t)blockIdx.y * F + f] = m;
+  put_terms(xs + (size_t)blockIdx.y * 3 * F, F, f, m);
 }
 
 // dG = dM U silu'(G), dU = dM silu(G) (silu' = s (1 + g (1 - s)), s = sigmoid).
@@ -288,19 +316,11 @@ MSD_DEV void split8(const float (&x)[8], uint4 (&t)[3]) {
   uint32_t w[3][4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    uint16_t b[3][2];
+    uint16_t lo[3], hi[3];
+    split3(x[2 * e], lo);
+    split3(x[2 * e + 1], hi);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      float v = x[2 * e + i];
-#pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        b[q][i] = f2bf(v);
-        // an infinite or NaN value has no remainder
-        v = fabsf(bf2f(b[q][i])) < INFINITY ? v - bf2f(b[q][i]) : 0.f;
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < 3; ++q) w[q][e] = b[q][0] | ((uint32_t)b[q][1] << 16);
+    for (int q = 0; q < 3; ++q) w[q][e] = lo[q] | ((uint32_t)hi[q] << 16);
   }
 #pragma unroll
   for (int q = 0; q < 3; ++q) t[q] = make_uint4(w[q][0], w[q][1], w[q][2], w[q][3]);
@@ -313,9 +333,7 @@ MSD_DEV void load8(const float* p, float (&x)[8]) {
 }
 
 // Rows of three terms; one thread per unit of eight columns.
-__global__ __launch_bounds__(TB) void k_tr_split(const float* src, size_t units, int C,
-                                                 uint16_t* dst) {
-  const size_t q = (size_t)blockIdx.x * TB + threadIdx.x;
+MSD_DEV void split_rows(const float* src, size_t q, size_t units, int C, uint16_t* dst) {
   if (q >= units) return;
   const int upr = C / 8;
   const size_t row = q / upr;
@@ -328,13 +346,25 @@ __global__ __launch_bounds__(TB) void k_tr_split(const float* src, size_t units,
 #pragma unroll
   for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4*>(d + (size_t)p * C) = t[p];
 }
+__global__ __launch_bounds__(TB) void k_tr_split(const float* src, size_t units, int C,
+                                                 uint16_t* dst) {
+  split_rows(src, (size_t)blockIdx.x * TB + threadIdx.x, units, C, dst);
+}
 
 // Packed planes of [R][C]; one thread per unit of the packed layout (see
 // k_gemm.hip), as k_pack.
 constexpr int PKB = 128, PTR = 64;
-__global__ __launch_bounds__(TB) void k_tr_pack(const float* src, int R, int C, int nkt,
-                                                size_t units, uint16_t* dst, size_t plane) {
-  const size_t q = (size_t)blockIdx.x * TB + threadIdx.x;
+// The matrices that an update packs again: terms of the masters (planes of
+// `plane` elements), or the bf16 copies as they are (src16).  A workgroup finds
+// its matrix by its first block: one launch for all of them, which at d_model 256
+// are a launch's latency each.
+__global__ __launch_bounds__(TB) void k_tr_pack(PackJobs jobs) {
+  int j = 0;
+  while (j + 1 < jobs.n && (int)blockIdx.x >= jobs.job[j + 1].first) ++j;
+  const PackJob& a = jobs.job[j];
+  const int nkt = (a.C + PKB - 1) / PKB;
+  const size_t units = (size_t)((a.R + PTR - 1) / PTR) * nkt * (PTR * PKB / 8);
+  const size_t q = (size_t)((int)blockIdx.x - a.first) * TB + threadIdx.x;
   if (q >= units) return;
   const int lane = (int)(q & 63);
   const size_t r = q >> 6;
@@ -343,12 +373,20 @@ __global__ __launch_bounds__(TB) void k_tr_pack(const float* src, int R, int C, 
   const int kb = (int)(blk % nkt), t = (int)(blk / nkt);
   const int row = t * PTR + g16 * 16 + (lane & 15);
   const int col = kb * PKB + 32 * (lane >> 4) + 8 * c;
+  const bool in = row < a.R && col < a.C;
+  const size_t o = (size_t)row * a.C + col;
+  if (a.src16) {
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (in) v = *reinterpret_cast<const uint4*>(a.src16 + o);
+    *reinterpret_cast<uint4*>(a.dst + q * 8) = v;
+    return;
+  }
   float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  if (row < R && col < C) load8(src + (size_t)row * C + col, x);
-  uint4 o[3];
-  split8(x, o);
+  if (in) load8(a.src + o, x);
+  uint4 u[3];
+  split8(x, u);
 #pragma unroll
-  for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4*>(dst + p * plane + q * 8) = o[p];
+  for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4*>(a.dst + p * a.plane + q * 8) = u[p];
 }
 
 // A 128-row x 64-column block of src in LDS (zero past R and C), then a unit
@@ -377,11 +415,9 @@ MSD_DEV void load_tile(float* sh, const T* src, int R, int C, int r0, int c0) {
   __syncthreads();
 }
 
-// The transpose as rows of three terms [C][3 Rp]; grid (Rp / 128, C / 64).
-__global__ __launch_bounds__(TB) void k_tr_split_t(const float* src, int R, int C, int Rp,
-                                                   uint16_t* dst) {
-  __shared__ float sh[128 * TLD];
-  const int r0 = blockIdx.x * 128, c0 = blockIdx.y * 64;
+// The transpose as rows of three terms [C][3 Rp], rows r0.. and columns c0.. of src.
+MSD_DEV void split_tile_t(float* sh, const float* src, int R, int C, int Rp, int r0, int c0,
+                          uint16_t* dst) {
   load_tile(sh, src, R, C, r0, c0);
   for (int q = threadIdx.x; q < 64 * 16; q += TB) {
     const int c = q >> 4, u = q & 15;  // 16 threads write one row's 256 bytes
@@ -397,13 +433,10 @@ __global__ __launch_bounds__(TB) void k_tr_split_t(const float* src, int R, int 
   }
 }
 
-// Packed planes of the transpose: one block of 64 columns x 128 rows of src per
-// workgroup; grid (nkt, n_tiles).
+// Packed planes of the transpose: block (t, kb), 64 columns x 128 rows of src.
 template <typename T>
-__global__ __launch_bounds__(TB) void k_tr_pack_t(const T* src, int R, int C, int nkt,
-                                                  uint16_t* dst, size_t plane) {
-  __shared__ float sh[128 * TLD];
-  const int kb = blockIdx.x, t = blockIdx.y;
+MSD_DEV void pack_tile_t(float* sh, const T* src, int R, int C, int nkt, int kb, int t,
+                         uint16_t* dst, size_t plane) {
   load_tile(sh, src, R, C, kb * PKB, t * PTR);
   uint16_t* const o = dst + ((size_t)t * nkt + kb) * PKB * PTR;
   for (int q = threadIdx.x; q < 1024; q += TB) {
@@ -420,15 +453,55 @@ __global__ __launch_bounds__(TB) void k_tr_pack_t(const T* src, int R, int C, in
   }
 }
 
+__global__ __launch_bounds__(TB) void k_tr_pack_t16(const uint16_t* src, int R, int C, int nkt,
+                                                    uint16_t* dst) {
+  __shared__ float sh[128 * TLD];
+  pack_tile_t(sh, src, R, C, nkt, blockIdx.x, blockIdx.y, dst, (size_t)0);
+}
+
+// k_tr_pack of the masters' transposes.
+__global__ __launch_bounds__(TB) void k_tr_pack_t(PackJobs jobs) {
+  __shared__ float sh[128 * TLD];
+  int j = 0;
+  while (j + 1 < jobs.n && (int)blockIdx.x >= jobs.job[j + 1].first) ++j;
+  const PackJob& a = jobs.job[j];
+  const int nkt = (a.R + PKB - 1) / PKB, b = (int)blockIdx.x - a.first;
+  pack_tile_t(sh, a.src, a.R, a.C, nkt, b % nkt, b / nkt, a.dst, a.plane);
+}
+
+// The operands of one product's gradients: the terms of dY [R][N] transposed
+// (dyt, rows [N][3 Rp]) and of A [R][K] transposed and packed (at) for the weight's,
+// and of dY as it is (dy, when given) for the input's.  One launch: the first bt
+// workgroups take dyt, the next ba at, the others dy (a 64-row step of d_model 256:
+// nine launches fewer).
+__global__ __launch_bounds__(TB) void k_tr_operands(const float* dY, const float* A, int R, int N,
+                                                    int K, int Rp, int bt, int ba, uint16_t* dyt,
+                                                    uint16_t* at, size_t plane, uint16_t* dy) {
+  __shared__ float sh[128 * TLD];
+  const int nkt = (Rp + PKB - 1) / PKB;
+  int b = blockIdx.x;
+  if (b < bt) {
+    split_tile_t(sh, dY, R, N, Rp, b % nkt * 128, b / nkt * 64, dyt);
+    return;
+  }
+  b -= bt;
+  if (b < ba) {
+    pack_tile_t(sh, A, R, K, nkt, b % nkt, b / nkt, at, plane);
+    return;
+  }
+  b -= ba;
+  split_rows(dY, (size_t)b * TB + threadIdx.x, (size_t)R * (N / 8), N, dy);
+}
+
 unsigned blocks(size_t n) { return (unsigned)((n + TB - 1) / TB); }
 
 }  // namespace
 
 void tr_inputs(const uint16_t* h, const uint16_t* E, const int* tok, const int* vis_idx,
                const uint16_t* visual, int n, int d, int visual_feature, float* H, float* X0,
-               float* E0, hipStream_t st) {
+               float* E0, uint16_t* xs, hipStream_t st) {
   hipLaunchKernelGGL(k_tr_inputs, dim3(n), dim3(TB), 0, st, h, E, tok, vis_idx, visual, n, d,
-                     visual_feature, H, X0, E0);
+                     visual_feature, H, X0, E0, xs);
 }
 void tr_visual_rows(float* F, const float* E0, const int* vis_idx, int R, int d, hipStream_t st) {
   hipLaunchKernelGGL(k_tr_visual_rows, dim3(R), dim3(TB), 0, st, F, E0, vis_idx, d);
@@ -437,8 +510,8 @@ void tr_zero_visual(float* dF, const int* vis_idx, int R, int d, hipStream_t st)
   hipLaunchKernelGGL(k_tr_zero_visual, dim3(R), dim3(TB), 0, st, dF, vis_idx, d);
 }
 void tr_rmsnorm(const float* X, const float* g, float eps, int R, int d, float* Y, float* rstd,
-                hipStream_t st) {
-  hipLaunchKernelGGL(k_tr_rmsnorm, dim3(R), dim3(TB), 0, st, X, g, eps, d, Y, rstd);
+                uint16_t* xs, hipStream_t st) {
+  hipLaunchKernelGGL(k_tr_rmsnorm, dim3(R), dim3(TB), 0, st, X, g, eps, d, Y, rstd, xs);
 }
 size_t tr_gain_scratch(int d) { return (size_t)GAIN_PARTS * d; }
 void tr_rmsnorm_bwd(const float* X, const float* g, const float* rstd, const float* dY,
@@ -459,8 +532,8 @@ void tr_softmax(float* S, int R, int heads, float scale, hipStream_t st) {
 void tr_softmax_bwd(const float* P, float* dP, int R, int heads, float scale, hipStream_t st) {
   hipLaunchKernelGGL(k_tr_softmax_bwd, dim3(R, heads), dim3(TB), 0, st, P, dP, R, scale);
 }
-void tr_silu(const float* GU, int R, int F, float* Mx, hipStream_t st) {
-  hipLaunchKernelGGL(k_tr_silu, dim3(blocks(F), R), dim3(TB), 0, st, GU, F, Mx);
+void tr_silu(const float* GU, int R, int F, float* Mx, uint16_t* xs, hipStream_t st) {
+  hipLaunchKernelGGL(k_tr_silu, dim3(blocks(F), R), dim3(TB), 0, st, GU, F, Mx, xs);
 }
 void tr_silu_bwd(const float* GU, const float* dM, int R, int F, float* dGU, hipStream_t st) {
   hipLaunchKernelGGL(k_tr_silu_bwd, dim3(blocks(F), R), dim3(TB), 0, st, GU, dM, F, dGU);
@@ -487,25 +560,30 @@ void tr_split(const float* src, int R, int C, uint16_t* dst, hipStream_t st) {
   const size_t units = (size_t)R * (C / 8);
   hipLaunchKernelGGL(k_tr_split, dim3(blocks(units)), dim3(TB), 0, st, src, units, C, dst);
 }
-void tr_split_t(const float* src, int R, int C, int Rp, uint16_t* dst, hipStream_t st) {
-  hipLaunchKernelGGL(k_tr_split_t, dim3((Rp + 127) / 128, (C + 63) / 64), dim3(TB), 0, st, src, R,
-                     C, Rp, dst);
-}
-void tr_pack(const float* src, int R, int C, uint16_t* dst, size_t plane, hipStream_t st) {
-  const size_t units = packed_elems(R, C) / 8;
-  hipLaunchKernelGGL(k_tr_pack, dim3(blocks(units)), dim3(TB), 0, st, src, R, C,
-                     (C + PKB - 1) / PKB, units, dst, plane);
-}
-void tr_pack_t(const float* src, int R, int C, int Rp, uint16_t* dst, size_t plane,
-               hipStream_t st) {
+void tr_operands(const float* dY, const float* A, int R, int N, int K, int Rp, uint16_t* dyt,
+                 uint16_t* at, size_t plane, uint16_t* dy, hipStream_t st) {
   const int nkt = (Rp + PKB - 1) / PKB;
-  hipLaunchKernelGGL((k_tr_pack_t<float>), dim3(nkt, (C + PTR - 1) / PTR), dim3(TB), 0, st, src, R,
-                     C, nkt, dst, plane);
+  const int bt = nkt * ((N + 63) / 64), ba = nkt * ((K + PTR - 1) / PTR);
+  const unsigned bd = dy ? blocks((size_t)R * (N / 8)) : 0;
+  hipLaunchKernelGGL(k_tr_operands, dim3(bt + ba + bd), dim3(TB), 0, st, dY, A, R, N, K, Rp, bt, ba,
+                     dyt, at, plane, dy);
+}
+void PackJobs::add(const float* src, const uint16_t* src16, int R, int C, uint16_t* dst,
+                   size_t plane, bool transposed) {
+  job[n++] = PackJob{src, src16, R, C, dst, plane, wgs};
+  wgs += transposed ? ((R + PKB - 1) / PKB) * ((C + PTR - 1) / PTR)
+                    : (int)blocks(packed_elems(R, C) / 8);
+}
+void tr_pack(const PackJobs& j, hipStream_t st) {
+  hipLaunchKernelGGL(k_tr_pack, dim3(j.wgs), dim3(TB), 0, st, j);
+}
+void tr_pack_t(const PackJobs& j, hipStream_t st) {
+  hipLaunchKernelGGL(k_tr_pack_t, dim3(j.wgs), dim3(TB), 0, st, j);
 }
 void tr_pack_t16(const uint16_t* src, int R, int C, int Rp, uint16_t* dst, hipStream_t st) {
   const int nkt = (Rp + PKB - 1) / PKB;
-  hipLaunchKernelGGL((k_tr_pack_t<uint16_t>), dim3(nkt, (C + PTR - 1) / PTR), dim3(TB), 0, st, src,
-                     R, C, nkt, dst, (size_t)0);
+  hipLaunchKernelGGL(k_tr_pack_t16, dim3(nkt, (C + PTR - 1) / PTR), dim3(TB), 0, st, src, R, C, nkt,
+                     dst);
 }
 
 }  // namespace msd

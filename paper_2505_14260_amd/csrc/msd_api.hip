@@ -1114,40 +1114,61 @@ int train_gemm(msd_ctx* c, const uint16_t* X, int M, int K, int TX, const uint16
   return MSD_OK;
 }
 
-// C[R][N] = add + A[R][K] W^T: A's terms are made here.
+// C[R][N] = add + A[R][K] W^T; A's terms are made here, or lie in xs (A null).
 int train_linear(msd_ctx* c, const float* A, int R, int K, const TrainState::Planes& W, int N,
                  float* C, const float* add) {
-  tr_split(A, R, K, c->tr->xs, c->st);
+  if (A) tr_split(A, R, K, c->tr->xs, c->st);
   return train_gemm(c, c->tr->xs, R, K, 3, W.p, N, 3, W.plane, C, N, add);
 }
 
-// Weight gradient G[N][K] = (G when add) + sum over rows of dY[r][n] A[r][k].
-int train_wgrad(msd_ctx* c, const float* dY, int N, const float* A, int K, int R, float* G,
-                bool add) {
+// Gradients of Y = A W^T (rows R): the weight's G[N][K] = (G when add) + sum over
+// rows of dY[r][n] A[r][k], and with dA the input's dA[R][K] = dY W (Wt: W's
+// transpose).
+int train_back(msd_ctx* c, const float* dY, int N, const float* A, int K, int R, float* G, bool add,
+               const TrainState::Planes& Wt, float* dA) {
   TrainState* t = c->tr;
   const int Rp = (R + 63) / 64 * 64;
   const size_t plane = packed_elems(K, Rp);
-  tr_split_t(dY, R, N, Rp, t->xt, c->st);
-  tr_pack_t(A, R, K, Rp, t->wt, plane, c->st);
-  return train_gemm(c, t->xt, N, Rp, 3, t->wt, K, 3, plane, G, K, add ? G : nullptr);
+  tr_operands(dY, A, R, N, K, Rp, t->xt, t->wt, plane, dA ? t->xs : nullptr, c->st);
+  TRY(train_gemm(c, t->xt, N, Rp, 3, t->wt, K, 3, plane, G, K, add ? G : nullptr));
+  return dA ? train_gemm(c, t->xs, R, N, 3, Wt.p, K, 3, Wt.plane, dA, K, nullptr) : MSD_OK;
 }
 
-// The packed terms of the master weights, after they changed.
-int train_pack(msd_ctx* c, TrainState* t) {
+// The packed terms of the master weights and, after an update (decoder), the
+// draft weights that the decoder reads.
+int train_pack(msd_ctx* c, TrainState* t, bool decoder) {
   const msd_model_desc& m = c->m;
   const int d = m.d_model, F = m.ffn_dim, qd = m.n_heads * m.head_dim;
-  const int nq = qd + 2 * m.n_kv_heads * m.head_dim;
+  const int kd = m.n_kv_heads * m.head_dim, nq = qd + 2 * kd;
   const float* w = t->w;
   const size_t* o = t->off;
-  tr_pack(w + o[0], d, 2 * d, t->fc.p, t->fc.plane, c->st);
-  tr_pack(w + o[1], nq, d, t->qkv.p, t->qkv.plane, c->st);
-  tr_pack(w + o[4], d, qd, t->o.p, t->o.plane, c->st);
-  tr_pack(w + o[5], 2 * F, d, t->gu.p, t->gu.plane, c->st);
-  tr_pack(w + o[7], d, F, t->dn.p, t->dn.plane, c->st);
-  tr_pack_t(w + o[1], nq, d, nq, t->qkv_t.p, t->qkv_t.plane, c->st);
-  tr_pack_t(w + o[4], d, qd, d, t->o_t.p, t->o_t.plane, c->st);
-  tr_pack_t(w + o[5], 2 * F, d, 2 * F, t->gu_t.p, t->gu_t.plane, c->st);
-  tr_pack_t(w + o[7], d, F, d, t->dn_t.p, t->dn_t.plane, c->st);
+  PackJobs rows, cols;
+  rows.add(w + o[0], nullptr, d, 2 * d, t->fc.p, t->fc.plane);
+  rows.add(w + o[1], nullptr, nq, d, t->qkv.p, t->qkv.plane);
+  rows.add(w + o[4], nullptr, d, qd, t->o.p, t->o.plane);
+  rows.add(w + o[5], nullptr, 2 * F, d, t->gu.p, t->gu.plane);
+  rows.add(w + o[7], nullptr, d, F, t->dn.p, t->dn.plane);
+  if (decoder) {
+    const PackedLayer& pl = c->pdlayer;
+    const size_t pq = packed_elems(qd, d), pk = packed_elems(kd, d);
+    const auto add = [&](int i, int R, int C, const uint16_t* dst) {
+      rows.add(nullptr, t->wb + o[i], R, C, const_cast<uint16_t*>(dst), 0);
+    };
+    add(0, d, 2 * d, c->fc_p);
+    add(1, qd, d, pl.qkv);
+    add(2, kd, d, pl.qkv + pq);
+    add(3, kd, d, pl.qkv + pq + pk);
+    add(4, d, qd, pl.o);
+    add(5, F, d, pl.g);
+    add(6, F, d, pl.u);
+    add(7, d, F, pl.d);
+  }
+  cols.add(w + o[1], nullptr, nq, d, t->qkv_t.p, t->qkv_t.plane, true);
+  cols.add(w + o[4], nullptr, d, qd, t->o_t.p, t->o_t.plane, true);
+  cols.add(w + o[5], nullptr, 2 * F, d, t->gu_t.p, t->gu_t.plane, true);
+  cols.add(w + o[7], nullptr, d, F, t->dn_t.p, t->dn_t.plane, true);
+  tr_pack(rows, c->st);
+  tr_pack_t(cols, c->st);
   LAUNCHED(c);
   return MSD_OK;
 }
@@ -1299,7 +1320,7 @@ int train_setup(msd_ctx* c, TrainState* t) {
   tr_widen(t->wb, np, t->w, c->st);
   tr_fill(t->m, np, 0.f, c->st);
   tr_fill(t->v, np, 0.f, c->st);
-  TRY(train_pack(c, t));
+  TRY(train_pack(c, t, false));
   // the LM head's transpose, from its rows (in the activations' place)
   uint16_t* const lm16 = static_cast<uint16_t*>(arena);
   launch_unpack(c->lm_p, V, d, lm16, c->st);
@@ -1341,13 +1362,13 @@ int train_pass(msd_ctx* c, int n, const void* visual_d, double* loss3) {
   const bool add = t->rows > 0;  // gradients of earlier sequences are in g
   // ---- forward
   tr_inputs(c->h, c->embed, c->rows.tok, c->rows.vis, (const uint16_t*)visual_d, n, d,
-            c->visual_input == MSD_DRAFT_VISUAL_FEATURE, t->H, t->X0, t->E0, st);
+            c->visual_input == MSD_DRAFT_VISUAL_FEATURE, t->H, t->X0, t->E0, t->xs, st);
   LAUNCHED(c);
-  TRY(train_linear(c, t->X0, R, 2 * d, t->fc, d, t->F, nullptr));
+  TRY(train_linear(c, nullptr, R, 2 * d, t->fc, d, t->F, nullptr));
   tr_visual_rows(t->F, t->E0, c->rows.vis, R, d, st);
-  tr_rmsnorm(t->F, n1, eps, R, d, t->A1, t->r1, st);
+  tr_rmsnorm(t->F, n1, eps, R, d, t->A1, t->r1, t->xs, st);
   LAUNCHED(c);
-  TRY(train_linear(c, t->A1, R, d, t->qkv, nq, t->QKV, nullptr));
+  TRY(train_linear(c, nullptr, R, d, t->qkv, nq, t->QKV, nullptr));
   tr_rope(t->QKV, R, nq, H + KV, hd, c->rope, 1, st);
   LAUNCHED(c);
   // head kv Gq + j reads kv head kv: one batch over the kv heads for each j
@@ -1362,12 +1383,12 @@ int train_pass(msd_ctx* c, int n, const void* visual_d, double* loss3) {
     TRY(head_gemms(c, KV, false, false, R, hd, R, t->S + j * RR, R, sS, Vc, nq, hd, 0.f,
                    t->O + j * hd, qd, sq));
   TRY(train_linear(c, t->O, R, qd, t->o, d, t->X1, t->F));
-  tr_rmsnorm(t->X1, n2, eps, R, d, t->A2, t->r2, st);
+  tr_rmsnorm(t->X1, n2, eps, R, d, t->A2, t->r2, t->xs, st);
   LAUNCHED(c);
-  TRY(train_linear(c, t->A2, R, d, t->gu, 2 * F, t->GU, nullptr));
-  tr_silu(t->GU, R, F, t->Mx, st);
+  TRY(train_linear(c, nullptr, R, d, t->gu, 2 * F, t->GU, nullptr));
+  tr_silu(t->GU, R, F, t->Mx, t->xs, st);
   LAUNCHED(c);
-  TRY(train_linear(c, t->Mx, R, F, t->dn, d, t->D, t->X1));
+  TRY(train_linear(c, nullptr, R, F, t->dn, d, t->D, t->X1));
   // ---- loss: regression toward h_{i+1}, token term against softmax(W_lm h_{i+1})
   tr_reg(t->D, t->H, R, d, t->dD, t->reg, st);
   tr_split(t->D, R, d, t->xs, st);
@@ -1380,16 +1401,13 @@ int train_pass(msd_ctx* c, int n, const void* visual_d, double* loss3) {
   LAUNCHED(c);
   TRY(train_gemm(c, t->xs, R, t->Vp, 3, t->lm_t, d, 1, 0, t->dD, d, t->dD));
   // ---- backward (gradient sums over the rows, into g)
-  TRY(train_wgrad(c, t->dD, d, t->Mx, F, R, g + o[7], add));
-  TRY(train_linear(c, t->dD, R, d, t->dn_t, F, t->dMx, nullptr));
+  TRY(train_back(c, t->dD, d, t->Mx, F, R, g + o[7], add, t->dn_t, t->dMx));
   tr_silu_bwd(t->GU, t->dMx, R, F, t->dGU, st);
   LAUNCHED(c);
-  TRY(train_wgrad(c, t->dGU, 2 * F, t->A2, d, R, g + o[5], add));
-  TRY(train_linear(c, t->dGU, R, 2 * F, t->gu_t, d, t->dA2, nullptr));
+  TRY(train_back(c, t->dGU, 2 * F, t->A2, d, R, g + o[5], add, t->gu_t, t->dA2));
   tr_rmsnorm_bwd(t->X1, n2, t->r2, t->dA2, t->dD, R, d, t->dX1, g + o[9], add, t->gain, st);
   LAUNCHED(c);
-  TRY(train_wgrad(c, t->dX1, d, t->O, qd, R, g + o[4], add));
-  TRY(train_linear(c, t->dX1, R, d, t->o_t, qd, t->dO, nullptr));
+  TRY(train_back(c, t->dX1, d, t->O, qd, R, g + o[4], add, t->o_t, t->dO));
   float *dKc = t->dQKV + qd, *dVc = t->dQKV + qd + kd;
   for (int j = 0; j < Gq; ++j) {
     TRY(head_gemms(c, KV, true, false, R, hd, R, t->S + j * RR, R, sS, t->dO + j * hd, qd, sq,
@@ -1407,12 +1425,11 @@ int train_pass(msd_ctx* c, int n, const void* visual_d, double* loss3) {
   }
   tr_rope(t->dQKV, R, nq, H + KV, hd, c->rope, -1, st);
   LAUNCHED(c);
-  TRY(train_wgrad(c, t->dQKV, nq, t->A1, d, R, g + o[1], add));
-  TRY(train_linear(c, t->dQKV, R, nq, t->qkv_t, d, t->dA1, nullptr));
+  TRY(train_back(c, t->dQKV, nq, t->A1, d, R, g + o[1], add, t->qkv_t, t->dA1));
   tr_rmsnorm_bwd(t->F, n1, t->r1, t->dA1, t->dX1, R, d, t->dF, g + o[8], add, t->gain, st);
   tr_zero_visual(t->dF, c->rows.vis, R, d, st);
   LAUNCHED(c);
-  TRY(train_wgrad(c, t->dF, d, t->X0, 2 * d, R, g + o[0], add));
+  TRY(train_back(c, t->dF, d, t->X0, 2 * d, R, g + o[0], add, {}, nullptr));
   // the rows' loss terms, summed in row order on the host
   std::vector<float> rc(2 * (size_t)R);
   HIPC(c, hipMemcpyAsync(rc.data(), t->reg, sizeof(float) * R, hipMemcpyDeviceToHost, st));
@@ -1965,8 +1982,6 @@ int msd_train_apply(msd_ctx* c, double lr) {
   TrainState* t = c->tr;
   if (!t || t->rows <= 0) return fail(c, MSD_ERR_INVALID_ARG, "no accumulated gradients");
   if (!(lr >= 0.0)) return fail(c, MSD_ERR_INVALID_ARG, "bad learning rate");
-  const msd_model_desc& m = c->m;
-  const int d = m.d_model, F = m.ffn_dim, H = m.n_heads, KV = m.n_kv_heads, hd = m.head_dim;
   const size_t np = t->off[TRAIN_PARAMS];
   t->steps += 1;
   const float c1 = (float)(1.0 - std::pow((double)ADAM_B1, t->steps));
@@ -1974,20 +1989,8 @@ int msd_train_apply(msd_ctx* c, double lr) {
   tr_adamw(t->w, t->g, t->m, t->v, np, (float)(1.0 / t->rows), (float)lr, c1, c2, ADAM_B1, ADAM_B2,
            ADAM_EPS, t->wb, c->st);
   LAUNCHED(c);
-  // the decoder's packed copies (the norm gains it reads from wb directly)
-  const PackedLayer& pl = c->pdlayer;
-  const size_t pq = packed_elems(H * hd, d), pk = packed_elems(KV * hd, d);
-  uint16_t* qkv = const_cast<uint16_t*>(pl.qkv);
-  launch_pack(t->wb + t->off[0], d, 2 * d, const_cast<uint16_t*>(c->fc_p), c->st);
-  launch_pack(t->wb + t->off[1], H * hd, d, qkv, c->st);
-  launch_pack(t->wb + t->off[2], KV * hd, d, qkv + pq, c->st);
-  launch_pack(t->wb + t->off[3], KV * hd, d, qkv + pq + pk, c->st);
-  launch_pack(t->wb + t->off[4], d, H * hd, const_cast<uint16_t*>(pl.o), c->st);
-  launch_pack(t->wb + t->off[5], F, d, const_cast<uint16_t*>(pl.g), c->st);
-  launch_pack(t->wb + t->off[6], F, d, const_cast<uint16_t*>(pl.u), c->st);
-  launch_pack(t->wb + t->off[7], d, F, const_cast<uint16_t*>(pl.d), c->st);
-  TRY(train_pack(c, t));
-  LAUNCHED(c);
+  // with the decoder's packed copies (the norm gains it reads from wb directly)
+  TRY(train_pack(c, t, true));
   t->rows = 0;  // the next sequence's gradients replace g
   HIPC(c, hipStreamSynchronize(c->st));
   return MSD_OK;

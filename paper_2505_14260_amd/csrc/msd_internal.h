@@ -343,13 +343,14 @@ void launch_set_int(int* p, int idx, const int* src, int src_idx, hipStream_t st
 // R = n - 1 rows.
 // visual_feature: visual rows take the target feature (the Visual Feature
 // variant) instead of their embedding
+// xs here and below: the terms of the rows of X0 (of Y, of Mx), as tr_split's
 void tr_inputs(const uint16_t* h, const uint16_t* E, const int* tok, const int* vis_idx,
                const uint16_t* visual, int n, int d, int visual_feature, float* H, float* X0,
-               float* E0, hipStream_t st);
+               float* E0, uint16_t* xs, hipStream_t st);
 void tr_visual_rows(float* F, const float* E0, const int* vis_idx, int R, int d, hipStream_t st);
 void tr_zero_visual(float* dF, const int* vis_idx, int R, int d, hipStream_t st);
 void tr_rmsnorm(const float* X, const float* g, float eps, int R, int d, float* Y, float* rstd,
-                hipStream_t st);
+                uint16_t* xs, hipStream_t st);
 // dX = base + the input gradient, dg = (dg when add) + the gain gradient;
 // scratch: tr_gain_scratch(d) floats
 size_t tr_gain_scratch(int d);
@@ -361,7 +362,7 @@ void tr_rope(float* X, int R, int ld, int nh, int hd, const float2* tab, int dir
 void tr_softmax(float* S, int R, int heads, float scale, hipStream_t st);
 void tr_softmax_bwd(const float* P, float* dP, int R, int heads, float scale, hipStream_t st);
 // GU: rows of 2F, gate then up
-void tr_silu(const float* GU, int R, int F, float* Mx, hipStream_t st);
+void tr_silu(const float* GU, int R, int F, float* Mx, uint16_t* xs, hipStream_t st);
 void tr_silu_bwd(const float* GU, const float* dM, int R, int F, float* dGU, hipStream_t st);
 void tr_reg(const float* D, const float* H, int R, int d, float* dD, float* reg, hipStream_t st);
 // rows of ld floats, V of them logits
@@ -370,15 +371,32 @@ void tr_adamw(float* w, const float* gsum, float* m, float* v, size_t n, float g
               float c1, float c2, float b1, float b2, float eps, uint16_t* wb, hipStream_t st);
 void tr_widen(const uint16_t* src, size_t n, float* dst, hipStream_t st);
 void tr_fill(float* p, size_t n, float v, hipStream_t st);
-// float32 matrices [R][C] (row stride C) as three bf16 terms x = h + m + l:
-// rows [R][3C]; the transpose as rows [C][3 Rp], zero past R; packed planes of
-// the matrix; packed planes of the transpose with K = Rp.  C a multiple of 8,
-// Rp of 8 (tr_split_t and tr_pack_t read R rows).
+// float32 matrices [R][C] (row stride C) as three bf16 terms x = h + m + l: rows
+// [R][3C] (C a multiple of 8)
 void tr_split(const float* src, int R, int C, uint16_t* dst, hipStream_t st);
-void tr_split_t(const float* src, int R, int C, int Rp, uint16_t* dst, hipStream_t st);
-void tr_pack(const float* src, int R, int C, uint16_t* dst, size_t plane, hipStream_t st);
-void tr_pack_t(const float* src, int R, int C, int Rp, uint16_t* dst, size_t plane,
-               hipStream_t st);
+// Operands of the gradients of Y = A W^T, dY [R][N] and A [R][K]: dyt, dY's
+// transpose as rows [N][3 Rp], zero past R; at, packed planes of A's transpose
+// (K rows of Rp); dy, rows of dY, when not null.  N and K multiples of 8, Rp of 64.
+void tr_operands(const float* dY, const float* A, int R, int N, int K, int Rp, uint16_t* dyt,
+                 uint16_t* at, size_t plane, uint16_t* dy, hipStream_t st);
+// Matrices to pack in one launch: planes of the terms of src [R][C], or of its
+// transpose (R a multiple of 8), or src16 as it is (one plane).
+struct PackJob {
+  const float* src;
+  const uint16_t* src16;
+  int R, C;
+  uint16_t* dst;
+  size_t plane;
+  int first;  // first workgroup
+};
+struct PackJobs {
+  PackJob job[16];
+  int n = 0, wgs = 0;
+  void add(const float* src, const uint16_t* src16, int R, int C, uint16_t* dst, size_t plane,
+           bool transposed = false);
+};
+void tr_pack(const PackJobs& j, hipStream_t st);
+void tr_pack_t(const PackJobs& j, hipStream_t st);
 // the transpose of a row-major bf16 matrix [R][C], packed (one plane)
 void tr_pack_t16(const uint16_t* src, int R, int C, int Rp, uint16_t* dst, hipStream_t st);
 
