@@ -203,7 +203,7 @@ int msd_set_draft_input(msd_ctx* ctx, int visual_input);
  * its weights (msd_train_accumulate).  enable != 0: its output, gate, up and down
  * products read the row-major matrices given to msd_create (wo, w_gate, w_up and
  * w_down of every target layer) in place, instead of first unpacking each packed
- * copy (a 640-row LLaVA-1.5-7B-shaped training step: 32.2 -> 28.4 ms).  Those
+ * copy (a 640-row LLaVA-1.5-7B-shaped training step: 3.8 ms less).  Those
  * matrices must then stay valid and unchanged until msd_destroy or a call with
  * enable = 0.  Results equal the default path's bit for bit: the same products
  * on the same values.  Every other call reads the packed copies only and is not
